@@ -51,9 +51,10 @@ extern "C" {
 /* ---- return codes -------------------------------------------------------- */
 #define MAGX_OK          0
 #define MAGX_EINVAL     -1   /* null pointer, non-positive size or spacing, bad flag, DMI without exchange */
-#define MAGX_ESIZE      -2   /* n > 4096 on an axis, or an extended-grid length P = next power of two
-                                >= 2n exceeds the FFT passes' limits: Py <= 4096; Px <= 4096 (float)
-                                or 2048 (double); Pz <= 1024 */
+#define MAGX_ESIZE      -2   /* n > 4096 on an axis, or the next power of two P >= 2n exceeds the FFT
+                                passes' limits: Py <= 4096; Px <= 4096 (float) or 2048 (double);
+                                Pz <= 1024.  (From 2^16 cells on the extended lengths along x and y
+                                may be 5/8 or 3/4 of that power of two; the limits stay.) */
 #define MAGX_EDTYPE     -3   /* unknown element type */
 #define MAGX_EWORKSPACE -4   /* magx_step_static: the grid needs more than its fixed workspace;
                                 elsewhere buffer sizes are the caller's contract (see magx_sizes) */

@@ -2,20 +2,27 @@
 
     python -m paper_2602_12242_amd.build          # or build() from Python
 
-Every HIP source and the C-ABI host file are compiled in one hipcc call.
-Packed-FP32 instructions are disabled for the device code.  The sign of a
-zero result is not significant anywhere in the library, so x + 0 may fold to
-x (the zero-padded halves of the first FFT passes then cost no arithmetic).
+Every source is compiled by itself, in parallel; conv.hip and pencil.hip
+once per element type (MAGX_REAL = 32 or 64).  Packed-FP32 instructions are
+disabled for the device code.  The sign of a zero result is not significant
+anywhere in the library, so x + 0 may fold to x (the zero-padded halves of the
+first FFT passes then cost no arithmetic).
 """
 import os
 import subprocess
 import sys
+import tempfile
+from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(os.path.dirname(HERE), "include")
 LIB = os.path.join(HERE, "libmagx.so")
-SOURCES = ["magx_api.cpp", "tensor.hip", "conv.hip", "pencil.hip", "mri.hip"]
+# (source, element types it is compiled for; None: once)
+SOURCES = [("pencil.hip", (64, 32)), ("conv.hip", (64, 32)), ("mri.hip", (None,)), ("tensor.hip", (None,)),
+           ("magx_api.cpp", (None,))]
+FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Xclang", "-target-feature", "-Xclang",
+         "-packed-fp32-ops", "-fno-signed-zeros", "-Wno-unused-command-line-argument", "-I", INCLUDE]
 
 
 def hipcc():
@@ -23,26 +30,29 @@ def hipcc():
     return os.path.join(rocm, "bin", "hipcc")
 
 
-def build(verbose=False):
-    srcs = [os.path.join(CSRC, s) for s in SOURCES]
-    tmp = LIB + ".tmp"
-    cmd = [hipcc(), "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared", "-fgpu-rdc", "--hip-link",
-           "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-fno-signed-zeros",
-           "-Wno-unused-command-line-argument",
-           "-I", INCLUDE, "-o", tmp] + [("-x", "hip", s) if s.endswith(".hip") else ("-x", "hip", s) for s in srcs]
-    flat = []
-    for c in cmd:
-        if isinstance(c, tuple):
-            flat.extend(c)
-        else:
-            flat.append(c)
+def _run(cmd, verbose):
     if verbose:
-        print(" ".join(flat), flush=True)
-    res = subprocess.run(flat, capture_output=True, text=True)
+        print(" ".join(cmd), flush=True)
+    res = subprocess.run(cmd, capture_output=True, text=True)
     if res.returncode != 0:
         sys.stderr.write(res.stdout + res.stderr)
         raise RuntimeError("hipcc failed building libmagx.so")
-    os.replace(tmp, LIB)
+
+
+def build(verbose=False):
+    with tempfile.TemporaryDirectory() as tmp:
+        jobs, objs = [], []
+        for src, reals in SOURCES:
+            for real in reals:
+                obj = os.path.join(tmp, f"{os.path.splitext(src)[0]}{real or ''}.o")
+                define = [f"-DMAGX_REAL={real}"] if real else []
+                jobs.append([hipcc(), *FLAGS, *define, "-x", "hip", "-c", os.path.join(CSRC, src), "-o", obj])
+                objs.append(obj)
+        with ThreadPoolExecutor(len(jobs)) as pool:
+            list(pool.map(lambda c: _run(c, verbose), jobs))
+        out = LIB + ".tmp"
+        _run([hipcc(), "--offload-arch=gfx950", "-fPIC", "-shared", "-o", out, *objs], verbose)
+    os.replace(out, LIB)
     return LIB
 
 

@@ -19,9 +19,10 @@ template <bool BIG> constexpr int maxslot() { return BIG ? 8 : 4; }
 
 struct PG {
     int nx, ny, nz, Lh, lgLh, Hx, Sx, lgPx, np, npen_total;   // npen_total: pencils of one member
-    // log2 of the cell-pair slots per line, max(Lh/2, 1): the cells fill the
-    // lower half of a packed line (x < nx <= Px/2); the upper half is the zero
-    // padding, which the forward pass never reads and nothing writes
+    // log2 of the cell-pair slots per line (of their power-of-two factor, see
+    // slot_of), max(Lh/2, 1): the cells fill the lower half of a packed line
+    // (x < nx <= Px/2); the upper half is the zero padding, which the forward
+    // pass never reads and nothing writes
     int lgLq;
     int bpm;                                                 // blocks per member
     int zmajor;                                              // block order: z fastest (see block_pencils)
@@ -35,29 +36,56 @@ struct PG {
 inline size_t pencil_lds(const Plan& pl) { return (size_t)3 * pl.np * pl.Lh * pl.esize * 2; }
 inline bool pencil_big(const Plan& pl) { return pl.np * pl.Lh > 1024; }
 
-// Compile-time line geometry: for a power-of-two line nx = Lh = 2^LG (so
-// Px = 2 nx, Hx = Lh + 1, Sx = Lh + 16) the kernels are instantiated with the
-// sizes as constants, which turns the FFT strides and row offsets into
-// immediates; LG = 0 keeps them runtime values.
-constexpr int kPencilLgMin = 7, kPencilLgMax = 10;
+// Compile-time line geometry: the kernels are instantiated with the transform
+// length LN = Lh (a multiple of 16, so Hx = LN + 1, Sx = LN + 16) as a constant
+// for the lengths with an odd factor, and for the power-of-two lines 128 ... 1024
+// of grids with nx = Lh, where nx is a constant too; that turns the FFT strides
+// and row offsets into immediates.  LN = 0 keeps runtime values (powers of two).
+constexpr bool pencil_exact(int LN) { return LN > 0 && odd_part(LN) == 1; }
 
-inline int pencil_lg(const Plan& pl) {
-    if (pl.nx != pl.Lh || pl.lgLh < kPencilLgMin || pl.lgLh > kPencilLgMax || pl.Sx != pl.Lh + 16 ||
-        pl.np * pl.Lh > 1024)
-        return 0;
-    return pl.lgLh;
+inline int pencil_line(const Plan& pl) {
+    if (pl.np * pl.Lh > 1024) return 0;
+    if (odd_part(pl.Lh) > 1) return pl.Lh;
+    return pl.nx == pl.Lh && pl.Lh >= 128 && pl.Lh <= 1024 ? pl.Lh : 0;
 }
 
-template <int LG>
+template <int LN>
 __device__ __forceinline__ void pg_fix(PG& g) {
-    if constexpr (LG > 0) {
-        g.lgLh = LG;
-        g.lgLq = LG - 1;
-        g.Lh = 1 << LG;
-        g.lgPx = LG + 1;
-        g.nx = 1 << LG;
-        g.Hx = (1 << LG) + 1;
-        g.Sx = (1 << LG) + 16;
+    if constexpr (LN > 0) {
+        constexpr int lg = ilog2c(LN / odd_part(LN));
+        g.lgLh = lg;
+        g.lgLq = lg - 1;
+        g.Lh = LN;
+        g.lgPx = lg + 1;
+        if (pencil_exact(LN)) g.nx = LN;
+        g.Hx = LN + 1;
+        g.Sx = LN + 16;
+    }
+}
+
+// Cases of a launch switch over the line length: the lengths with an odd factor.
+#define MAGX_ODD_LINES(KERNEL, LDS, ...)                                                                  \
+    case 80: hipLaunchKernelGGL((KERNEL<R, false, 80>), grid_, block_, LDS, s, __VA_ARGS__); break;      \
+    case 96: hipLaunchKernelGGL((KERNEL<R, false, 96>), grid_, block_, LDS, s, __VA_ARGS__); break;      \
+    case 160: hipLaunchKernelGGL((KERNEL<R, false, 160>), grid_, block_, LDS, s, __VA_ARGS__); break;    \
+    case 192: hipLaunchKernelGGL((KERNEL<R, false, 192>), grid_, block_, LDS, s, __VA_ARGS__); break;    \
+    case 320: hipLaunchKernelGGL((KERNEL<R, false, 320>), grid_, block_, LDS, s, __VA_ARGS__); break;    \
+    case 384: hipLaunchKernelGGL((KERNEL<R, false, 384>), grid_, block_, LDS, s, __VA_ARGS__); break;    \
+    case 640: hipLaunchKernelGGL((KERNEL<R, false, 640>), grid_, block_, LDS, s, __VA_ARGS__); break;    \
+    case 768: hipLaunchKernelGGL((KERNEL<R, false, 768>), grid_, block_, LDS, s, __VA_ARGS__); break;
+
+// Cell-pair slots of npen lines (Lh/2 each) and the line p and pair n of slot e.
+template <int LN> constexpr int line_odd() { return LN > 0 ? odd_part(LN) : 1; }
+template <int LN> __device__ __forceinline__ int slots_of(const PG& g, int npen) {
+    return line_odd<LN>() > 1 ? npen * (LN / 2) : npen << g.lgLq;
+}
+template <int LN> __device__ __forceinline__ void slot_of(const PG& g, int e, int& p, int& n) {
+    if constexpr (line_odd<LN>() > 1) {
+        p = (int)((unsigned)e / (unsigned)(LN / 2));
+        n = e - p * (LN / 2);
+    } else {
+        p = e >> g.lgLq;
+        n = e & ((1 << g.lgLq) - 1);
     }
 }
 
@@ -437,19 +465,20 @@ template <int V> struct IntC { static constexpr int value = V; };
 // of line l is buf[l*Lh + x/2].x (x even) or .y (x odd).  Split step of the
 // half-length inverse, Z[k] = (X[k] + X*[Lh-k]) + i (X[k] - X*[Lh-k]) w^-k
 // (w^-k = conj(W^k)), into LDS; then the inverse FFT of every line in LDS.
-template <typename R, bool BIG>
+template <typename R, bool BIG, int LN>
 __device__ void c2r_lines(cx<R>* buf, const cx<R>* Y1, const PG& g, int mb, int pen0, int npen) {
+    constexpr int ODD = line_odd<LN>();
     const int Lh = g.Lh;
     const int lgq = g.lgLh > 0 ? g.lgLh - 1 : 0;
-    const int twsh = kTwLog - g.lgPx;
+    const int twsh = tw_log(ODD) - g.lgPx;
     auto split = [](cx<R> a, cx<R> b, cx<R> wc) {   // a = X[k], b = X[Lh-k], wc = conj(W^k)
         const cx<R> bc = cconj<R>(b);
         const cx<R> A = cadd<R>(a, bc);
         const cx<R> B = cmul<R>(csub<R>(a, bc), wc);
         return mk<R>(A.x - B.y, A.y + B.x);
     };
-    tw_lds_fill<R>();   // pass twiddles, read after the barrier below
-    if ((1 << lgq) >= kNT) {
+    tw_lds_fill<R, ODD>();   // pass twiddles, read after the barrier below
+    if (ODD == 1 && (1 << lgq) >= kNT) {
         // at least one item per thread and line: thread tid takes items
         // t = tid + k kNT of every line, so its twiddles are the same for all
         // lines and each line's row address is uniform (scalar registers).
@@ -506,28 +535,37 @@ __device__ void c2r_lines(cx<R>* buf, const cx<R>* Y1, const PG& g, int mb, int 
     } else {
     // items in chunks of kXIt per thread: all loads of a chunk are issued
     // before any is used (no load behind a branch or a loop-carried wait)
-    const int count = (npen * 3) << lgq;
+    const int count = slots_of<LN>(g, npen * 3);
     for (int base = 0; base < count; base += kXIt * kNT) {
         cx<R> A[kXIt], B[kXIt], C[kXIt], W[kXIt];
         const int wave0 = base + ((int)threadIdx.x & ~63);
 #pragma unroll
         for (int i = 0; i < kXIt; ++i) {
             const int e = min(base + (int)threadIdx.x + i * kNT, count - 1);
-            const int line = e >> lgq, t = e & ((1 << lgq) - 1);
+            int line, t;
+            slot_of<LN>(g, e, line, t);
             const int p = line / 3, c = line - 3 * p;
             const cx<R>* row = Y1 + x_row(g, mb, c, pen0 + p);
             A[i] = row[t];
             B[i] = row[Lh - t];
-            W[i] = tw_fwd<R>(t << twsh);
+            W[i] = tw_fwd<R, ODD>(t << twsh);
             C[i] = mk<R>((R)0, (R)0);
             // X[Lh/2] for item 0 of a line, loaded only by waves holding such an item
-            if (lgq < 6 || ((wave0 + i * kNT) & ((1 << lgq) - 1)) == 0) C[i] = row[t == 0 ? (Lh >> 1) : t];
+            bool has0;
+            if constexpr (ODD > 1) {
+                const unsigned w = (unsigned)(wave0 + i * kNT) % (unsigned)(LN / 2);
+                has0 = w == 0 || w + 64u > (unsigned)(LN / 2);
+            } else {
+                has0 = lgq < 6 || ((wave0 + i * kNT) & ((1 << lgq) - 1)) == 0;
+            }
+            if (has0) C[i] = row[t == 0 ? (Lh >> 1) : t];
         }
 #pragma unroll
         for (int i = 0; i < kXIt; ++i) {
             const int e = base + (int)threadIdx.x + i * kNT;
             if (e >= count) break;
-            const int line = e >> lgq, t = e & ((1 << lgq) - 1);
+            int line, t;
+            slot_of<LN>(g, e, line, t);
             cx<R>* out = buf + line * Lh;
             if (t == 0) {
                 out[0] = split(A[i], B[i], mk<R>((R)1, (R)0));
@@ -543,7 +581,7 @@ __device__ void c2r_lines(cx<R>* buf, const cx<R>* Y1, const PG& g, int mb, int 
     __syncthreads();
     auto none_load = [&](int, int) -> cx<R> { return mk<R>(0, 0); };
     auto none_store = [&](int, int, cx<R>) {};
-    fft_io<R, true, pemax<BIG>(), true, true, kLines, 1, false, true, lgmax<pemax<BIG>()>(), kNT, true>(
+    fft_io<R, true, pemax<BIG>(), true, true, kLines, 1, false, true, lgmax<pemax<BIG>()>(), kNT, true, ODD>(
         buf, g.lgLh, 0, npen * 3, none_load, none_store);
 }
 
@@ -551,19 +589,20 @@ __device__ void c2r_lines(cx<R>* buf, const cx<R>* Y1, const PG& g, int mb, int 
 // Hx-column half spectrum of every line to X1.  Merge step: with P = Z[k],
 // Q = Z[Lh-k], E = (P + Q*)/2, O = (P - Q*)/(2i) and T = W^k O,
 // X[k] = E + T and X[Lh-k] = (E - T)*.
-template <typename R, bool BIG>
+template <typename R, bool BIG, int LN>
 __device__ void r2c_lines(cx<R>* buf, cx<R>* X1, const PG& g, int mb, int pen0, int npen) {
+    constexpr int ODD = line_odd<LN>();
     const int Lh = g.Lh;
     const int lgq = g.lgLh > 0 ? g.lgLh - 1 : 0;
-    const int twsh = kTwLog - g.lgPx;
+    const int twsh = tw_log(ODD) - g.lgPx;
     auto none_load = [&](int, int) -> cx<R> { return mk<R>(0, 0); };
     auto none_store = [&](int, int, cx<R>) {};
-    tw_lds_fill<R>();   // pass twiddles (same values if c2r_lines filled them)
+    tw_lds_fill<R, ODD>();   // pass twiddles (same values if c2r_lines filled them)
     __syncthreads();
-    fft_io<R, false, pemax<BIG>(), true, true, kLines, 1, true, false, lgmax<pemax<BIG>()>(), kNT, true>(
+    fft_io<R, false, pemax<BIG>(), true, true, kLines, 1, true, false, lgmax<pemax<BIG>()>(), kNT, true, ODD>(
         buf, g.lgLh, 0, npen * 3, none_load, none_store);
     const R half = (R)0.5;
-    if ((1 << lgq) >= kNT) {
+    if (ODD == 1 && (1 << lgq) >= kNT) {
         // as in the split step: fixed items t = tid + k kNT of every line,
         // uniform row addresses
         auto lines = [&](auto ipl_c) {
@@ -600,19 +639,22 @@ __device__ void r2c_lines(cx<R>* buf, cx<R>* X1, const PG& g, int mb, int pen0, 
         else lines(IntC<4>{});
         return;
     }
-    const int count = (npen * 3) << lgq;
+    const int count = slots_of<LN>(g, npen * 3);
     for (int base = 0; base < count; base += kXIt * kNT) {
         cx<R> W[kXIt];
 #pragma unroll
         for (int i = 0; i < kXIt; ++i) {
             const int e = min(base + (int)threadIdx.x + i * kNT, count - 1);
-            W[i] = tw_fwd<R>((e & ((1 << lgq) - 1)) << twsh);
+            int line, t;
+            slot_of<LN>(g, e, line, t);
+            W[i] = tw_fwd<R, ODD>(t << twsh);
         }
 #pragma unroll
         for (int i = 0; i < kXIt; ++i) {
             const int e = base + (int)threadIdx.x + i * kNT;
             if (e >= count) break;
-            const int line = e >> lgq, t = e & ((1 << lgq) - 1);
+            int line, t;
+            slot_of<LN>(g, e, line, t);
             const int p = line / 3, c = line - 3 * p;
             cx<R>* row = X1 + x_row(g, mb, c, pen0 + p);
             const cx<R>* in = buf + line * Lh;

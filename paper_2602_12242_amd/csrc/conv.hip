@@ -27,11 +27,18 @@ namespace magx {
 // EM: FFT elements held per thread (T * L <= kNT * EM); 16 or 32.
 //
 // Every kernel is persistent: the launch has as many blocks as can be
-// resident, and block lb walks the contiguous tile range
-// [ntiles*lb/G, ntiles*(lb+1)/G) (logical blocks of one XCD are contiguous,
-// so neighbouring tiles share its L2).  The first FFT pass of a tile takes its
+// resident, and a block walks the contiguous tile range of its share (logical
+// blocks of one XCD are contiguous, so neighbouring tiles share its L2).  The first FFT pass of a tile takes its
 // inputs from registers, and right after it the next tile's inputs are
 // requested, so the loads of tile t+1 are in flight while tile t finishes.
+
+// Range [u0, u1) of n units that share pr of npairs takes (32-bit arithmetic;
+// the shares differ by at most one unit).
+__device__ __forceinline__ void share_range(int n, int npairs, int pr, int& u0, int& u1) {
+    const int q = n / npairs, r = n - q * npairs;
+    u0 = q * pr + min(pr, r);
+    u1 = u0 + q + (pr < r ? 1 : 0);
+}
 
 // Walk of a block of a pair over the y-pass tiles (plane, tx): units are
 // (plane, txp) with txp = tx / 2; a pair of blocks (adjacent logical indices,
@@ -39,52 +46,70 @@ namespace magx {
 // column tile 2 txp / 2 txp + 1 (skipped when past the last tile).
 struct PairWalk {
     int ntx, ntxp, side, u0, u1;
-    __device__ PairWalk(int ntiles, int ntx_) : ntx(ntx_) {
+    // (force-inlined: as a call, the walk lives in scratch memory and its
+    // uniform values in vector registers)
+    __device__ __forceinline__ PairWalk(int ntiles, int ntx_) : ntx(ntx_) {
         ntxp = (ntx + 1) >> 1;
         const int lbp = xcd_logical_block(blockIdx.x, gridDim.x);
         side = lbp & 1;
-        const int npairs = gridDim.x >> 1, pr = lbp >> 1;
-        const long long nunits = (long long)(ntiles / ntx) * ntxp;
-        u0 = (int)(nunits * pr / npairs);
-        u1 = (int)(nunits * (pr + 1) / npairs);
+        share_range((ntiles / ntx) * ntxp, gridDim.x >> 1, lbp >> 1, u0, u1);
     }
-    __device__ bool valid(int u) const { return 2 * (u % ntxp) + side < ntx; }
-    __device__ int first() const {
-        int u = u0;
-        while (u < u1 && !valid(u)) ++u;
-        return u;
-    }
-    __device__ int next(int u) const {
-        ++u;
-        while (u < u1 && !valid(u)) ++u;
-        return u;
-    }
-    __device__ int tile(int u) const { return (u / ntxp) * ntx + 2 * (u % ntxp) + side; }
+    __device__ __forceinline__ bool valid(int u) const { return 2 * (u % ntxp) + side < ntx; }
+    // the next valid unit from u on (at most every ntxp-th one is not)
+    __device__ __forceinline__ int skip(int u) const { return u < u1 && !valid(u) ? (ntxp > 1 ? u + 1 : u1) : u; }
+    __device__ __forceinline__ int first() const { return skip(u0); }
+    __device__ __forceinline__ int next(int u) const { return skip(u + 1); }
+    __device__ __forceinline__ int tile(int u) const { return (u / ntxp) * ntx + 2 * (u % ntxp) + side; }
 };
 
-// Compile-time geometry of the y passes for square power-of-two grids,
-// nx = ny = 2^(LG-1) (Px = Py = 2^LG): every size of the pass (row stride,
-// tile width, tile count) becomes a constant, so the FFT strides and row
-// offsets are immediates.  LG = 0 keeps runtime sizes.  The tile width is the
-// plan's, ty = min(16, budget / Py) with a budget of 2^14 complex values in
-// single precision and in double precision 2^13 for Py >= 1024, 2^12 below
-// (128 KiB and 64 KiB of LDS; at Py = 512 the smaller tile measured faster).
-template <typename R> constexpr int ytile_lg(int LG) {
-    constexpr int lgb = sizeof(R) == 4 ? 14 : 13;
-    if constexpr (sizeof(R) == 8) {
-        if (LG <= 9) return LG >= 8 ? 12 - LG : 4;
-    }
-    return LG >= lgb - 4 ? lgb - LG : 4;
-}
+// Configuration of the y passes of one length PY = ODD 2^k: tile width T (the
+// plan's ty: at most 16 columns, a budget of 2^14 complex values in single
+// precision and in double precision 2^13, 2^12 for PY <= 512, where the
+// smaller tile measured faster), threads per block NT, FFT elements per thread
+// EM and log2 of the largest radix.  The length is a compile-time constant for
+// PY >= 128 (PY = 0 keeps runtime sizes, powers of two up to 64), so the pass
+// plan is straight-line code: with a runtime length the switch over the first
+// radix spilled 69-101 scalar registers into scratch memory.  Lengths with an
+// odd factor take a thread count that divides their butterflies evenly
+// (radices 4 8 5 at 160, 8 8 x at 192 and 320, 8 16 x at 384 and 640, 16 16 3 at 768).
+template <typename R, int PY> struct YCfg {
+    static constexpr bool F = sizeof(R) == 4;
+    static constexpr int ODD = PY ? odd_part(PY) : 1;
+    static constexpr int LG = PY ? ilog2c(PY / ODD) : 0;          // log2 of the power-of-two factor
+    static constexpr int BUDGET = F ? 16384 : (PY <= 512 ? 4096 : 8192);
+    static constexpr int T = PY ? (BUDGET / PY >= 16 ? 16 : 1 << ilog2c(BUDGET / PY)) : 0;
+    static constexpr int NE = PY * T;
+    static constexpr int NT = PY == 0     ? kNT
+                              : ODD == 1  ? (NE > kNT * (F ? 32 : 16) ? 512 : kNT)
+                              : PY == 160 ? 320
+                              : PY == 192 ? 384
+                              : PY == 320 ? 320
+                              : PY == 384 ? (F ? 384 : kNT)
+                              : PY == 640 ? 640
+                                          : (F ? 768 : 384);
+    static constexpr int EM = PY == 0     ? 16
+                              : ODD == 1  ? (F && NE > kNT * 16 ? 32 : 16)
+                              : PY == 160 ? 10
+                              : PY == 192 ? 9
+                              : PY == 320 ? (F ? 20 : 10)
+                              : PY == 384 ? (F ? 18 : 16)
+                              : PY == 640 ? (F ? 20 : 16)
+                                          : 18;
+    static constexpr int LGM = ODD == 1 ? lgmax<EM>() : (LG >= 7 ? 4 : 3);
+};
 
-template <typename R, int LG>
+// Compile-time sizes of a y pass.  SQ: square power-of-two grids nx = ny = PY/2
+// (Px = Py): the row stride and the tile count are constants as well.
+template <typename R, int PY, bool SQ>
 __device__ __forceinline__ void ygeom_fix(int& ny, int& lgPy, int& Hx, int& Sx, int& lgT, int& ntx) {
-    if constexpr (LG > 0) {
-        ny = 1 << (LG - 1);
-        lgPy = LG;
-        Hx = (1 << (LG - 1)) + 1;
-        Sx = (1 << (LG - 1)) + 16;
-        lgT = ytile_lg<R>(LG);
+    if constexpr (PY > 0) {
+        lgPy = YCfg<R, PY>::LG;
+        lgT = ilog2c(YCfg<R, PY>::T);
+    }
+    if constexpr (SQ) {
+        ny = PY / 2;
+        Hx = PY / 2 + 1;
+        Sx = PY / 2 + 16;
         ntx = (Hx + (1 << lgT) - 1) >> lgT;
     }
 }
@@ -106,15 +131,17 @@ __device__ __forceinline__ unsigned nyq_pack(int ky, int Py, unsigned Sx) {
     return (unsigned)prow * Sx + (unsigned)(q & 15);
 }
 
-template <typename R, int EM, int NT, int LG>
-__global__ void __launch_bounds__(NT) yfwd_kernel(const cx<R>* __restrict__ X1, cx<R>* __restrict__ X2, int ny,
-                                                  int lgPy, int Hx, int Sx, int lgT, int ntx, int ntiles, int nyq) {
-    ygeom_fix<R, LG>(ny, lgPy, Hx, Sx, lgT, ntx);
-    tw_lds_fill<R>();   // read by the second pass, after the first barrier
+template <typename R, int PY, bool SQ>
+__global__ void __launch_bounds__((YCfg<R, PY>::NT))
+    yfwd_kernel(const cx<R>* __restrict__ X1, cx<R>* __restrict__ X2, int ny, int lgPy, int Hx, int Sx, int lgT,
+                int ntx, int ntiles, int nyq) {
+    constexpr int EM = YCfg<R, PY>::EM, NT = YCfg<R, PY>::NT, LGM = YCfg<R, PY>::LGM, ODD = YCfg<R, PY>::ODD;
+    ygeom_fix<R, PY, SQ>(ny, lgPy, Hx, Sx, lgT, ntx);
+    tw_lds_fill<R, ODD>();   // read by the second pass, after the first barrier
     extern __shared__ unsigned char smem_raw[];
     cx<R>* buf = reinterpret_cast<cx<R>*>(smem_raw);
     const int T = 1 << lgT;
-    const int Py = 1 << lgPy;
+    const int Py = ODD << lgPy;
     // block pairs: unit u = (plane, column-tile pair); the even block of a pair
     // takes column tile 2 txp, the odd one 2 txp + 1, at the same time, so the
     // two halves of every 128-byte row segment are requested together
@@ -134,7 +161,7 @@ __global__ void __launch_bounds__(NT) yfwd_kernel(const cx<R>* __restrict__ X1, 
     };
     FirstIn<R, EM, true> in;
     int u = pw.first();
-    if (u < pw.u1) first_load<R, EM, kCols, 1, true, lgmax<EM>(), NT>(in, lgPy, lgT, T, loader(pw.tile(u)));
+    if (u < pw.u1) first_load<R, EM, kCols, 1, true, LGM, NT, ODD>(in, lgPy, lgT, T, loader(pw.tile(u)));
     while (u < pw.u1) {
         const int un = pw.next(u);
         const int t = pw.tile(u);
@@ -153,23 +180,25 @@ __global__ void __launch_bounds__(NT) yfwd_kernel(const cx<R>* __restrict__ X1, 
         };
         auto next = [&]() {
             if (un < pw.u1)
-                first_load<R, EM, kCols, 1, true, lgmax<EM>(), NT>(in, lgPy, lgT, T, loader(pw.tile(un)));
+                first_load<R, EM, kCols, 1, true, LGM, NT, ODD>(in, lgPy, lgT, T, loader(pw.tile(un)));
         };
-        fft_reg<R, false, EM, false, kCols, 1, true, false, lgmax<EM>(), NT, true>(buf, lgPy, lgT, T, in, next, store);
+        fft_reg<R, false, EM, false, kCols, 1, true, false, LGM, NT, true, ODD>(buf, lgPy, lgT, T, in, next, store);
         __syncthreads();   // the last pass read LDS; the next tile's first pass writes it
         u = un;
     }
 }
 
-template <typename R, int EM, int NT, int LG>
-__global__ void __launch_bounds__(NT) yinv_kernel(const cx<R>* __restrict__ X2, cx<R>* __restrict__ Y1, int ny,
-                                                  int lgPy, int Hx, int Sx, int lgT, int ntx, int ntiles, int nyq) {
-    ygeom_fix<R, LG>(ny, lgPy, Hx, Sx, lgT, ntx);
-    tw_lds_fill<R>();   // read by the second pass, after the first barrier
+template <typename R, int PY, bool SQ>
+__global__ void __launch_bounds__((YCfg<R, PY>::NT))
+    yinv_kernel(const cx<R>* __restrict__ X2, cx<R>* __restrict__ Y1, int ny, int lgPy, int Hx, int Sx, int lgT,
+                int ntx, int ntiles, int nyq) {
+    constexpr int EM = YCfg<R, PY>::EM, NT = YCfg<R, PY>::NT, LGM = YCfg<R, PY>::LGM, ODD = YCfg<R, PY>::ODD;
+    ygeom_fix<R, PY, SQ>(ny, lgPy, Hx, Sx, lgT, ntx);
+    tw_lds_fill<R, ODD>();   // read by the second pass, after the first barrier
     extern __shared__ unsigned char smem_raw[];
     cx<R>* buf = reinterpret_cast<cx<R>*>(smem_raw);
     const int T = 1 << lgT;
-    const int Py = 1 << lgPy;
+    const int Py = ODD << lgPy;
     const PairWalk pw(ntiles, ntx);
     auto loader = [=](int t) {
         const int tx = t % ntx;
@@ -188,7 +217,7 @@ __global__ void __launch_bounds__(NT) yinv_kernel(const cx<R>* __restrict__ X2, 
     };
     FirstIn<R, EM, false> in;
     int u = pw.first();
-    if (u < pw.u1) first_load<R, EM, kCols, 1, false, lgmax<EM>(), NT>(in, lgPy, lgT, T, loader(pw.tile(u)));
+    if (u < pw.u1) first_load<R, EM, kCols, 1, false, LGM, NT, ODD>(in, lgPy, lgT, T, loader(pw.tile(u)));
     while (u < pw.u1) {
         const int un = pw.next(u);
         const int t = pw.tile(u);
@@ -203,9 +232,9 @@ __global__ void __launch_bounds__(NT) yinv_kernel(const cx<R>* __restrict__ X2, 
         };
         auto next = [&]() {
             if (un < pw.u1)
-                first_load<R, EM, kCols, 1, false, lgmax<EM>(), NT>(in, lgPy, lgT, T, loader(pw.tile(un)));
+                first_load<R, EM, kCols, 1, false, LGM, NT, ODD>(in, lgPy, lgT, T, loader(pw.tile(un)));
         };
-        fft_reg<R, true, EM, false, kCols, 1, false, true, lgmax<EM>(), NT, true>(buf, lgPy, lgT, T, in, next, store);
+        fft_reg<R, true, EM, false, kCols, 1, false, true, LGM, NT, true, ODD>(buf, lgPy, lgT, T, in, next, store);
         __syncthreads();
         u = un;
     }
@@ -433,8 +462,8 @@ __global__ void __launch_bounds__(kNT) zconv_kernel(cx<R>* __restrict__ X2, cons
     // unit range of this block's pair
     const int npairs = gridDim.x >> 1;
     const int pr = lbp >> 1;
-    const int t0 = (int)((long long)nunits * pr / npairs);
-    const int t1 = (int)((long long)nunits * (pr + 1) / npairs);
+    int t0, t1;
+    share_range(nunits, npairs, pr, t0, t1);
     FirstIn<R, EM, true> in;
     if (t0 < t1) {
         first_load<R, EM, kCols, 3, true, 3>(in, lgPz, lgT, T3, loader(t0));
@@ -846,8 +875,8 @@ __global__ void __launch_bounds__(256) zconvr128_kernel(cx<R>* __restrict__ X2, 
     };
     const int npairs = gridDim.x >> 1;
     const int pr = lbp >> 1;
-    const int t0 = (int)((long long)nunits * pr / npairs);
-    const int t1 = (int)((long long)nunits * (pr + 1) / npairs);
+    int t0, t1;
+    share_range(nunits, npairs, pr, t0, t1);
     if (t0 < t1) {
         tensor_copy(t0);
         load_tile(t0);
@@ -1062,8 +1091,8 @@ __global__ void __launch_bounds__(ZD<P>::NT)
     };
     const int npairs = gridDim.x >> 1;
     const int pr = lbp >> 1;
-    const int t0 = (int)((long long)nunits * pr / npairs);
-    const int t1 = (int)((long long)nunits * (pr + 1) / npairs);
+    int t0, t1;
+    share_range(nunits, npairs, pr, t0, t1);
     if (t0 < t1) {
         tensor_copy(t0);
         load_tile(t0);
@@ -1212,32 +1241,38 @@ static int pair_grid(int resident, long long nunits) {
     return (int)g;
 }
 
-template <typename R, int EM, int NT, int LG = 0>
+template <typename R, int PY, bool SQ = false>
 static hipError_t run_yfwd(const Plan& pl, const void* X1, void* X2, hipStream_t s) {
+    constexpr int NT = YCfg<R, PY>::NT;
+    if (PY ? (pl.Py != PY || pl.ty != YCfg<R, PY>::T) : (pl.Py * pl.ty > NT * YCfg<R, 0>::EM))
+        return hipErrorInvalidValue;
     const int lgT = ilog2(pl.ty);
     const int ntx = (pl.Hx + pl.ty - 1) / pl.ty;
     const int ntiles = ntx * 3 * pl.nz * pl.nbatch;
     const size_t lds = (size_t)pl.Py * pl.ty * sizeof(cx<R>);
-    const int grid = pair_grid(persistent_grid(reinterpret_cast<const void*>(&yfwd_kernel<R, EM, NT, LG>), lds,
+    const int grid = pair_grid(persistent_grid(reinterpret_cast<const void*>(&yfwd_kernel<R, PY, SQ>), lds,
                                                1LL << 30, NT),
                                (long long)(ntiles / ntx) * ((ntx + 1) / 2));
     if (grid < 2) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((yfwd_kernel<R, EM, NT, LG>), dim3(grid), dim3(NT), lds, s, static_cast<const cx<R>*>(X1),
+    hipLaunchKernelGGL((yfwd_kernel<R, PY, SQ>), dim3(grid), dim3(NT), lds, s, static_cast<const cx<R>*>(X1),
                        static_cast<cx<R>*>(X2), pl.ny, pl.lgPy, pl.Hx, pl.Sx, lgT, ntx, ntiles, pl.nyqpack);
     return hipGetLastError();
 }
 
-template <typename R, int EM, int NT, int LG = 0>
+template <typename R, int PY, bool SQ = false>
 static hipError_t run_yinv(const Plan& pl, const void* X2, void* Y1, hipStream_t s) {
+    constexpr int NT = YCfg<R, PY>::NT;
+    if (PY ? (pl.Py != PY || pl.ty != YCfg<R, PY>::T) : (pl.Py * pl.ty > NT * YCfg<R, 0>::EM))
+        return hipErrorInvalidValue;
     const int lgT = ilog2(pl.ty);
     const int ntx = (pl.Hx + pl.ty - 1) / pl.ty;
     const int ntiles = ntx * 3 * pl.nz * pl.nbatch;
     const size_t lds = (size_t)pl.Py * pl.ty * sizeof(cx<R>);
-    const int grid = pair_grid(persistent_grid(reinterpret_cast<const void*>(&yinv_kernel<R, EM, NT, LG>), lds,
+    const int grid = pair_grid(persistent_grid(reinterpret_cast<const void*>(&yinv_kernel<R, PY, SQ>), lds,
                                                1LL << 30, NT),
                                (long long)(ntiles / ntx) * ((ntx + 1) / 2));
     if (grid < 2) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((yinv_kernel<R, EM, NT, LG>), dim3(grid), dim3(NT), lds, s, static_cast<const cx<R>*>(X2),
+    hipLaunchKernelGGL((yinv_kernel<R, PY, SQ>), dim3(grid), dim3(NT), lds, s, static_cast<const cx<R>*>(X2),
                        static_cast<cx<R>*>(Y1), pl.ny, pl.lgPy, pl.Hx, pl.Sx, lgT, ntx, ntiles, pl.nyqpack);
     return hipGetLastError();
 }
@@ -1272,76 +1307,37 @@ static hipError_t run_y2(const Plan& pl, const void* in, void* out, hipStream_t 
     return hipGetLastError();
 }
 
-// Tiles of more than 256 x 32 elements (up to 128 KiB of LDS, one block per
-// CU): 512 threads of 32 elements (two radix-32 passes for Py = 1024).
-static bool y_huge(const Plan& pl) { return (long long)pl.Py * pl.ty > (long long)kNT * 32; }
-
-// LG of the compile-time y geometry that matches the plan, 0 if none.
-template <typename R>
-static int y_lg(const Plan& pl) {
-    if (pl.Px != pl.Py || 2 * pl.nx != pl.Px || 2 * pl.ny != pl.Py) return 0;
-    if (pl.lgPy < 8 || pl.lgPy > 11) return 0;
-    if (pl.ty != (1 << ytile_lg<R>(pl.lgPy)) || pl.Sx != pl.Px / 2 + 16) return 0;
-    return pl.lgPy;
+// Square power-of-two grids whose y passes have their whole geometry at compile time.
+static bool y_square(const Plan& pl) {
+    return pl.Px == pl.Py && 2 * pl.nx == pl.Px && 2 * pl.ny == pl.Py && pl.Sx == pl.Px / 2 + 16;
 }
+
+#define MAGX_Y_SWITCH(RUN, ...)                                                                       \
+    switch (pl.Py) {                                                                                  \
+        case 128: return RUN<R, 128>(__VA_ARGS__);                                                    \
+        case 160: return RUN<R, 160>(__VA_ARGS__);                                                    \
+        case 192: return RUN<R, 192>(__VA_ARGS__);                                                    \
+        case 256: return y_square(pl) ? RUN<R, 256, true>(__VA_ARGS__) : RUN<R, 256>(__VA_ARGS__);    \
+        case 320: return RUN<R, 320>(__VA_ARGS__);                                                    \
+        case 384: return RUN<R, 384>(__VA_ARGS__);                                                    \
+        case 512: return y_square(pl) ? RUN<R, 512, true>(__VA_ARGS__) : RUN<R, 512>(__VA_ARGS__);    \
+        case 640: return RUN<R, 640>(__VA_ARGS__);                                                    \
+        case 768: return RUN<R, 768>(__VA_ARGS__);                                                    \
+        case 1024: return y_square(pl) ? RUN<R, 1024, true>(__VA_ARGS__) : RUN<R, 1024>(__VA_ARGS__); \
+        case 4096: return RUN<R, 4096>(__VA_ARGS__);                                                  \
+        default: return RUN<R, 0>(__VA_ARGS__);                                                       \
+    }
 
 template <typename R>
 hipError_t launch_yfwd(const Plan& pl, const void* X1, void* X2, hipStream_t s) {
     if (pl.Py == 2048) return run_y2<R, false>(pl, X1, X2, s);
-    if constexpr (std::is_same<R, float>::value) {
-        switch (y_lg<R>(pl)) {
-            case 8: return run_yfwd<R, 16, kNT, 8>(pl, X1, X2, s);
-            case 9: return run_yfwd<R, 32, kNT, 9>(pl, X1, X2, s);
-            case 10: return run_yfwd<R, 32, 512, 10>(pl, X1, X2, s);
-            case 11: return run_yfwd<R, 32, 512, 11>(pl, X1, X2, s);
-            default: break;
-        }
-    } else {
-        // double precision: tiles of 2^12 values (256 threads of 16) or 2^13 (512 threads of 16)
-        switch (y_lg<R>(pl)) {
-            case 8: return run_yfwd<R, 16, kNT, 8>(pl, X1, X2, s);
-            case 9: return run_yfwd<R, 16, kNT, 9>(pl, X1, X2, s);
-            case 10: return run_yfwd<R, 16, 512, 10>(pl, X1, X2, s);
-            case 11: return run_yfwd<R, 16, 512, 11>(pl, X1, X2, s);
-            default: break;
-        }
-        // tiles of up to 2^12 values: 256 threads of 16; up to 2^13 (128 KiB): 512 threads of 16
-        if (!em_big((long long)pl.Py * pl.ty)) return run_yfwd<R, 16, kNT>(pl, X1, X2, s);
-        return run_yfwd<R, 16, 512>(pl, X1, X2, s);
-    }
-    // tiles of up to 256 x 16 elements: 256 threads of 16; up to 256 x 32
-    // (64 KiB in single precision): 256 threads of 32
-    if (!em_big((long long)pl.Py * pl.ty)) return run_yfwd<R, 16, kNT>(pl, X1, X2, s);
-    if (y_huge(pl)) return run_yfwd<R, 32, 512>(pl, X1, X2, s);
-    return run_yfwd<R, 32, kNT>(pl, X1, X2, s);
+    MAGX_Y_SWITCH(run_yfwd, pl, X1, X2, s)
 }
 
 template <typename R>
 hipError_t launch_yinv(const Plan& pl, const void* X2, void* Y1, hipStream_t s) {
     if (pl.Py == 2048) return run_y2<R, true>(pl, X2, Y1, s);
-    if constexpr (std::is_same<R, float>::value) {
-        switch (y_lg<R>(pl)) {
-            case 8: return run_yinv<R, 16, kNT, 8>(pl, X2, Y1, s);
-            case 9: return run_yinv<R, 32, kNT, 9>(pl, X2, Y1, s);
-            case 10: return run_yinv<R, 32, 512, 10>(pl, X2, Y1, s);
-            case 11: return run_yinv<R, 32, 512, 11>(pl, X2, Y1, s);
-            default: break;
-        }
-    } else {
-        switch (y_lg<R>(pl)) {
-            case 8: return run_yinv<R, 16, kNT, 8>(pl, X2, Y1, s);
-            case 9: return run_yinv<R, 16, kNT, 9>(pl, X2, Y1, s);
-            case 10: return run_yinv<R, 16, 512, 10>(pl, X2, Y1, s);
-            case 11: return run_yinv<R, 16, 512, 11>(pl, X2, Y1, s);
-            default: break;
-        }
-        // tiles of up to 2^12 values: 256 threads of 16; up to 2^13 (128 KiB): 512 threads of 16
-        if (!em_big((long long)pl.Py * pl.ty)) return run_yinv<R, 16, kNT>(pl, X2, Y1, s);
-        return run_yinv<R, 16, 512>(pl, X2, Y1, s);
-    }
-    if (!em_big((long long)pl.Py * pl.ty)) return run_yinv<R, 16, kNT>(pl, X2, Y1, s);
-    if (y_huge(pl)) return run_yinv<R, 32, 512>(pl, X2, Y1, s);
-    return run_yinv<R, 32, kNT>(pl, X2, Y1, s);
+    MAGX_Y_SWITCH(run_yinv, pl, X2, Y1, s)
 }
 
 template <typename R, int EM>
@@ -1550,6 +1546,7 @@ hipError_t launch_yzfilm(const Plan& pl, void* X1, const void* spec, R Ms, hipSt
     return hipGetLastError();
 }
 
+#if MAGX_REAL == 32
 // ---- memory patterns without arithmetic (diagnostics) ---------------------------
 // The practical bandwidth of the access patterns of the passes, measured on
 // the same buffer: a float4 stream copy, and in-place read + write (scaled by
@@ -1617,14 +1614,20 @@ hipError_t launch_memory_probe(const Plan& pl, int kind, void* X2, hipStream_t s
     }
     return hipGetLastError();
 }
+#endif
 
-template hipError_t launch_yfwd<float>(const Plan&, const void*, void*, hipStream_t);
-template hipError_t launch_yfwd<double>(const Plan&, const void*, void*, hipStream_t);
-template hipError_t launch_yinv<float>(const Plan&, const void*, void*, hipStream_t);
-template hipError_t launch_yinv<double>(const Plan&, const void*, void*, hipStream_t);
-template hipError_t launch_zconv<float>(const Plan&, void*, const void*, float, hipStream_t);
-template hipError_t launch_zconv<double>(const Plan&, void*, const void*, double, hipStream_t);
-template hipError_t launch_yzfilm<float>(const Plan&, void*, const void*, float, hipStream_t);
-template hipError_t launch_yzfilm<double>(const Plan&, void*, const void*, double, hipStream_t);
+#define MAGX_INST(R)                                                                       \
+    template hipError_t launch_yfwd<R>(const Plan&, const void*, void*, hipStream_t);      \
+    template hipError_t launch_yinv<R>(const Plan&, const void*, void*, hipStream_t);      \
+    template hipError_t launch_zconv<R>(const Plan&, void*, const void*, R, hipStream_t);  \
+    template hipError_t launch_yzfilm<R>(const Plan&, void*, const void*, R, hipStream_t);
+
+#if MAGX_REAL == 32
+MAGX_INST(float)
+MAGX_TW_INIT(init_tw_conv32)
+#else
+MAGX_INST(double)
+MAGX_TW_INIT(init_tw_conv64)
+#endif
 
 }  // namespace magx

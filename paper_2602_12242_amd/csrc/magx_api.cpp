@@ -89,6 +89,22 @@ static int next_pow2_at_least(long long v) {
 
 static size_t align256(size_t v) { return (v + 255) & ~size_t(255); }
 
+// Extended length of an axis of n cells along x or y.  Below 2^16 cells the
+// smallest power of two >= 2n: such grids are bound by the latency of their
+// kernels, not by the length of their lines.  From 2^16 cells on also
+// 5/8 and 3/4 of that power of two (5 2^k, 3 2^k) where they are >= 2n and at
+// least 160 and at most `most`, the longest such length the passes have: the
+// spectral fields, their traffic and the tensor shrink with it.
+constexpr long long kOddMinCells = 1LL << 16;
+static int extended_length(int n, long long ncell, int most) {
+    const int p = next_pow2_at_least(std::max(2, 2 * n));
+    if (ncell < kOddMinCells || p < 256) return p;
+    const int c5 = p / 8 * 5, c3 = p / 4 * 3;
+    if (c5 >= 2 * n && c5 <= most) return c5;
+    if (c3 >= 2 * n && c3 <= most) return c3;
+    return p;
+}
+
 static int pow2_floor(long long v) {
     int p = 1;
     while ((long long)p * 2 <= v) p <<= 1;
@@ -115,16 +131,27 @@ int make_plan(const magx_grid* g, magx_dtype dt, int nbatch, Plan* pl) {
     // Py*ty, z columns 3*Pz*tz complex values
     const int lds_cplx = dt == MAGX_F32 ? 8192 : 4096;
     if (p.Py > 4096 || 3 * (p.Px / 2) > lds_cplx || 3 * p.Pz > lds_cplx) return MAGX_ESIZE;
-    p.lgPx = ilog2(p.Px); p.lgPy = ilog2(p.Py); p.lgPz = ilog2(p.Pz);
+    // size limits, also that of magx_step_static's fixed workspace (the flag
+    // word, X1, X2 and three fields), are those of the power-of-two lengths
+    p.nbatch = nbatch;
+    p.ncell = (long long)p.nx * p.ny * p.nz;
+    {
+        const long long Sx = (p.Px / 2 + 1 + 15) / 16 * 16;
+        const size_t rows = (size_t)3 * nbatch * p.nz, c = (size_t)Sx * 2 * p.esize;
+        p.static_bytes = align256(align256(256 + rows * p.ny * c) + rows * p.Py * c) +
+                         3 * align256((size_t)3 * nbatch * p.ncell * p.esize);
+        if (3LL * nbatch * p.nz * p.Py * Sx >= (1LL << 31) || p.Py * Sx >= (1LL << 23) ||
+            6LL * (p.Pz / 2 + 1) * (p.Py / 2 + 1) * Sx >= (1LL << 31))
+            return MAGX_ESIZE;
+    }
+    p.Px = extended_length(p.nx, p.ncell, 1536);
+    // films whose power-of-two tile keeps the fused y and z kernel stay there
+    if (p.nz > 1 || 3LL * p.Py * 8 * 2 * p.esize > 65536) p.Py = extended_length(p.ny, p.ncell, 768);
+    p.lgPx = ilog2(p.Px / odd_part(p.Px)); p.lgPy = ilog2(p.Py / odd_part(p.Py)); p.lgPz = ilog2(p.Pz);
     p.Lh = p.Px / 2; p.lgLh = p.lgPx - 1;
     p.Hx = p.Lh + 1; p.Hy = p.Py / 2 + 1; p.Hz = p.Pz / 2 + 1;
     p.Sx = (p.Hx + 15) / 16 * 16;
-    // 32-bit element offsets inside the spectral arrays (whole batch), 24-bit row strides
-    p.nbatch = nbatch;
-    if (3LL * nbatch * p.nz * p.Py * p.Sx >= (1LL << 31) || (long long)p.Py * p.Sx >= (1LL << 23) ||
-        6LL * p.Hz * p.Hy * p.Sx >= (1LL << 31))
-        return MAGX_ESIZE;
-    p.ncell = (long long)p.nx * p.ny * p.nz;
+    // 32-bit element offsets inside the spectral arrays (whole batch), 24-bit row strides (checked above)
     if (3LL * nbatch * p.ncell >= (1LL << 31) || nbatch > 65535) return MAGX_ESIZE;
     // y tile: Py*ty complex in LDS, up to 128 KiB (one block of 512 threads
     // per CU; single precision: 16 columns = whole 128-byte row segments at
@@ -163,7 +190,7 @@ int make_plan(const magx_grid* g, magx_dtype dt, int nbatch, Plan* pl) {
     // columns (8 ... 16, whole 64- to 128-byte row segments) fits in 64 KiB;
     // on small films the tiles narrow (down to 4 columns) until there are 64
     // of them, since there the kernel's latency, not its traffic, counts
-    if (p.nz == 1) {
+    if (p.nz == 1 && odd_part(p.Py) == 1) {
         int t = 16;
         while (t >= 8 && 3LL * p.Py * t * 2 * p.esize > 65536) t >>= 1;
         if (t >= 8) {
@@ -206,7 +233,7 @@ int make_plan(const magx_grid* g, magx_dtype dt, int nbatch, Plan* pl) {
     // (not at Pz = 8: its one-wave blocks come two units per pair on grids of
     // that depth, too few to balance a Nyquist unit against)
     p.nyqpack = (dt == MAGX_F32 && p.zreg && p.Pz >= 16 && p.Pz <= 64 && p.Py >= 32 && p.Py <= 1024 &&
-                 p.Lh >= p.tz && p.Sx == p.Lh + 16) ? 1 : 0;
+                 p.Lh >= p.tz && p.Lh % p.tz == 0 && p.Sx == p.Lh + 16) ? 1 : 0;
     p.tn_off = (long long)p.Hy * p.ntz * 6 * p.Hz * p.tz;
     const long long tn_blocks = p.nyqpack ? (p.Py / 2 + p.tz - 1) / p.tz + 1 : 0;
     p.spectrum_bytes = (size_t)(p.tn_off + tn_blocks * 6 * p.Hz * p.tz) * es;
@@ -304,7 +331,8 @@ static int ensure_twiddles(hipStream_t s, int* device) {
     if (dev < 0 || dev >= 64) return MAGX_EHIP;
     std::lock_guard<std::mutex> lk(g_tw_mutex);
     if (g_tw_ready[dev]) return MAGX_OK;
-    if (launch_twiddle_init(s) != hipSuccess) return MAGX_EHIP;
+    for (auto init : {init_tw_tensor, init_tw_conv32, init_tw_conv64, init_tw_pencil32, init_tw_pencil64, init_tw_mri})
+        if (init(s) != hipSuccess) return MAGX_EHIP;
     // other streams of this device may use the table right away
     if (hipStreamSynchronize(s) != hipSuccess) return MAGX_EHIP;
     g_tw_ready[dev] = true;
@@ -933,7 +961,7 @@ int magx_step_static(magx_ctx* ctx, void* m, const magx_params* p, double dt, in
     if (rc) return rc;
     // RK4 without a tape uses the flag word, X1, X2 and three fields: the
     // workspace prefix up to the fourth field
-    if (ctx->pl.off_f[3] > kStaticWsBytes) return MAGX_EWORKSPACE;
+    if (ctx->pl.static_bytes > kStaticWsBytes || ctx->pl.off_f[3] > kStaticWsBytes) return MAGX_EWORKSPACE;
     void* ws = static_ws(ctx->device);
     if (!ws) return MAGX_EHIP;
     if (nsteps == 0) return MAGX_OK;

@@ -13,8 +13,16 @@
 namespace magx {
 
 constexpr int kNT = 256;          // threads per block of the pencil kernels (and default of the FFT core)
-constexpr int kTwLog = 12;        // twiddle table covers lengths up to 4096
-constexpr int kTwN = 1 << kTwLog;
+
+// Transform lengths are ODD 2^k with ODD = 1, 3 or 5.  Their twiddles come
+// from one table of roots of unity per ODD: 4096, 3072 = 3 2^10 and
+// 5120 = 5 2^10 entries, back to back in one array.
+constexpr int tw_log(int odd) { return odd == 1 ? 12 : 10; }       // log2(entries / ODD)
+constexpr int tw_size(int odd) { return odd << tw_log(odd); }
+constexpr int tw_offset(int odd) { return odd == 1 ? 0 : (odd == 3 ? tw_size(1) : tw_size(1) + tw_size(3)); }
+constexpr int kTwLog = tw_log(1);
+constexpr int kTwAll = tw_size(1) + tw_size(3) + tw_size(5);
+__host__ __device__ constexpr int odd_part(int n) { return n % 5 == 0 ? 5 : (n % 3 == 0 ? 3 : 1); }
 
 template <typename R> struct vec2;
 template <> struct vec2<float> { using type = float2; };
@@ -34,40 +42,59 @@ template <typename R, bool INV> __device__ __forceinline__ cx<R> mul_mi(cx<R> a)
     return INV ? mk<R>(-a.y, a.x) : mk<R>(a.y, -a.x);
 }
 
-// exp(-2 pi i k / 4096), k in [0, 4096), filled once per device at context
-// creation (double-precision sincospi, rounded once for the float table).
-extern __device__ float2 g_tw32[kTwN];
-extern __device__ double2 g_tw64[kTwN];
+// exp(-2 pi i k / tw_size(ODD)) at tw_offset(ODD) + k, filled once per device
+// at context creation (double-precision sincospi, rounded once for the float
+// table).  Every translation unit with kernels has its own copy, so each is
+// compiled by itself; MAGX_TW_INIT defines the unit's filling launch.
+static __device__ float2 g_tw32[kTwAll];
+static __device__ double2 g_tw64[kTwAll];
 
-template <typename R> __device__ __forceinline__ cx<R> tw_fwd(int k);
-template <> __device__ __forceinline__ float2 tw_fwd<float>(int k) { return g_tw32[(unsigned)k]; }
-template <> __device__ __forceinline__ double2 tw_fwd<double>(int k) { return g_tw64[(unsigned)k]; }
-// w^k for a transform of direction INV; k indexes the 4096-point table.
-template <typename R, bool INV> __device__ __forceinline__ cx<R> tw(int k) {
-    cx<R> w = tw_fwd<R>(k);
+static __global__ void twiddle_init_kernel() {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= kTwAll) return;
+    const int odd = i < tw_offset(3) ? 1 : (i < tw_offset(5) ? 3 : 5);
+    double s, c;
+    sincospi(-2.0 * (double)(i - tw_offset(odd)) / (double)tw_size(odd), &s, &c);
+    g_tw64[i] = make_double2(c, s);
+    g_tw32[i] = make_float2((float)c, (float)s);
+}
+#define MAGX_TW_INIT(NAME)                                                                          \
+    hipError_t NAME(hipStream_t s) {                                                                \
+        hipLaunchKernelGGL(twiddle_init_kernel, dim3((kTwAll + kNT - 1) / kNT), dim3(kNT), 0, s);   \
+        return hipGetLastError();                                                                   \
+    }
+
+template <typename R, int ODD = 1> __device__ __forceinline__ cx<R> tw_fwd(int k) {
+    if constexpr (sizeof(R) == 4) return g_tw32[(unsigned)(tw_offset(ODD) + k)];
+    else return g_tw64[(unsigned)(tw_offset(ODD) + k)];
+}
+// w^k for a transform of direction INV; k indexes the table of ODD.
+template <typename R, bool INV, int ODD = 1> __device__ __forceinline__ cx<R> tw(int k) {
+    cx<R> w = tw_fwd<R, ODD>(k);
     return INV ? cconj<R>(w) : w;
 }
 
-// Two-level copy of the twiddle table in LDS for the FFT passes of a block:
-// W^k = W^(64 (k >> 6)) W^(k & 63) (W = exp(-2 pi i / 4096)), 128 entries.
-// A pass twiddle then costs two LDS reads and a complex product instead of a
-// global (L2) load.  Every kernel that asks the passes for it (TWL) fills it
-// with tw_lds_fill before its first barrier.
-template <typename R> __device__ __forceinline__ cx<R>* tw_lds() {
-    __shared__ cx<R> t[128];
+// Two-level copy of a twiddle table in LDS for the FFT passes of a block:
+// W^k = W^(64 (k >> 6)) W^(k & 63) (W = exp(-2 pi i / tw_size(ODD))), 64 +
+// tw_size(ODD)/64 entries.  A pass twiddle then costs two LDS reads and a
+// complex product instead of a global (L2) load.  Every kernel that asks the
+// passes for it (TWL) fills it with tw_lds_fill before its first barrier.
+template <typename R, int ODD = 1> __device__ __forceinline__ cx<R>* tw_lds() {
+    __shared__ cx<R> t[64 + tw_size(ODD) / 64];
     return t;
 }
-template <typename R> __device__ __forceinline__ void tw_lds_fill() {
-    cx<R>* t = tw_lds<R>();
-    for (int i = threadIdx.x; i < 128; i += blockDim.x) t[i] = tw_fwd<R>(i < 64 ? i : (i - 64) << 6);
+template <typename R, int ODD = 1> __device__ __forceinline__ void tw_lds_fill() {
+    cx<R>* t = tw_lds<R, ODD>();
+    for (int i = threadIdx.x; i < 64 + tw_size(ODD) / 64; i += blockDim.x)
+        t[i] = tw_fwd<R, ODD>(i < 64 ? i : (i - 64) << 6);
 }
-template <typename R, bool INV, bool TWL> __device__ __forceinline__ cx<R> tw_pass(int k) {
+template <typename R, bool INV, bool TWL, int ODD = 1> __device__ __forceinline__ cx<R> tw_pass(int k) {
     if constexpr (TWL) {
-        const cx<R>* t = tw_lds<R>();
+        const cx<R>* t = tw_lds<R, ODD>();
         const cx<R> w = cmul<R>(t[64 + (k >> 6)], t[k & 63]);
         return INV ? cconj<R>(w) : w;
     } else {
-        return tw<R, INV>(k);
+        return tw<R, INV, ODD>(k);
     }
 }
 
@@ -107,6 +134,34 @@ template <typename R, bool INV> __device__ __forceinline__ void dft8(cx<R>* v) {
     v[6] = csub<R>(e[2], o2);
     v[3] = cadd<R>(e[3], o3);
     v[7] = csub<R>(e[3], o3);
+}
+
+// Lengths 3 and 5 from the real and imaginary parts of the roots: with
+// a = v[1] + v[N-1], b = v[1] - v[N-1] (and the same for v[2], v[3]),
+// X[k], X[N-k] = v[0] + sum a cos(2 pi k j / N) -+ i sum b sin(2 pi k j / N).
+template <typename R, bool INV> __device__ __forceinline__ void dft3(cx<R>* v) {
+    const R h = (R)0.86602540378443864676;
+    const cx<R> a = cadd<R>(v[1], v[2]), b = mul_mi<R, INV>(cscale<R>(csub<R>(v[1], v[2]), h));
+    const cx<R> m = mk<R>(v[0].x - (R)0.5 * a.x, v[0].y - (R)0.5 * a.y);
+    v[0] = cadd<R>(v[0], a);
+    v[1] = cadd<R>(m, b);
+    v[2] = csub<R>(m, b);
+}
+
+template <typename R, bool INV> __device__ __forceinline__ void dft5(cx<R>* v) {
+    const R c1 = (R)0.30901699437494742410, c2 = (R)-0.80901699437494742410;
+    const R s1 = (R)0.95105651629515357212, s2 = (R)0.58778525229247312917;
+    const cx<R> a1 = cadd<R>(v[1], v[4]), b1 = csub<R>(v[1], v[4]);
+    const cx<R> a2 = cadd<R>(v[2], v[3]), b2 = csub<R>(v[2], v[3]);
+    const cx<R> m1 = mk<R>(v[0].x + c1 * a1.x + c2 * a2.x, v[0].y + c1 * a1.y + c2 * a2.y);
+    const cx<R> m2 = mk<R>(v[0].x + c2 * a1.x + c1 * a2.x, v[0].y + c2 * a1.y + c1 * a2.y);
+    const cx<R> n1 = mul_mi<R, INV>(mk<R>(s1 * b1.x + s2 * b2.x, s1 * b1.y + s2 * b2.y));
+    const cx<R> n2 = mul_mi<R, INV>(mk<R>(s2 * b1.x - s1 * b2.x, s2 * b1.y - s1 * b2.y));
+    v[0] = cadd<R>(v[0], cadd<R>(a1, a2));
+    v[1] = cadd<R>(m1, n1);
+    v[4] = csub<R>(m1, n1);
+    v[2] = cadd<R>(m2, n2);
+    v[3] = csub<R>(m2, n2);
 }
 
 // cos(pi j / 16), j = 0..8 (the 32nd roots of unity follow by symmetry)
@@ -190,7 +245,10 @@ template <typename R, bool INV> __device__ __forceinline__ void dft32(cx<R>* v) 
         u[2] = tw32_n2k1<R, INV, 2, K1>(y[2][K1]);        \
         u[3] = tw32_n2k1<R, INV, 3, K1>(y[3][K1]);        \
         dft4<R, INV>(u);                                  \
-        for (int k2 = 0; k2 < 4; ++k2) v[K1 + 8 * k2] = u[k2]; \
+        v[K1] = u[0];                                     \
+        v[K1 + 8] = u[1];                                 \
+        v[K1 + 16] = u[2];                                \
+        v[K1 + 24] = u[3];                                \
     }
     MAGX_TW(0) MAGX_TW(1) MAGX_TW(2) MAGX_TW(3) MAGX_TW(4) MAGX_TW(5) MAGX_TW(6) MAGX_TW(7)
 #undef MAGX_TW
@@ -198,6 +256,8 @@ template <typename R, bool INV> __device__ __forceinline__ void dft32(cx<R>* v) 
 
 template <typename R, int RAD, bool INV> __device__ __forceinline__ void dft(cx<R>* v) {
     if constexpr (RAD == 2) dft2<R, INV>(v);
+    else if constexpr (RAD == 3) dft3<R, INV>(v);
+    else if constexpr (RAD == 5) dft5<R, INV>(v);
     else if constexpr (RAD == 4) dft4<R, INV>(v);
     else if constexpr (RAD == 8) dft8<R, INV>(v);
     else if constexpr (RAD == 16) dft16<R, INV>(v);
@@ -207,13 +267,14 @@ template <typename R, int RAD, bool INV> __device__ __forceinline__ void dft(cx<
 constexpr int ilog2c(int v) { return v <= 1 ? 0 : 1 + ilog2c(v >> 1); }
 
 // ---- Stockham FFTs in LDS ----------------------------------------------------------
-// nseq independent sequences of length L = 2^lgL (1 <= L <= 4096).  Two LDS
-// layouts:
+// nseq independent sequences of length L = ODD 2^lgL (1 <= L <= 4096; with
+// ODD = 3 or 5 the passes of the power of two come first, so their twiddles
+// are those of lengths 2^k, and a pass of radix ODD last).  Two LDS layouts:
 //  * columns (LAYOUT = kCols): nseq = NC << lgT sequences, element j of
 //    sequence b at b + j*nseq; consecutive threads take consecutive b
 //    (coalesced column tiles; NC = 1 or 3 is a compile-time constant so the
 //    thread -> (b, j) split needs no runtime division);
-//  * lines (LAYOUT = kLines): element j of sequence b at (b << lgL) + j;
+//  * lines (LAYOUT = kLines): element j of sequence b at b L + j;
 //    consecutive threads take consecutive j.
 // Each of the NT threads of the block holds at most EMAX elements
 // (nseq * L <= NT * EMAX).
@@ -235,21 +296,25 @@ __device__ __forceinline__ unsigned umul24(unsigned a, unsigned b) { return __um
 // threadIdx.x behind an empty volatile asm statement: index arithmetic derived
 // from it is recomputed in each pass instead of being hoisted out of a tile
 // loop and held in registers across it.
-__device__ __forceinline__ int tid_opaque() {
+template <int NT = kNT> __device__ __forceinline__ int tid_opaque() {
     int t = threadIdx.x;
     asm volatile("" : "+v"(t));
+    __builtin_assume(t >= 0 && t < NT);
     return t;
 }
 
 // v[r] *= w^(r k), r = 1..RAD-1, for the pass twiddle w: w^k, w^2k, w^4k, ...
 // come from the table and every other power is a product of those (at most
 // log2(RAD) - 1 products deep).
-template <typename R, bool INV, int RAD, bool TWL = false>
+template <typename R, bool INV, int RAD, bool TWL = false, int ODD = 1>
 __device__ __forceinline__ void twiddle_apply(cx<R>* v, int k, int twshift) {
     if (!k) return;
+    // table index of w^(p k): N / (Ns RAD) p k with N = ODD 2^tw_log entries
+    // (the odd factor of N is in RAD itself in the last pass of radix ODD)
+    constexpr int F = RAD == ODD ? 1 : ODD;
     cx<R> w[RAD];
 #pragma unroll
-    for (int p = 1; p < RAD; p <<= 1) w[p] = tw_pass<R, INV, TWL>((p * k) << twshift);
+    for (int p = 1; p < RAD; p <<= 1) w[p] = tw_pass<R, INV, TWL, ODD>((F * p * k) << twshift);
 #pragma unroll
     for (int r = 3; r < RAD; ++r) {
         if ((r & (r - 1)) == 0) continue;
@@ -262,9 +327,13 @@ __device__ __forceinline__ void twiddle_apply(cx<R>* v, int k, int twshift) {
 
 // Thread slot t -> (sequence b, butterfly j); unsigned arithmetic throughout
 // (no sign fix-ups in shifts and divisions).
-template <int LAYOUT, int NC>
+template <int LAYOUT, int NC, int FO = 1>
 __device__ __forceinline__ void seq_split(unsigned t, int lgT, int lgnb, unsigned nseq, unsigned& b, unsigned& j) {
-    if constexpr (LAYOUT == kLines) {
+    if constexpr (LAYOUT == kLines && FO > 1) {
+        // nb = FO 2^lgnb butterflies per sequence (lgnb is a constant here)
+        b = (t >> lgnb) / (unsigned)FO;
+        j = t - b * ((unsigned)FO << lgnb);
+    } else if constexpr (LAYOUT == kLines) {
         b = t >> lgnb;
         j = t & ((1u << lgnb) - 1u);
     } else if constexpr (NC == 1) {
@@ -292,29 +361,32 @@ struct FirstIn {
 };
 
 template <typename R, int RAD, bool INV, int EMAX, int SRC, bool DST_LDS, int LAYOUT, int NC, bool HIN,
-          bool HOUT, int NT, bool TWL, class Load, class Store, class In>
+          bool HOUT, int NT, bool TWL, int ODD = 1, class Load, class Store, class In>
 __device__ __forceinline__ void stockham_io_pass(cx<R>* __restrict__ buf, int lgL, int lgNs, int lgT, int nseq,
                                                  Load& load, Store& store, In& in) {
     constexpr bool SRC_LDS = SRC == kSrcLds;
     constexpr int PER = EMAX / RAD > 0 ? EMAX / RAD : 1;
-    constexpr int LGR = ilog2c(RAD);
+    constexpr bool LAST_ODD = RAD == 3 || RAD == 5;        // the pass of radix ODD (Ns = 2^lgL)
+    constexpr int FO = LAST_ODD ? 1 : ODD;                 // butterflies per sequence: nb = FO 2^lgnb
+    constexpr int LGR = LAST_ODD ? 0 : ilog2c(RAD);
     const int lgnb = lgL - LGR;
-    const unsigned nb = 1u << lgnb;
+    const unsigned nb = (unsigned)FO << lgnb;
+    const unsigned L = (unsigned)ODD << lgL;
     const unsigned total = nb * (unsigned)nseq;
     const unsigned Ns = 1u << lgNs;
-    const int twshift = kTwLog - LGR - lgNs;
+    const int twshift = tw_log(ODD) - LGR - lgNs;
     // uniform strides between the RAD inputs / outputs of one butterfly
     const unsigned in_stride = LAYOUT == kLines ? nb : (nb * (unsigned)nseq);
     const unsigned out_stride = LAYOUT == kLines ? Ns : (Ns * (unsigned)nseq);
     cx<R> v[PER][RAD];
     unsigned seqv[PER], pos0[PER], obase[PER];
-    const unsigned tid = (unsigned)tid_opaque();
+    const unsigned tid = (unsigned)tid_opaque<NT>();
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
         const unsigned t = tid + (unsigned)(i * NT);
         if (t < total) {
             unsigned b, j;
-            seq_split<LAYOUT, NC>(t, lgT, lgnb, (unsigned)nseq, b, j);
+            seq_split<LAYOUT, NC, FO>(t, lgT, lgnb, (unsigned)nseq, b, j);
             seqv[i] = b;
             // with HIN the inputs r >= RAD/2 lie in the zero half (first pass: lgNs = 0)
             constexpr int RIN = HIN ? RAD / 2 : RAD;
@@ -322,19 +394,19 @@ __device__ __forceinline__ void stockham_io_pass(cx<R>* __restrict__ buf, int lg
 #pragma unroll
                 for (int r = 0; r < RIN; ++r) v[i][r] = in.v[i * RIN + r];
             } else if constexpr (SRC_LDS) {
-                const unsigned ib = LAYOUT == kLines ? (b << lgL) + j : b + umul24(j, (unsigned)nseq);
+                const unsigned ib = LAYOUT == kLines ? (ODD == 1 ? b << lgL : b * L) + j : b + umul24(j, (unsigned)nseq);
 #pragma unroll
                 for (int r = 0; r < RIN; ++r) v[i][r] = buf[ib + (unsigned)r * in_stride];
             } else {
 #pragma unroll
-                for (int r = 0; r < RIN; ++r) v[i][r] = load((int)b, (int)(j + ((unsigned)r << lgnb)));
+                for (int r = 0; r < RIN; ++r) v[i][r] = load((int)b, (int)(j + (unsigned)r * nb));
             }
 #pragma unroll
             for (int r = RIN; r < RAD; ++r) v[i][r] = mk<R>((R)0, (R)0);
             const unsigned k = j & (Ns - 1u);
             pos0[i] = ((j >> lgNs) << (lgNs + LGR)) + k;
-            obase[i] = LAYOUT == kLines ? (b << lgL) + pos0[i] : b + umul24(pos0[i], (unsigned)nseq);
-            twiddle_apply<R, INV, RAD, TWL>(v[i], (int)k, twshift);
+            obase[i] = LAYOUT == kLines ? (ODD == 1 ? b << lgL : b * L) + pos0[i] : b + umul24(pos0[i], (unsigned)nseq);
+            twiddle_apply<R, INV, RAD, TWL, ODD>(v[i], (int)k, twshift);
             dft<R, RAD, INV>(v[i]);
         }
     }
@@ -344,8 +416,9 @@ __device__ __forceinline__ void stockham_io_pass(cx<R>* __restrict__ buf, int lg
         const unsigned t = tid + (unsigned)(i * NT);
         if (t < total) {
 #pragma unroll
-            // with HOUT the outputs r >= RAD/2 land in the unwanted half (last pass)
-            for (int r = 0; r < (HOUT ? RAD / 2 : RAD); ++r) {
+            // with HOUT the outputs r >= RAD/2 land in the unwanted half (last pass;
+            // of an odd radix the middle one straddles it and is stored whole)
+            for (int r = 0; r < (HOUT ? (RAD + 1) / 2 : RAD); ++r) {
                 if constexpr (DST_LDS) buf[obase[i] + (unsigned)r * out_stride] = v[i][r];
                 else store((int)seqv[i], (int)(pos0[i] + (unsigned)r * Ns), v[i][r]);
             }
@@ -371,9 +444,10 @@ template <int EMAX> constexpr int lgmax() { return EMAX >= 32 ? 5 : (EMAX >= 16 
     }
 
 template <typename R, bool INV, int EMAX, bool SRC_LDS, bool DST_LDS, int LAYOUT, int NC, bool HALF_IN = false,
-          bool HALF_OUT = false, int LGM = lgmax<EMAX>(), int NT = kNT, bool TWL = false, class Load, class Store>
+          bool HALF_OUT = false, int LGM = lgmax<EMAX>(), int NT = kNT, bool TWL = false, int ODD = 1, class Load,
+          class Store>
 __device__ __forceinline__ void fft_io(cx<R>* __restrict__ buf, int lgL, int lgT, int nseq, Load load, Store store) {
-    if (lgL == 0) {   // length 1: the transform is the identity
+    if (ODD == 1 && lgL == 0) {   // length 1: the transform is the identity
         for (int b = threadIdx.x; b < nseq; b += NT) {
             cx<R> x;
             if constexpr (SRC_LDS) x = buf[b];
@@ -392,13 +466,13 @@ __device__ __forceinline__ void fft_io(cx<R>* __restrict__ buf, int lgL, int lgT
     struct NoIn { cx<R> v[1]; } noin;
     {
         const int g = rem ? rem : LGM;
-        const bool last = left == g;
+        const bool last = ODD == 1 && left == g;
 #define MAGX_BODY(RADIX)                                                                                          \
     if (last)                                                                                                     \
-        stockham_io_pass<R, RADIX, INV, EMAX, SRC_LDS ? kSrcLds : kSrcFn, DST_LDS, LAYOUT, NC, HALF_IN, HALF_OUT, NT, TWL>(  \
+        stockham_io_pass<R, RADIX, INV, EMAX, SRC_LDS ? kSrcLds : kSrcFn, DST_LDS, LAYOUT, NC, HALF_IN, HALF_OUT, NT, TWL, ODD>(  \
             buf, lgL, lgNs, lgT, nseq, load, store, noin);                                                        \
     else                                                                                                          \
-        stockham_io_pass<R, RADIX, INV, EMAX, SRC_LDS ? kSrcLds : kSrcFn, true, LAYOUT, NC, HALF_IN, false, NT, TWL>(      \
+        stockham_io_pass<R, RADIX, INV, EMAX, SRC_LDS ? kSrcLds : kSrcFn, true, LAYOUT, NC, HALF_IN, false, NT, TWL, ODD>(      \
             buf, lgL, lgNs, lgT, nseq, load, store, noin);
         MAGX_RADIX_SWITCH(g, LGM)
 #undef MAGX_BODY
@@ -407,45 +481,50 @@ __device__ __forceinline__ void fft_io(cx<R>* __restrict__ buf, int lgL, int lgT
     }
     while (left > 0) {
         constexpr int RADIX = 1 << LGM;
-        if (left == LGM)
-            stockham_io_pass<R, RADIX, INV, EMAX, kSrcLds, DST_LDS, LAYOUT, NC, false, HALF_OUT, NT, TWL>(
+        if (ODD == 1 && left == LGM)
+            stockham_io_pass<R, RADIX, INV, EMAX, kSrcLds, DST_LDS, LAYOUT, NC, false, HALF_OUT, NT, TWL, ODD>(
                 buf, lgL, lgNs, lgT, nseq, load, store, noin);
         else
-            stockham_io_pass<R, RADIX, INV, EMAX, kSrcLds, true, LAYOUT, NC, false, false, NT, TWL>(
+            stockham_io_pass<R, RADIX, INV, EMAX, kSrcLds, true, LAYOUT, NC, false, false, NT, TWL, ODD>(
                 buf, lgL, lgNs, lgT, nseq, load, store, noin);
         lgNs += LGM;
         left -= LGM;
     }
+    if constexpr (ODD > 1)
+        stockham_io_pass<R, ODD, INV, EMAX, kSrcLds, DST_LDS, LAYOUT, NC, false, HALF_OUT, NT, TWL, ODD>(
+            buf, lgL, lgL, lgT, nseq, load, store, noin);
 }
 
 // Loads the first pass's inputs of one tile into `in` (lgL >= 1), in the
 // order the register-sourced first pass of fft_reg consumes them.
-template <typename R, int RAD, int EMAX, int LAYOUT, int NC, bool HIN, int NT, class Load>
+template <typename R, int RAD, int EMAX, int LAYOUT, int NC, bool HIN, int NT, int ODD = 1, class Load>
 __device__ __forceinline__ void first_load_rad(FirstIn<R, EMAX, HIN>& in, int lgL, int lgT, int nseq, Load& load) {
     constexpr int PER = EMAX / RAD > 0 ? EMAX / RAD : 1;
     constexpr int LGR = ilog2c(RAD);
     constexpr int RIN = HIN ? RAD / 2 : RAD;
     static_assert(PER * RIN <= FirstIn<R, EMAX, HIN>::N, "first-pass register budget");
     const int lgnb = lgL - LGR;
-    const unsigned total = (1u << lgnb) * (unsigned)nseq;
-    const unsigned tid = (unsigned)tid_opaque();
+    const unsigned nb = (unsigned)ODD << lgnb;
+    const unsigned total = nb * (unsigned)nseq;
+    const unsigned tid = (unsigned)tid_opaque<NT>();
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
         const unsigned t = tid + (unsigned)(i * NT);
         if (t < total) {
             unsigned b, j;
-            seq_split<LAYOUT, NC>(t, lgT, lgnb, (unsigned)nseq, b, j);
+            seq_split<LAYOUT, NC, ODD>(t, lgT, lgnb, (unsigned)nseq, b, j);
 #pragma unroll
-            for (int r = 0; r < RIN; ++r) in.v[i * RIN + r] = load((int)b, (int)(j + ((unsigned)r << lgnb)));
+            for (int r = 0; r < RIN; ++r) in.v[i * RIN + r] = load((int)b, (int)(j + (unsigned)r * nb));
         }
     }
 }
 
-template <typename R, int EMAX, int LAYOUT, int NC, bool HIN, int LGM = lgmax<EMAX>(), int NT = kNT, class Load>
+template <typename R, int EMAX, int LAYOUT, int NC, bool HIN, int LGM = lgmax<EMAX>(), int NT = kNT, int ODD = 1,
+          class Load>
 __device__ __forceinline__ void first_load(FirstIn<R, EMAX, HIN>& in, int lgL, int lgT, int nseq, Load load) {
     const int rem = lgL % LGM;
     const int g = rem ? rem : LGM;
-#define MAGX_BODY(RADIX) first_load_rad<R, RADIX, EMAX, LAYOUT, NC, HIN, NT>(in, lgL, lgT, nseq, load);
+#define MAGX_BODY(RADIX) first_load_rad<R, RADIX, EMAX, LAYOUT, NC, HIN, NT, ODD>(in, lgL, lgT, nseq, load);
     MAGX_RADIX_SWITCH(g, LGM)
 #undef MAGX_BODY
 }
@@ -460,7 +539,7 @@ __device__ __forceinline__ void first_apply_rad(FirstIn<R, EMAX, HIN>& in, int l
     constexpr int RIN = HIN ? RAD / 2 : RAD;
     const int lgnb = lgL - LGR;
     const unsigned total = (1u << lgnb) * (unsigned)nseq;
-    const unsigned tid = (unsigned)tid_opaque();
+    const unsigned tid = (unsigned)tid_opaque<NT>();
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
         const unsigned t = tid + (unsigned)(i * NT);
@@ -487,7 +566,7 @@ __device__ __forceinline__ void first_apply(FirstIn<R, EMAX, HIN>& in, int lgL, 
 // after_first() runs once the first pass has consumed them, typically to
 // issue the next tile's first_load.  Requires lgL >= 1.
 template <typename R, bool INV, int EMAX, bool DST_LDS, int LAYOUT, int NC, bool HALF_IN, bool HALF_OUT,
-          int LGM = lgmax<EMAX>(), int NT = kNT, bool TWL = false, class After, class Store>
+          int LGM = lgmax<EMAX>(), int NT = kNT, bool TWL = false, int ODD = 1, class After, class Store>
 __device__ __forceinline__ void fft_reg(cx<R>* __restrict__ buf, int lgL, int lgT, int nseq,
                                         FirstIn<R, EMAX, HALF_IN>& in, After after_first, Store store) {
     static_assert(LGM >= 3 && LGM <= lgmax<EMAX>(), "pass radix beyond the register budget");
@@ -497,13 +576,13 @@ __device__ __forceinline__ void fft_reg(cx<R>* __restrict__ buf, int lgL, int lg
     int lgNs = 0, left = lgL;
     {
         const int g = rem ? rem : LGM;
-        const bool last = left == g;
+        const bool last = ODD == 1 && left == g;
 #define MAGX_BODY(RADIX)                                                                                     \
     if (last)                                                                                                \
-        stockham_io_pass<R, RADIX, INV, EMAX, kSrcReg, DST_LDS, LAYOUT, NC, HALF_IN, HALF_OUT, NT, TWL>(              \
+        stockham_io_pass<R, RADIX, INV, EMAX, kSrcReg, DST_LDS, LAYOUT, NC, HALF_IN, HALF_OUT, NT, TWL, ODD>(         \
             buf, lgL, lgNs, lgT, nseq, none_load, store, in);                                                \
     else                                                                                                     \
-        stockham_io_pass<R, RADIX, INV, EMAX, kSrcReg, true, LAYOUT, NC, HALF_IN, false, NT, TWL>(buf, lgL, lgNs, lgT, \
+        stockham_io_pass<R, RADIX, INV, EMAX, kSrcReg, true, LAYOUT, NC, HALF_IN, false, NT, TWL, ODD>(buf, lgL, lgNs, lgT, \
                                                                                          nseq, none_load,    \
                                                                                          store, in);
         MAGX_RADIX_SWITCH(g, LGM)
@@ -514,15 +593,18 @@ __device__ __forceinline__ void fft_reg(cx<R>* __restrict__ buf, int lgL, int lg
     after_first();
     while (left > 0) {
         constexpr int RADIX = 1 << LGM;
-        if (left == LGM)
-            stockham_io_pass<R, RADIX, INV, EMAX, kSrcLds, DST_LDS, LAYOUT, NC, false, HALF_OUT, NT, TWL>(
+        if (ODD == 1 && left == LGM)
+            stockham_io_pass<R, RADIX, INV, EMAX, kSrcLds, DST_LDS, LAYOUT, NC, false, HALF_OUT, NT, TWL, ODD>(
                 buf, lgL, lgNs, lgT, nseq, none_load, store, noin);
         else
-            stockham_io_pass<R, RADIX, INV, EMAX, kSrcLds, true, LAYOUT, NC, false, false, NT, TWL>(
+            stockham_io_pass<R, RADIX, INV, EMAX, kSrcLds, true, LAYOUT, NC, false, false, NT, TWL, ODD>(
                 buf, lgL, lgNs, lgT, nseq, none_load, store, noin);
         lgNs += LGM;
         left -= LGM;
     }
+    if constexpr (ODD > 1)
+        stockham_io_pass<R, ODD, INV, EMAX, kSrcLds, DST_LDS, LAYOUT, NC, false, HALF_OUT, NT, TWL, ODD>(
+            buf, lgL, lgL, lgT, nseq, none_load, store, noin);
 }
 
 // Division of 0 <= n < 2^31 by a divisor fixed at launch: with

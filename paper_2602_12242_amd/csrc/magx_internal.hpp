@@ -7,10 +7,11 @@ namespace magx {
 
 // Geometry and buffer layout of one grid, derived on the host.
 //
-// Extended grid (Section II-B): P_a = smallest power of two >= 2 n_a (the
-// convolution is exact for any P_a >= 2 n_a - 1).  x is transformed real to
-// complex, so spectral rows hold Hx = Px/2 + 1 columns, stored with a row
-// stride Sx rounded up to 16 columns.
+// Extended grid (Section II-B): P_a = smallest power of two >= 2 n_a, along x
+// and y also 3 2^k or 5 2^k (extended_length in magx_api.cpp; the convolution
+// is exact for any P_a >= 2 n_a - 1).  x is transformed real to complex, so
+// spectral rows hold Hx = Px/2 + 1 columns, stored with a row stride Sx rounded
+// up to 16 columns.
 //
 // Spectral intermediates (complex, x fastest):
 //   X1 [3][nz][ny][Sx]   after the forward x pass; reused for the inverse-y output
@@ -23,7 +24,8 @@ struct Plan {
     int esize;                  // 4 or 8
     int nx, ny, nz;
     double dx, dy, dz;
-    int Px, Py, Pz, lgPx, lgPy, lgPz;
+    int Px, Py, Pz;
+    int lgPx, lgPy, lgPz;       // log2 of the power-of-two factor of each length
     int Lh, lgLh;               // Px/2: length of the half-size complex FFT of the x pass
     int Hx, Hy, Hz, Sx;
     long long ncell;            // cells of one member
@@ -49,6 +51,7 @@ struct Plan {
     // workspace layout (bytes): the non-finite flag word first, then X1, X2,
     // five fields and the per-block partials
     size_t off_flag, off_x1, off_x2, off_f[5], off_part, ws_bytes;
+    size_t static_bytes;        // workspace magx_step_static would need at power-of-two lengths
     size_t field_bytes;
     size_t tape_step_bytes, tape_extra_bytes;
     size_t spectrum_bytes, scratch_bytes;
@@ -79,7 +82,13 @@ struct Phys {
                           // non-finite output), or null when the call does not check
 };
 
-hipError_t launch_twiddle_init(hipStream_t s);
+// twiddle tables of the translation units
+hipError_t init_tw_tensor(hipStream_t s);
+hipError_t init_tw_conv32(hipStream_t s);
+hipError_t init_tw_conv64(hipStream_t s);
+hipError_t init_tw_pencil32(hipStream_t s);
+hipError_t init_tw_pencil64(hipStream_t s);
+hipError_t init_tw_mri(hipStream_t s);
 hipError_t build_tensor_spectrum(const Plan& pl, void* spectrum, void* scratch, hipStream_t s);
 
 // FFT convolution passes (conv.hip)

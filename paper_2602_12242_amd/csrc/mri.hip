@@ -19,11 +19,12 @@ namespace magx {
 
 // Slow stage: inverse x pass of the convolution output + slow local terms +
 // torque; r = wa*Sa + wb*Sb + wn*S (Sa, Sb earlier slow torques or null).
-template <typename R, bool BIG>
+template <typename R, bool BIG, int LN>
 __global__ void __launch_bounds__(kNT) mri_slow_kernel(const cx<R>* __restrict__ Y1, const R* __restrict__ y,
                                                        PG g, Phys<R> ph, int has_demag, R* __restrict__ S_out,
                                                        const R* __restrict__ Sa, const R* __restrict__ Sb, R wa,
                                                        R wb, R wn, R* __restrict__ r_out) {
+    pg_fix<LN>(g);
     const bool stream = stream_of<BIG>(g);
     extern __shared__ unsigned char smem_raw[];
     cx<R>* buf = reinterpret_cast<cx<R>*>(smem_raw);
@@ -41,9 +42,10 @@ __global__ void __launch_bounds__(kNT) mri_slow_kernel(const cx<R>* __restrict__
 #pragma unroll
     for (int c = 0; c < 3; ++c) hbv[c] = ph.hbm ? ph.hbm[mb * 3 + c] : ph.hb[c];
     const bool vec = (g.nx & 1) == 0;
-    if (has_demag) c2r_lines<R, BIG>(buf, Y1, g, mb, pen0, npen);
-    for (int e = threadIdx.x; e < npen << g.lgLq; e += kNT) {
-        const int p = e >> g.lgLq, n = e & ((1 << g.lgLq) - 1);
+    if (has_demag) c2r_lines<R, BIG, LN>(buf, Y1, g, mb, pen0, npen);
+    for (int e = threadIdx.x; e < slots_of<LN>(g, npen); e += kNT) {
+        int p, n;
+        slot_of<LN>(g, e, p, n);
         const int x0 = 2 * n;
         if (x0 >= g.nx) continue;
         const bool two = x0 + 1 < g.nx;
@@ -85,11 +87,12 @@ __global__ void __launch_bounds__(kNT) mri_slow_kernel(const cx<R>* __restrict__
 
 // One fast stage: F = R(v, H_exch(v)) + r; q <- Ak q + h F (q not read when
 // first); v_out = v + Bk q, renormalised if norm; r2c of v_out into X1 if fwd.
-template <typename R, bool BIG>
+template <typename R, bool BIG, int LN>
 __global__ void __launch_bounds__(kNT) mri_fast_kernel(const R* __restrict__ v, R* __restrict__ vout,
                                                        R* __restrict__ qbuf, const R* __restrict__ rbuf, PG g,
                                                        Phys<R> ph, R Ak, R Bk, R h, int first, int norm, int fwd,
                                                        cx<R>* __restrict__ X1) {
+    pg_fix<LN>(g);
     const bool stream = stream_of<BIG>(g);
     extern __shared__ unsigned char smem_raw[];
     cx<R>* buf = reinterpret_cast<cx<R>*>(smem_raw);
@@ -108,8 +111,9 @@ __global__ void __launch_bounds__(kNT) mri_fast_kernel(const R* __restrict__ v, 
 #pragma unroll 1
     for (int i = 0; i < maxslot<BIG>(); ++i) {
         const int e = threadIdx.x + i * kNT;
-        if (e >= npen << g.lgLq) continue;
-        const int p = e >> g.lgLq, n = e & ((1 << g.lgLq) - 1);
+        if (e >= slots_of<LN>(g, npen)) continue;
+        int p, n;
+        slot_of<LN>(g, e, p, n);
         const int x0 = 2 * n;
         if (x0 >= g.nx) {
             if (fwd) {
@@ -155,20 +159,30 @@ __global__ void __launch_bounds__(kNT) mri_fast_kernel(const R* __restrict__ v, 
         }
     }
     if (!fwd) return;
-    r2c_lines<R, BIG>(buf, X1, g, mb, pen0, npen);
+    r2c_lines<R, BIG, LN>(buf, X1, g, mb, pen0, npen);
 }
+
+// lines with an odd factor are compile-time lengths, the others runtime ones
+static int odd_line(const Plan& pl) { return odd_part(pl.Lh) > 1 ? pl.Lh : 0; }
+#define MAGX_LINE_LAUNCH(KERNEL, LINE, ...)                                                          \
+    do {                                                                                             \
+        const dim3 grid_((unsigned)pl.pencil_blocks), block_(kNT);                                   \
+        switch (LINE) {                                                                              \
+            MAGX_ODD_LINES(KERNEL, lds, __VA_ARGS__)                                                 \
+            default:                                                                                 \
+                if (pencil_big(pl))                                                                  \
+                    hipLaunchKernelGGL((KERNEL<R, true, 0>), grid_, block_, lds, s, __VA_ARGS__);    \
+                else                                                                                 \
+                    hipLaunchKernelGGL((KERNEL<R, false, 0>), grid_, block_, lds, s, __VA_ARGS__);   \
+        }                                                                                            \
+    } while (0)
 
 template <typename R>
 hipError_t launch_mri_slow(const Plan& pl, const Phys<R>& ph, const void* Y1, const R* y, int has_demag, R* S_out,
                            const R* Sa, const R* Sb, R wa, R wb, R wn, R* r_out, hipStream_t s) {
     const PG g = make_pg(pl);
     const size_t lds = has_demag ? pencil_lds(pl) : 0;
-    if (pencil_big(pl))
-        hipLaunchKernelGGL((mri_slow_kernel<R, true>), dim3(pl.pencil_blocks), dim3(kNT), lds, s,
-                           static_cast<const cx<R>*>(Y1), y, g, ph, has_demag, S_out, Sa, Sb, wa, wb, wn, r_out);
-    else
-        hipLaunchKernelGGL((mri_slow_kernel<R, false>), dim3(pl.pencil_blocks), dim3(kNT), lds, s,
-                           static_cast<const cx<R>*>(Y1), y, g, ph, has_demag, S_out, Sa, Sb, wa, wb, wn, r_out);
+    MAGX_LINE_LAUNCH(mri_slow_kernel, odd_line(pl), static_cast<const cx<R>*>(Y1), y, g, ph, has_demag, S_out, Sa, Sb, wa, wb, wn, r_out);
     return hipGetLastError();
 }
 
@@ -178,12 +192,7 @@ hipError_t launch_mri_fast(const Plan& pl, const Phys<R>& ph, const R* v, R* vou
     const PG g = make_pg(pl);
     const int fwd = X1 != nullptr;
     const size_t lds = fwd ? pencil_lds(pl) : 0;
-    if (pencil_big(pl))
-        hipLaunchKernelGGL((mri_fast_kernel<R, true>), dim3(pl.pencil_blocks), dim3(kNT), lds, s, v, vout, q, r, g,
-                           ph, Ak, Bk, h, first, norm, fwd, static_cast<cx<R>*>(X1));
-    else
-        hipLaunchKernelGGL((mri_fast_kernel<R, false>), dim3(pl.pencil_blocks), dim3(kNT), lds, s, v, vout, q, r,
-                           g, ph, Ak, Bk, h, first, norm, fwd, static_cast<cx<R>*>(X1));
+    MAGX_LINE_LAUNCH(mri_fast_kernel, odd_line(pl), v, vout, q, r, g, ph, Ak, Bk, h, first, norm, fwd, static_cast<cx<R>*>(X1));
     return hipGetLastError();
 }
 
@@ -196,5 +205,7 @@ template hipError_t launch_mri_fast<float>(const Plan&, const Phys<float>&, cons
                                            const float*, float, float, float, int, int, void*, hipStream_t);
 template hipError_t launch_mri_fast<double>(const Plan&, const Phys<double>&, const double*, double*, double*,
                                             const double*, double, double, double, int, int, void*, hipStream_t);
+
+MAGX_TW_INIT(init_tw_mri)
 
 }  // namespace magx

@@ -25,10 +25,10 @@ namespace magx {
 
 // ---- kernels -------------------------------------------------------------------
 
-template <typename R, bool BIG, int LG>
+template <typename R, bool BIG, int LN>
 __global__ void __launch_bounds__(kNT) xfwd_kernel(const R* __restrict__ f, cx<R>* __restrict__ X1, PG g,
                                                    const R* __restrict__ msp) {
-    pg_fix<LG>(g);
+    pg_fix<LN>(g);
     extern __shared__ unsigned char smem_raw[];
     cx<R>* buf = reinterpret_cast<cx<R>*>(smem_raw);
     // logical block -> member mb and its first pencil; members own contiguous block ranges
@@ -39,7 +39,7 @@ __global__ void __launch_bounds__(kNT) xfwd_kernel(const R* __restrict__ f, cx<R
     const long long mo = (long long)mb * 3 * g.N;   // member offset of vector fields
     f += mo;
     const bool vec = (g.nx & 1) == 0;
-    const int nitem = npen << g.lgLq;
+    const int nitem = slots_of<LN>(g, npen);
     // every cell pair of this thread is loaded first (one 8-byte load per
     // component when nx is even), so that their latencies overlap; the LDS
     // line entries are written afterwards
@@ -51,7 +51,8 @@ __global__ void __launch_bounds__(kNT) xfwd_kernel(const R* __restrict__ f, cx<R
 #pragma unroll
         for (int c = 0; c < 3; ++c) va[i][c] = vb[i][c] = (R)0;
         if (e >= nitem) continue;
-        const int p = e >> g.lgLq, n = e & ((1 << g.lgLq) - 1);
+        int p, n;
+        slot_of<LN>(g, e, p, n);
         const int x0 = 2 * n;
         if (x0 >= g.nx) continue;
         int y, z;
@@ -69,24 +70,25 @@ __global__ void __launch_bounds__(kNT) xfwd_kernel(const R* __restrict__ f, cx<R
     for (int i = 0; i < maxslot<BIG>(); ++i) {
         const int e = threadIdx.x + i * kNT;
         if (e >= nitem) continue;
-        const int p = e >> g.lgLq, n = e & ((1 << g.lgLq) - 1);
+        int p, n;
+        slot_of<LN>(g, e, p, n);
 #pragma unroll
         for (int c = 0; c < 3; ++c) buf[(3 * p + c) * g.Lh + n] = mk<R>(s0[i] * va[i][c], s1[i] * vb[i][c]);
     }
-    r2c_lines<R, BIG>(buf, X1, g, mb, pen0, npen);
+    r2c_lines<R, BIG, LN>(buf, X1, g, mb, pen0, npen);
 }
 
 // mode: 0 -> write H (with bias if with_bias); 1 -> energy partials (m.H_term).
 // RED: the block sums (energy, or the sum of the input field) are wanted; the
 // plain field evaluation is a kernel of its own without their accumulators,
 // which keeps it within the registers of five waves per SIMD.
-template <typename R, bool BIG, int LG, bool RED>
+template <typename R, bool BIG, int LN, bool RED>
 __device__ __forceinline__ void field_body(const cx<R>* __restrict__ Y1, const R* __restrict__ f,
                                            R* __restrict__ H, PG g, Phys<R> ph, int has_demag,
                                            int with_bias, int energy, int sum_input,
                                            double* __restrict__ partials) {
     if constexpr (!RED) energy = sum_input = 0;
-    pg_fix<LG>(g);
+    pg_fix<LN>(g);
     const bool stream = stream_of<BIG>(g);
     extern __shared__ unsigned char smem_raw[];
     cx<R>* buf = reinterpret_cast<cx<R>*>(smem_raw);
@@ -103,10 +105,11 @@ __device__ __forceinline__ void field_body(const cx<R>* __restrict__ Y1, const R
 #pragma unroll
     for (int c = 0; c < 3; ++c) hbv[c] = ph.hbm ? ph.hbm[mb * 3 + c] : ph.hb[c];
     const bool vec = (g.nx & 1) == 0;
-    if (has_demag) c2r_lines<R, BIG>(buf, Y1, g, mb, pen0, npen);
+    if (has_demag) c2r_lines<R, BIG, LN>(buf, Y1, g, mb, pen0, npen);
     double acc[6] = {0, 0, 0, 0, 0, 0};
-    for (int e = threadIdx.x; e < npen << g.lgLq; e += kNT) {
-        const int p = e >> g.lgLq, n = e & ((1 << g.lgLq) - 1);
+    for (int e = threadIdx.x; e < slots_of<LN>(g, npen); e += kNT) {
+        int p, n;
+        slot_of<LN>(g, e, p, n);
         const int x0 = 2 * n;
         if (x0 >= g.nx) continue;
         const bool two = x0 + 1 < g.nx;
@@ -164,26 +167,26 @@ __device__ __forceinline__ void field_body(const cx<R>* __restrict__ Y1, const R
     }
 }
 
-template <typename R, bool BIG, int LG>
+template <typename R, bool BIG, int LN>
 __global__ void __launch_bounds__(kNT) field_kernel(const cx<R>* __restrict__ Y1, const R* __restrict__ f,
                                                     R* __restrict__ H, PG g, Phys<R> ph, int has_demag,
                                                     int with_bias, int energy, int sum_input,
                                                     double* __restrict__ partials) {
-    field_body<R, BIG, LG, false>(Y1, f, H, g, ph, has_demag, with_bias, energy, sum_input, partials);
+    field_body<R, BIG, LN, false>(Y1, f, H, g, ph, has_demag, with_bias, energy, sum_input, partials);
 }
 
-template <typename R, bool BIG, int LG>
+template <typename R, bool BIG, int LN>
 __global__ void __launch_bounds__(kNT) field_reduce_kernel(const cx<R>* __restrict__ Y1, const R* __restrict__ f,
                                                            R* __restrict__ H, PG g, Phys<R> ph, int has_demag,
                                                            int with_bias, int energy, int sum_input,
                                                            double* __restrict__ partials) {
-    field_body<R, BIG, LG, true>(Y1, f, H, g, ph, has_demag, with_bias, energy, sum_input, partials);
+    field_body<R, BIG, LN, true>(Y1, f, H, g, ph, has_demag, with_bias, energy, sum_input, partials);
 }
 
-template <typename R, bool BIG, int LG>
+template <typename R, bool BIG, int LN>
 __global__ void __launch_bounds__(kNT) stage_kernel(const cx<R>* Y1, cx<R>* X1, PG g,
                                                     Phys<R> ph, StageArgs<R> a, int has_demag) {
-    pg_fix<LG>(g);
+    pg_fix<LN>(g);
     const bool stream = stream_of<BIG>(g);
     extern __shared__ unsigned char smem_raw[];
     cx<R>* buf = reinterpret_cast<cx<R>*>(smem_raw);
@@ -206,7 +209,7 @@ __global__ void __launch_bounds__(kNT) stage_kernel(const cx<R>* Y1, cx<R>* X1, 
 #pragma unroll
     for (int c = 0; c < 3; ++c) hbv[c] = ph.hbm ? ph.hbm[mb * 3 + c] : ph.hb[c];
     const bool vec = (g.nx & 1) == 0;
-    if (has_demag) c2r_lines<R, BIG>(buf, Y1, g, mb, pen0, npen);
+    if (has_demag) c2r_lines<R, BIG, LN>(buf, Y1, g, mb, pen0, npen);
     // classical RK4 tableau
     const R bw[4] = {(R)(1.0 / 6.0), (R)(1.0 / 3.0), (R)(1.0 / 3.0), (R)(1.0 / 6.0)};
     const R cw[4] = {(R)0, (R)0.5, (R)0.5, (R)1};
@@ -220,8 +223,9 @@ __global__ void __launch_bounds__(kNT) stage_kernel(const cx<R>* Y1, cx<R>* X1, 
 #pragma unroll 1
     for (int i = 0; i < maxslot<BIG>(); ++i) {
         const int e = threadIdx.x + i * kNT;
-        if (e >= npen << g.lgLq) continue;
-        const int p = e >> g.lgLq, n = e & ((1 << g.lgLq) - 1);
+        if (e >= slots_of<LN>(g, npen)) continue;
+        int p, n;
+        slot_of<LN>(g, e, p, n);
         const int x0 = 2 * n;
         if (x0 >= g.nx) {
             if (fwd) {
@@ -303,13 +307,13 @@ __global__ void __launch_bounds__(kNT) stage_kernel(const cx<R>* Y1, cx<R>* X1, 
         }
     }
     if (!fwd) return;
-    r2c_lines<R, BIG>(buf, X1, g, mb, pen0, npen);
+    r2c_lines<R, BIG, LN>(buf, X1, g, mb, pen0, npen);
 }
 
-template <typename R, bool BIG, int LG>
+template <typename R, bool BIG, int LN>
 __global__ void __launch_bounds__(kNT) bstart_kernel(cx<R>* __restrict__ X1, PG g, Phys<R> ph, StartArgs<R> a,
                                                      int has_demag, double* __restrict__ partials) {
-    pg_fix<LG>(g);
+    pg_fix<LN>(g);
     const bool stream = stream_of<BIG>(g);
     extern __shared__ unsigned char smem_raw[];
     cx<R>* buf = reinterpret_cast<cx<R>*>(smem_raw);
@@ -337,8 +341,9 @@ __global__ void __launch_bounds__(kNT) bstart_kernel(cx<R>* __restrict__ X1, PG 
 #pragma unroll 1
     for (int i = 0; i < maxslot<BIG>(); ++i) {
         const int e = threadIdx.x + i * kNT;
-        if (e >= npen << g.lgLq) continue;
-        const int p = e >> g.lgLq, n = e & ((1 << g.lgLq) - 1);
+        if (e >= slots_of<LN>(g, npen)) continue;
+        int p, n;
+        slot_of<LN>(g, e, p, n);
         const int x0 = 2 * n;
         if (x0 >= g.nx) {
             if (has_demag) {
@@ -398,14 +403,14 @@ __global__ void __launch_bounds__(kNT) bstart_kernel(cx<R>* __restrict__ X1, PG 
         }
     }
     if (!has_demag) return;
-    r2c_lines<R, BIG>(buf, X1, g, mb, pen0, npen);
+    r2c_lines<R, BIG, LN>(buf, X1, g, mb, pen0, npen);
 }
 
-template <typename R, bool BIG, int LG>
+template <typename R, bool BIG, int LN>
 __global__ void __launch_bounds__(kNT) bstage_kernel(const cx<R>* Y1, cx<R>* X1, PG g,
                                                      Phys<R> ph, BackArgs<R> a, int has_demag,
                                                      double* __restrict__ partials) {
-    pg_fix<LG>(g);
+    pg_fix<LN>(g);
     const bool stream = stream_of<BIG>(g);
     extern __shared__ unsigned char smem_raw[];
     cx<R>* buf = reinterpret_cast<cx<R>*>(smem_raw);
@@ -427,7 +432,7 @@ __global__ void __launch_bounds__(kNT) bstage_kernel(const cx<R>* Y1, cx<R>* X1,
     if (a.yprev) a.yprev += mo;
     if (a.nxs) a.nxs += mo1;
     const bool vec = (g.nx & 1) == 0;
-    if (has_demag) c2r_lines<R, BIG>(buf, Y1, g, mb, pen0, npen);
+    if (has_demag) c2r_lines<R, BIG, LN>(buf, Y1, g, mb, pen0, npen);
     const R bw[4] = {(R)(1.0 / 6.0), (R)(1.0 / 3.0), (R)(1.0 / 3.0), (R)(1.0 / 6.0)};
     const R cw[4] = {(R)0, (R)0.5, (R)0.5, (R)1};
     const int s = a.stage;
@@ -440,8 +445,9 @@ __global__ void __launch_bounds__(kNT) bstage_kernel(const cx<R>* Y1, cx<R>* X1,
 #pragma unroll 1
     for (int i = 0; i < maxslot<BIG>(); ++i) {
         const int e = threadIdx.x + i * kNT;
-        if (e >= npen << g.lgLq) continue;
-        const int p = e >> g.lgLq, n = e & ((1 << g.lgLq) - 1);
+        if (e >= slots_of<LN>(g, npen)) continue;
+        int p, n;
+        slot_of<LN>(g, e, p, n);
         const int x0 = 2 * n;
         if (x0 >= g.nx) {
             if (fwd) {
@@ -536,7 +542,7 @@ __global__ void __launch_bounds__(kNT) bstage_kernel(const cx<R>* Y1, cx<R>* X1,
         }
     }
     if (!fwd) return;
-    r2c_lines<R, BIG>(buf, X1, g, mb, pen0, npen);
+    r2c_lines<R, BIG, LN>(buf, X1, g, mb, pen0, npen);
 }
 
 template <typename R>
@@ -553,7 +559,7 @@ __global__ void rhs_kernel(const R* __restrict__ m, const R* __restrict__ H, R* 
     store3(out, N, id, k);
 }
 
-__global__ void fill_zero_kernel(double* p, long long n) {
+static __global__ void fill_zero_kernel(double* p, long long n) {
     const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) p[i] = 0.0;
 }
@@ -576,7 +582,7 @@ __global__ void reduce_partials_kernel(const double* __restrict__ partials, int 
 // e_out[6 mb + ...]: demag, exch, dmi, anis, zeeman, total (J) of member mb.
 // pref = -(mu0 Ms V)/2, vku_cell = V Ku (anisotropy constant term per magnetic
 // cell; partial 5 counts the magnetic cells).
-__global__ void energy_finish_kernel(const double* __restrict__ partials, int bpm, double pref,
+static __global__ void energy_finish_kernel(const double* __restrict__ partials, int bpm, double pref,
                                      double vku_cell, double* e_out) {
     __shared__ double red[kNT];
     const int mb = blockIdx.x;
@@ -608,23 +614,24 @@ __global__ void copy_kernel(const R* __restrict__ src, R* __restrict__ dst, long
 
 // ---- launchers -----------------------------------------------------------------
 
-// Pencil kernel launch: the power-of-two line lengths 2^7 ... 2^10 with
-// compile-time geometry, every other size with runtime geometry.
-#define MAGX_PENCIL_LAUNCH(KERNEL, ...)                                                                 \
-    do {                                                                                                \
-        const dim3 grid_((unsigned)pl.pencil_blocks), block_(kNT);                                      \
-        const size_t lds_ = pencil_lds(pl);                                                             \
-        switch (pencil_lg(pl)) {                                                                        \
-            case 7: hipLaunchKernelGGL((KERNEL<R, false, 7>), grid_, block_, lds_, s, __VA_ARGS__); break;  \
-            case 8: hipLaunchKernelGGL((KERNEL<R, false, 8>), grid_, block_, lds_, s, __VA_ARGS__); break;  \
-            case 9: hipLaunchKernelGGL((KERNEL<R, false, 9>), grid_, block_, lds_, s, __VA_ARGS__); break;  \
-            case 10: hipLaunchKernelGGL((KERNEL<R, false, 10>), grid_, block_, lds_, s, __VA_ARGS__); break; \
-            default:                                                                                    \
-                if (pencil_big(pl))                                                                     \
-                    hipLaunchKernelGGL((KERNEL<R, true, 0>), grid_, block_, lds_, s, __VA_ARGS__);      \
-                else                                                                                    \
-                    hipLaunchKernelGGL((KERNEL<R, false, 0>), grid_, block_, lds_, s, __VA_ARGS__);     \
-        }                                                                                               \
+// Pencil kernel launch: the line lengths of pencil_line with compile-time
+// geometry, every other size with runtime geometry.
+#define MAGX_PENCIL_LAUNCH(KERNEL, ...)                                                                     \
+    do {                                                                                                    \
+        const dim3 grid_((unsigned)pl.pencil_blocks), block_(kNT);                                          \
+        const size_t lds_ = pencil_lds(pl);                                                                 \
+        switch (pencil_line(pl)) {                                                                          \
+            MAGX_ODD_LINES(KERNEL, lds_, __VA_ARGS__)                                                       \
+            case 128: hipLaunchKernelGGL((KERNEL<R, false, 128>), grid_, block_, lds_, s, __VA_ARGS__); break;   \
+            case 256: hipLaunchKernelGGL((KERNEL<R, false, 256>), grid_, block_, lds_, s, __VA_ARGS__); break;   \
+            case 512: hipLaunchKernelGGL((KERNEL<R, false, 512>), grid_, block_, lds_, s, __VA_ARGS__); break;   \
+            case 1024: hipLaunchKernelGGL((KERNEL<R, false, 1024>), grid_, block_, lds_, s, __VA_ARGS__); break; \
+            default:                                                                                        \
+                if (pencil_big(pl))                                                                         \
+                    hipLaunchKernelGGL((KERNEL<R, true, 0>), grid_, block_, lds_, s, __VA_ARGS__);          \
+                else                                                                                        \
+                    hipLaunchKernelGGL((KERNEL<R, false, 0>), grid_, block_, lds_, s, __VA_ARGS__);         \
+        }                                                                                                   \
     } while (0)
 
 template <typename R>
@@ -676,10 +683,12 @@ hipError_t launch_rhs(const Plan& pl, const Phys<R>& ph, const R* m, const R* H,
     return hipGetLastError();
 }
 
+#if MAGX_REAL == 32
 hipError_t launch_fill_zero(double* p, long long n, hipStream_t s) {
     hipLaunchKernelGGL(fill_zero_kernel, dim3((unsigned)((n + kNT - 1) / kNT)), dim3(kNT), 0, s, p, n);
     return hipGetLastError();
 }
+#endif
 
 template <typename R>
 hipError_t launch_reduce_partials(const double* partials, int nbatch, int blocks_per_member, int nval, R* out,
@@ -689,12 +698,14 @@ hipError_t launch_reduce_partials(const double* partials, int nbatch, int blocks
     return hipGetLastError();
 }
 
+#if MAGX_REAL == 32
 hipError_t launch_energy_finish(const double* partials, int nbatch, int blocks_per_member, double pref,
                                 double vku_cell, double* e_out, hipStream_t s) {
     hipLaunchKernelGGL(energy_finish_kernel, dim3(nbatch), dim3(kNT), 0, s, partials, blocks_per_member, pref,
                        vku_cell, e_out);
     return hipGetLastError();
 }
+#endif
 
 template <typename R>
 hipError_t launch_copy(const R* src, R* dst, long long n, hipStream_t s) {
@@ -716,7 +727,12 @@ hipError_t launch_copy(const R* src, R* dst, long long n, hipStream_t s) {
     template hipError_t launch_reduce_partials<R>(const double*, int, int, int, R*, int, hipStream_t);          \
     template hipError_t launch_copy<R>(const R*, R*, long long, hipStream_t);
 
+#if MAGX_REAL == 32
 MAGX_INST(float)
+MAGX_TW_INIT(init_tw_pencil32)
+#else
 MAGX_INST(double)
+MAGX_TW_INIT(init_tw_pencil64)
+#endif
 
 }  // namespace magx

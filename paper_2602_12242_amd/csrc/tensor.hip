@@ -27,18 +27,7 @@
 
 namespace magx {
 
-__device__ float2 g_tw32[kTwN];
-__device__ double2 g_tw64[kTwN];
-
-__global__ void twiddle_init_kernel() {
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k < kTwN) {
-        double s, c;
-        sincospi(-2.0 * (double)k / (double)kTwN, &s, &c);
-        g_tw64[k] = make_double2(c, s);
-        g_tw32[k] = make_float2((float)c, (float)s);
-    }
-}
+MAGX_TW_INIT(init_tw_tensor)
 
 // ---- Newell auxiliary functions (double) ----------------------------------------
 __device__ double newell_f(double x, double y, double z) {
@@ -177,7 +166,7 @@ __global__ void __launch_bounds__(kNT) newell_octant_kernel(double* __restrict__
 // (orow = Hx, ostride = tz, oslab = ntz, and Hz = K).
 template <typename TO, bool TILED>
 __global__ void __launch_bounds__(kNT) axis_transform_kernel(const double* __restrict__ in, TO* __restrict__ out,
-                                                             int Q, int J, int K, int P, int lgP, unsigned odd,
+                                                             int Q, int J, int K, int P, unsigned odd,
                                                              double scale, unsigned neg, long long islab,
                                                              int orow, int ostride, long long oslab) {
     constexpr int TQ = 64, TK = 32, TJ = 32;
@@ -190,7 +179,10 @@ __global__ void __launch_bounds__(kNT) axis_transform_kernel(const double* __res
     const int tq = threadIdx.x & 15;     // 16 x 4 = 64 q
     const int tk = threadIdx.x >> 4;     // 16 x 2 = 32 k
     double acc[2][4] = {{0, 0, 0, 0}, {0, 0, 0, 0}};
-    const int twshift = kTwLog - lgP;
+    // roots of unity of order P in the table of P's odd factor
+    const int fo = odd_part(P);
+    const int twmul = tw_size(fo) / P;
+    const double2* tab = g_tw64 + tw_offset(fo);
     for (int j0 = 0; j0 < J; j0 += TJ) {
         for (int e = threadIdx.x; e < TQ * TJ; e += kNT) {
             const int jj = e % TJ, qq = e / TJ;
@@ -202,8 +194,8 @@ __global__ void __launch_bounds__(kNT) axis_transform_kernel(const double* __res
             const int k = k0 + kk, j = j0 + jj;
             double v = 0.0;
             if (j < J) {
-                const int idx = (int)(((long long)k * j) & (P - 1)) << twshift;
-                const double2 w = g_tw64[idx];     // (cos t, -sin t)
+                const unsigned kj = (unsigned)k * (unsigned)j;     // < 2^23
+                const double2 w = tab[(fo == 1 ? kj & (unsigned)(P - 1) : kj % (unsigned)P) * (unsigned)twmul];   // (cos t, -sin t)
                 v = isodd ? -w.y : w.x;
                 if (j > 0) v *= 2.0;
             }
@@ -286,11 +278,6 @@ static constexpr unsigned kOddX = (1u << 3) | (1u << 4);
 static constexpr unsigned kOddY = (1u << 3) | (1u << 5);
 static constexpr unsigned kOddZ = (1u << 4) | (1u << 5);
 
-hipError_t launch_twiddle_init(hipStream_t s) {
-    hipLaunchKernelGGL(twiddle_init_kernel, dim3(kTwN / kNT), dim3(kNT), 0, s);
-    return hipGetLastError();
-}
-
 // The tensor's Nyquist column kx = Hx - 1 (column 0 of each row's last tile)
 // once more, for the z pass's Nyquist units: blocks [6][Hz][tz] like the
 // column tiles', column c of block b holding row q = b tz + c (rows q >= Py/2
@@ -324,7 +311,7 @@ hipError_t build_tensor_spectrum(const Plan& pl, void* spectrum, void* scratch, 
     {
         const int Q = nz * ny, J = nx, K = pl.Hx;
         dim3 grid((Q + 63) / 64, (K + 31) / 32, 6);
-        hipLaunchKernelGGL((axis_transform_kernel<double, false>), grid, dim3(kNT), 0, s, oct, t1, Q, J, K, pl.Px, pl.lgPx,
+        hipLaunchKernelGGL((axis_transform_kernel<double, false>), grid, dim3(kNT), 0, s, oct, t1, Q, J, K, pl.Px,
                            kOddX, 1.0, 0u, n, Q, Q, (long long)K * Q);
         if (hipGetLastError() != hipSuccess) return hipErrorLaunchFailure;
     }
@@ -332,7 +319,7 @@ hipError_t build_tensor_spectrum(const Plan& pl, void* spectrum, void* scratch, 
     {
         const int Q = pl.Hx * nz, J = ny, K = pl.Hy;
         dim3 grid((Q + 63) / 64, (K + 31) / 32, 6);
-        hipLaunchKernelGGL((axis_transform_kernel<double, false>), grid, dim3(kNT), 0, s, t1, t2, Q, J, K, pl.Py, pl.lgPy,
+        hipLaunchKernelGGL((axis_transform_kernel<double, false>), grid, dim3(kNT), 0, s, t1, t2, Q, J, K, pl.Py,
                            kOddY, 1.0, 0u, (long long)pl.Hx * nz * ny, Q, Q, (long long)K * Q);
         if (hipGetLastError() != hipSuccess) return hipErrorLaunchFailure;
     }
@@ -346,11 +333,11 @@ hipError_t build_tensor_spectrum(const Plan& pl, void* spectrum, void* scratch, 
         const unsigned offdiag = (1u << 3) | (1u << 4) | (1u << 5);
         if (pl.dtype == MAGX_F32) {
             hipLaunchKernelGGL((axis_transform_kernel<float, true>), grid, dim3(kNT), 0, s, t2,
-                               static_cast<float*>(spectrum), Q, J, K, pl.Pz, pl.lgPz, kOddZ, sc, offdiag,
+                               static_cast<float*>(spectrum), Q, J, K, pl.Pz, kOddZ, sc, offdiag,
                                (long long)pl.Hy * pl.Hx * nz, pl.Hx, pl.tz, (long long)pl.ntz);
         } else {
             hipLaunchKernelGGL((axis_transform_kernel<double, true>), grid, dim3(kNT), 0, s, t2,
-                               static_cast<double*>(spectrum), Q, J, K, pl.Pz, pl.lgPz, kOddZ, sc, offdiag,
+                               static_cast<double*>(spectrum), Q, J, K, pl.Pz, kOddZ, sc, offdiag,
                                (long long)pl.Hy * pl.Hx * nz, pl.Hx, pl.tz, (long long)pl.ntz);
         }
         if (hipGetLastError() != hipSuccess) return hipErrorLaunchFailure;

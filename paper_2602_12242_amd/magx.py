@@ -207,12 +207,14 @@ class Context:
 
     def spectrum_array(self):
         """The stored tensor spectrum as a logical (6, Hz, Hy, Hx) array (for tests)."""
-        nx, ny, nz = self.n
-        Px, Py, Pz = (max(2, 1 << (2 * v - 1).bit_length()) for v in (nx, ny, nz))
-        Hx = Px // 2 + 1
         dims = (ctypes.c_int * 5)()
         _check(self.lib.magx_spectrum_layout(self.h, dims), "magx_spectrum_layout")
         Hy, ntz, six, Hz, tz = (int(v) for v in dims)
+        nx, ny, nz = self.n
+        Px, Py, Pz = max(2, 1 << (2 * nx - 1).bit_length()), 2 * (Hy - 1), 2 * (Hz - 1)
+        if nx * ny * nz >= 1 << 16 and Px >= 256:      # 5/8 or 3/4 of the power of two where that is enough
+            Px = next((c for c in (Px // 8 * 5, Px // 4 * 3) if 2 * nx <= c <= 1536), Px)
+        Hx = Px // 2 + 1
         el = self.spectrum.view(self.tdtype)[: Hy * ntz * six * Hz * tz]
         arr = el.view(Hy, ntz, six, Hz, tz).permute(2, 3, 0, 1, 4).reshape(six, Hz, Hy, ntz * tz)
         return arr[..., :Hx], (Px, Py, Pz)

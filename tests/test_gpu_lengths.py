@@ -1,0 +1,96 @@
+"""GPU parity at extended lengths with an odd factor (3 2^k and 5 2^k along x
+and y, taken from 2^16 cells on): every such line length of the x and y
+passes once, plus the grid just below the threshold, against the FP64 oracle
+on its own extended grid of length 2n.
+
+Bars as in test_gpu_parity.py: double precision 1e-11, single precision 1e-5
+(1e-10 and 1e-4 for the step's reverse mode)."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+pytestmark = pytest.mark.gpu
+
+from oracle import adjoint as oadj  # noqa: E402
+from oracle import field as ofield  # noqa: E402
+from oracle import llg as ollg  # noqa: E402
+from oracle import mri as omri  # noqa: E402
+from oracle import newell as onewell  # noqa: E402
+from oracle.params import Grid, Params  # noqa: E402
+from workloads import random_unit_field, random_vector_field  # noqa: E402
+
+MAT = dict(Ms=1e6, A=1.6e-11, D=2.5e-3, Ku=8e5, eK=(0.0, 0.6, 0.8), alpha=0.1, Hbias=(1e3, -2e3, 5e3), terms=31)
+D = (2e-9, 2.5e-9, 2e-9)
+# grid: extended lengths (Px, Py) in single precision
+GRIDS = {
+    (73, 130, 7): (160, 320),
+    (96, 192, 4): (192, 384),
+    (160, 80, 6): (320, 160),
+    (191, 96, 4): (384, 192),
+    (311, 75, 3): (640, 160),
+    (384, 171, 1): (768, 384),
+    (640, 107, 1): (1280, 256),
+    (700, 311, 1): (1536, 640),
+    (86, 384, 2): (192, 768),
+    (255, 257, 1): (512, 1024),    # 65535 cells: one short of the threshold, powers of two
+}
+_SETUP = {}
+
+
+def _setup(n):
+    if n not in _SETUP:
+        g = Grid(*n, *D)
+        _SETUP[n] = (g, Params(**MAT), onewell.spectrum(g))
+    return _SETUP[n]
+
+
+def _ctx(n, dtype):
+    from paper_2602_12242_amd import magx
+    return magx.Context(n, D, dtype=dtype), magx.make_params(**MAT)
+
+
+def _dev(a, dtype):
+    return torch.from_numpy(np.ascontiguousarray(a)).to("cuda", torch.float32 if dtype == 0 else torch.float64)
+
+
+def _err(a, b):
+    a, b = np.asarray(a, dtype=np.float64), np.asarray(b, dtype=np.float64)
+    return np.sqrt(((a - b) ** 2).sum(0)).max() / np.sqrt((b ** 2).sum(0)).max()
+
+
+@pytest.mark.parametrize("n", list(GRIDS))
+@pytest.mark.parametrize("dtype", [1, 0])
+def test_field_step_and_reverse_match_oracle(n, dtype):
+    g, p, spec = _setup(n)
+    tol = 1e-11 if dtype == 1 else 1e-5
+    ctx, q = _ctx(n, dtype)
+    arr, (Px, Py, Pz) = ctx.spectrum_array()
+    assert (Px, Py) == GRIDS[n] and arr.shape[1:] == (Pz // 2 + 1, Py // 2 + 1, Px // 2 + 1)
+    m = random_unit_field(n, 601, 2).astype(np.float32)
+    m64 = m.astype(np.float64)
+    assert _err(ctx.heff(_dev(m, dtype), q).cpu().numpy(), ofield.heff(g, p, m64, spec)) <= tol
+    gH = random_vector_field(n, 602).astype(np.float32)
+    gm, _ = ctx.heff_backward(_dev(gH, dtype), q)
+    assert _err(gm.cpu().numpy(), ofield.linear_part(g, p, gH.astype(np.float64), spec)) <= tol
+    dt = 5e-14
+    mg, tape = _dev(m, dtype), ctx.tape(1)
+    ctx.step(mg, q, dt, 1, tape=tape)
+    assert np.abs(mg.cpu().numpy() - ollg.rk4_step(g, p, m64, dt, spec)).max() <= tol
+    ref, refh = oadj.rk4_step_vjp(g, p, m64, dt, gH.astype(np.float64), spec)
+    lam, gh = _dev(gH, dtype), torch.zeros(3, dtype=mg.dtype, device="cuda")
+    ctx.step_backward(tape, 1, q, dt, lam, gh)
+    assert _err(lam.cpu().numpy(), ref) <= 10 * tol
+    assert np.abs(gh.cpu().numpy() - refh).max() <= 10 * tol * np.abs(refh).max()
+
+
+@pytest.mark.parametrize("n", [(640, 107, 1), (73, 130, 7)])
+@pytest.mark.parametrize("dtype", [1, 0])
+def test_multirate_step_matches_oracle(n, dtype):
+    g, p, spec = _setup(n)
+    m = random_unit_field(n, 603, 3).astype(np.float32)
+    ctx, q = _ctx(n, dtype)
+    mg = _dev(m, dtype)
+    ctx.step_mri(mg, q, 1e-13, 1, 1e-14)
+    ref = omri.mri_run(g, p, m.astype(np.float64), 1e-13, 1e-14, 1, spec)
+    assert _err(mg.cpu().numpy(), ref) <= (1e-11 if dtype == 1 else 1e-5)
