@@ -382,6 +382,125 @@ __device__ __forceinline__ void local_field_pair(const R* __restrict__ f, const 
     }
 }
 
+// The same without a magnetisation profile, for the cell pair at element id =
+// pen nx + x0 of row pen = z ny + y.  Accesses are a uniform base per component
+// plus one 32-bit byte offset per neighbour (a component of a member is below
+// 2^32 bytes: the plan's limits keep N below 2^29 elements), and a neighbour
+// outside the grid is loaded at the cell itself, which is its ghost already
+// except for the DMI rotation, added on the boundary cells.
+template <typename R>
+__device__ __forceinline__ void load_pair32(const R* __restrict__ f, long long N, unsigned off, bool vec, bool two,
+                                            R a[3], R b[3], bool stream = false) {
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        const char* p = reinterpret_cast<const char*>(f + c * N);
+        if (vec) {
+            const cx<R>* q = reinterpret_cast<const cx<R>*>(p + off);
+            const cx<R> v = stream ? ld_stream<R>(q) : *q;
+            a[c] = v.x;
+            b[c] = v.y;
+        } else {
+            a[c] = *reinterpret_cast<const R*>(p + off);
+            const R v1 = *reinterpret_cast<const R*>(p + (off + (two ? (unsigned)sizeof(R) : 0u)));
+            b[c] = two ? v1 : (R)0;
+        }
+    }
+}
+
+template <typename R>
+__device__ __forceinline__ void store_pair32(R* __restrict__ f, long long N, unsigned off, bool vec, bool two,
+                                             const R a[3], const R b[3], bool stream = false) {
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        char* p = reinterpret_cast<char*>(f + c * N);
+        if (vec) {
+            cx<R>* q = reinterpret_cast<cx<R>*>(p + off);
+            if (stream) st_stream<R>(q, mk<R>(a[c], b[c]));
+            else *q = mk<R>(a[c], b[c]);
+        } else {
+            R* q = reinterpret_cast<R*>(p + off);
+            q[0] = a[c];
+            if (two) q[1] = b[c];
+        }
+    }
+}
+
+template <typename R>
+__device__ __forceinline__ void local_field_plain(const R* __restrict__ f, const PG& g, int x0, int y, int z,
+                                                  unsigned off, bool vec, bool two, const Phys<R>& ph, R m[2][3],
+                                                  R h[2][3]) {
+    constexpr unsigned es = (unsigned)sizeof(R);
+    const long long N = g.N;
+    load_pair32(f, N, off, vec, two, m[0], m[1]);
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+#pragma unroll
+        for (int c = 0; c < 3; ++c) h[q][c] = (R)0;
+    if (ph.terms & (MAGX_EXCH | MAGX_DMI)) {
+        const unsigned rowb = (unsigned)g.nx * es, planeb = (unsigned)g.ny * rowb;
+        const bool gxl = x0 > 0, gxr = x0 + (two ? 2 : 1) < g.nx;
+        const bool gyp = y + 1 < g.ny, gym = y > 0, gzp = z + 1 < g.nz, gzm = z > 0;
+        const unsigned ol = gxl ? off - es : off, orr = off + ((two ? 1u : 0u) + (gxr ? 1u : 0u)) * es;
+        R xl[3], xr[3], yp[2][3], ym[2][3], zp[2][3], zm[2][3];
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            const char* p = reinterpret_cast<const char*>(f + c * N);
+            xl[c] = *reinterpret_cast<const R*>(p + ol);
+            xr[c] = *reinterpret_cast<const R*>(p + orr);
+        }
+        load_pair32(f, N, gyp ? off + rowb : off, vec, two, yp[0], yp[1]);
+        load_pair32(f, N, gym ? off - rowb : off, vec, two, ym[0], ym[1]);
+        load_pair32(f, N, gzp ? off + planeb : off, vec, two, zp[0], zp[1]);
+        load_pair32(f, N, gzm ? off - planeb : off, vec, two, zm[0], zm[1]);
+        if (ph.terms & MAGX_DMI) {
+            const R kdx = ph.kap * ph.dx, kdy = ph.kap * ph.dy;
+            if (!gxl) ghost_xm<R>(m[0], kdx, xl);
+            if (!gxr) {
+                if (two) ghost_xp<R>(m[1], kdx, xr);
+                else ghost_xp<R>(m[0], kdx, xr);
+            }
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                if (!gyp) ghost_yp<R>(m[q], kdy, yp[q]);
+                if (!gym) ghost_ym<R>(m[q], kdy, ym[q]);
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const R* mc = m[q];
+            R xp[3], xm[3], hx[3] = {(R)0, (R)0, (R)0}, hd[3] = {(R)0, (R)0, (R)0};
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                xm[c] = q == 0 ? xl[c] : m[0][c];
+                xp[c] = q == 1 || !two ? xr[c] : m[1][c];
+            }
+            if (ph.terms & MAGX_EXCH) {
+#pragma unroll
+                for (int c = 0; c < 3; ++c) {
+                    const R m2 = (R)2 * mc[c];
+                    hx[c] = ph.cex * ((xp[c] - m2 + xm[c]) * ph.idx2 + (yp[q][c] - m2 + ym[q][c]) * ph.idy2 +
+                                      (zp[q][c] - m2 + zm[q][c]) * ph.idz2);
+                }
+            }
+            if (ph.terms & MAGX_DMI) {
+                hd[0] = ph.cdmi * (xp[2] - xm[2]) * ph.h2x;
+                hd[1] = ph.cdmi * (yp[q][2] - ym[q][2]) * ph.h2y;
+                hd[2] = -ph.cdmi * ((xp[0] - xm[0]) * ph.h2x + (yp[q][1] - ym[q][1]) * ph.h2y);
+            }
+#pragma unroll
+            for (int c = 0; c < 3; ++c) h[q][c] = hx[c] + hd[c];
+        }
+    }
+    if (ph.terms & MAGX_ANIS) {
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const R pr = m[q][0] * ph.eK[0] + m[q][1] * ph.eK[1] + m[q][2] * ph.eK[2];
+#pragma unroll
+            for (int c = 0; c < 3; ++c) h[q][c] += ph.cani * pr * ph.eK[c];
+        }
+    }
+}
+
 // Non-finite detection (calls made with check_finite): true if any of the
 // n values is NaN or infinite; note_nonfinite sets the flag word with one
 // atomic from the first lane of every wave that met such a value (called by
@@ -447,10 +566,7 @@ constexpr int kXIt = 6;
 // Row of X1/Y1 holding component c of pencil p (32-bit element offset: the
 // spectral arrays of a whole batch stay below 2^31 elements).
 __device__ __forceinline__ unsigned x_row(const PG& g, int mb, int c, int pen) {
-    int y, z;
-    z = fdiv(pen, g.div_ny);
-    y = pen - z * g.ny;
-    return (((unsigned)(mb * 3 + c) * (unsigned)g.nz + (unsigned)z) * (unsigned)g.ny + (unsigned)y) * (unsigned)g.Sx;
+    return ((unsigned)(mb * 3 + c) * (unsigned)g.npen_total + (unsigned)pen) * (unsigned)g.Sx;
 }
 
 template <int V> struct IntC { static constexpr int value = V; };

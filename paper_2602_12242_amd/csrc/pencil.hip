@@ -82,12 +82,19 @@ __global__ void __launch_bounds__(kNT) xfwd_kernel(const R* __restrict__ f, cx<R
 // RED: the block sums (energy, or the sum of the input field) are wanted; the
 // plain field evaluation is a kernel of its own without their accumulators,
 // which keeps it within the registers of five waves per SIMD.
-template <typename R, bool BIG, int LN, bool RED>
+// V: 0 the general kernel, 1 without a magnetisation profile and the non-finite
+// check (energies, whose densities the plain local field does not split, are general).
+template <typename R, bool BIG, int LN, bool RED, int V>
 __device__ __forceinline__ void field_body(const cx<R>* __restrict__ Y1, const R* __restrict__ f,
                                            R* __restrict__ H, PG g, Phys<R> ph, int has_demag,
                                            int with_bias, int energy, int sum_input,
                                            double* __restrict__ partials) {
     if constexpr (!RED) energy = sum_input = 0;
+    if constexpr (V > 0) {
+        energy = 0;
+        ph.msp = nullptr;
+        ph.nf = nullptr;
+    }
     pg_fix<LN>(g);
     const bool stream = stream_of<BIG>(g);
     extern __shared__ unsigned char smem_raw[];
@@ -115,9 +122,12 @@ __device__ __forceinline__ void field_body(const cx<R>* __restrict__ Y1, const R
         const bool two = x0 + 1 < g.nx;
         int y, z;
         pen_coords<R>(g, pen0 + p, y, z);
-        R m[2][3], hl[2][3], ex[2], dm[2], an[2], out[2][3], sw[2];
-        local_field_pair<R>(f, g, x0, y, z, vec, two, ph, m, hl, ex, dm, an, energy != 0, sw);
-        const long long id = ((long long)z * g.ny + y) * g.nx + x0;
+        const unsigned id = (unsigned)(pen0 + p) * (unsigned)g.nx + (unsigned)x0;
+        R m[2][3], hl[2][3], ex[2], dm[2], an[2], out[2][3], sw[2] = {(R)1, (R)1};
+        if constexpr (V > 0)
+            local_field_plain<R>(f, g, x0, y, z, id * (unsigned)sizeof(R), vec, two, ph, m, hl);
+        else
+            local_field_pair<R>(f, g, x0, y, z, vec, two, ph, m, hl, ex, dm, an, energy != 0, sw);
 #pragma unroll
         for (int q = 0; q < 2; ++q) {
             R hd[3];
@@ -150,7 +160,7 @@ __device__ __forceinline__ void field_body(const cx<R>* __restrict__ Y1, const R
         }
         if (!energy) {
             if (ph.nf) note_nonfinite(ph.nf, any_nonfinite<R, 3>(out[0]) || (two && any_nonfinite<R, 3>(out[1])));
-            store_pair(H, g.N, id, vec, two, out[0], out[1], stream);
+            store_pair32(H, g.N, id * (unsigned)sizeof(R), vec, two, out[0], out[1], stream);
         }
     }
     if (energy && ph.nf) note_nonfinite(ph.nf, !isfinite(acc[0] + acc[1] + acc[2] + acc[3] + acc[4]));
@@ -167,23 +177,27 @@ __device__ __forceinline__ void field_body(const cx<R>* __restrict__ Y1, const R
     }
 }
 
-template <typename R, bool BIG, int LN>
+template <typename R, bool BIG, int LN, int V>
 __global__ void __launch_bounds__(kNT) field_kernel(const cx<R>* __restrict__ Y1, const R* __restrict__ f,
                                                     R* __restrict__ H, PG g, Phys<R> ph, int has_demag,
                                                     int with_bias, int energy, int sum_input,
                                                     double* __restrict__ partials) {
-    field_body<R, BIG, LN, false>(Y1, f, H, g, ph, has_demag, with_bias, energy, sum_input, partials);
+    field_body<R, BIG, LN, false, V>(Y1, f, H, g, ph, has_demag, with_bias, energy, sum_input, partials);
 }
 
-template <typename R, bool BIG, int LN>
+template <typename R, bool BIG, int LN, int V>
 __global__ void __launch_bounds__(kNT) field_reduce_kernel(const cx<R>* __restrict__ Y1, const R* __restrict__ f,
                                                            R* __restrict__ H, PG g, Phys<R> ph, int has_demag,
                                                            int with_bias, int energy, int sum_input,
                                                            double* __restrict__ partials) {
-    field_body<R, BIG, LN, true>(Y1, f, H, g, ph, has_demag, with_bias, energy, sum_input, partials);
+    field_body<R, BIG, LN, true, V>(Y1, f, H, g, ph, has_demag, with_bias, energy, sum_input, partials);
 }
 
-template <typename R, bool BIG, int LN>
+// V: 0 the general kernel (magnetisation profile, non-finite check), 1 without
+// either and without a tape, 2 the same with a tape.  The plain kernels carry
+// fewer uniform values (the general one spills about 60 scalar registers to
+// vector lanes, a lane read each time one is used) and no ghost selects.
+template <typename R, bool BIG, int LN, int V>
 __global__ void __launch_bounds__(kNT) stage_kernel(const cx<R>* Y1, cx<R>* X1, PG g,
                                                     Phys<R> ph, StageArgs<R> a, int has_demag) {
     pg_fix<LN>(g);
@@ -201,19 +215,27 @@ __global__ void __launch_bounds__(kNT) stage_kernel(const cx<R>* Y1, cx<R>* X1, 
     a.mn += mo;
     a.acc += mo;
     a.yout += mo;
-    if (a.yout2) a.yout2 += mo;
-    if (a.tapeH) a.tapeH += mo;
-    if (a.tapeYin) a.tapeYin += mo;
-    if (a.tapeNx) a.tapeNx += mo1;
+    if constexpr (V == 1) {
+        a.yout2 = a.tapeH = a.tapeYin = a.tapeNx = nullptr;
+    } else {
+        if (a.yout2) a.yout2 += mo;
+        if (a.tapeH) a.tapeH += mo;
+        if (a.tapeYin) a.tapeYin += mo;
+        if (a.tapeNx) a.tapeNx += mo1;
+    }
+    if constexpr (V > 0) {
+        ph.msp = nullptr;
+        ph.nf = nullptr;
+    }
     R hbv[3];
 #pragma unroll
     for (int c = 0; c < 3; ++c) hbv[c] = ph.hbm ? ph.hbm[mb * 3 + c] : ph.hb[c];
     const bool vec = (g.nx & 1) == 0;
     if (has_demag) c2r_lines<R, BIG, LN>(buf, Y1, g, mb, pen0, npen);
     // classical RK4 tableau
-    const R bw[4] = {(R)(1.0 / 6.0), (R)(1.0 / 3.0), (R)(1.0 / 3.0), (R)(1.0 / 6.0)};
-    const R cw[4] = {(R)0, (R)0.5, (R)0.5, (R)1};
     const int s = a.stage;
+    const R bws = s == 2 || s == 3 ? (R)(1.0 / 3.0) : (R)(1.0 / 6.0);
+    const R cdt = (s == 3 ? (R)1 : (R)0.5) * a.dt;
     // stage 0 is a forward Euler step: m_{n+1} = y + dt k, renormalised like a new state
     const bool norm = (s >= 1 && s < 4) ? (ph.renorm == 2) : (ph.renorm >= 1);
     // the next stage input goes straight into this thread's own LDS line
@@ -237,15 +259,21 @@ __global__ void __launch_bounds__(kNT) stage_kernel(const cx<R>* Y1, cx<R>* X1, 
         const bool two = x0 + 1 < g.nx;
         int y, z;
         pen_coords<R>(g, pen0 + p, y, z);
-        const long long id = ((long long)z * g.ny + y) * g.nx + x0;
+        const unsigned id = (unsigned)(pen0 + p) * (unsigned)g.nx + (unsigned)x0;
+        const unsigned off = id * (unsigned)sizeof(R);
         // RK4 registers first, so their loads are in flight with the stencil's
         R k[2][3], mn[2][3], acc[2][3], xn[2][3], nrm[2];
         if (s > 1) {
-            load_pair(a.mn, g.N, id, vec, two, mn[0], mn[1], stream);
-            load_pair(a.acc, g.N, id, vec, two, acc[0], acc[1], stream);
+            load_pair32(a.mn, g.N, off, vec, two, mn[0], mn[1], stream);
+            load_pair32(a.acc, g.N, off, vec, two, acc[0], acc[1], stream);
         }
-        R ys[2][3], H[2][3], ex[2], dm[2], an[2], sw[2];
-        local_field_pair<R>(a.yin, g, x0, y, z, vec, two, ph, ys, H, ex, dm, an, false, sw);
+        R ys[2][3], H[2][3], sw[2] = {(R)1, (R)1};
+        if constexpr (V > 0) {
+            local_field_plain<R>(a.yin, g, x0, y, z, off, vec, two, ph, ys, H);
+        } else {
+            R ex[2], dm[2], an[2];
+            local_field_pair<R>(a.yin, g, x0, y, z, vec, two, ph, ys, H, ex, dm, an, false, sw);
+        }
 #pragma unroll
         for (int q = 0; q < 2; ++q) {
             // with a profile: no field (so no motion) outside the magnet
@@ -256,8 +284,8 @@ __global__ void __launch_bounds__(kNT) stage_kernel(const cx<R>* Y1, cx<R>* X1, 
                 if (ph.terms & MAGX_ZEEMAN) H[q][c] += inside * hbv[c];
             }
         }
-        if (a.tapeH) store_pair(a.tapeH, g.N, id, vec, two, H[0], H[1], stream);
-        if (a.tapeYin) store_pair(a.tapeYin, g.N, id, vec, two, ys[0], ys[1], stream);
+        if (a.tapeH) store_pair32(a.tapeH, g.N, off, vec, two, H[0], H[1], stream);
+        if (a.tapeYin) store_pair32(a.tapeYin, g.N, off, vec, two, ys[0], ys[1], stream);
 #pragma unroll
         for (int q = 0; q < 2; ++q) llg_rhs<R>(ys[q], H[q], ph.a, ph.alpha, k[q]);
         if (s <= 1) {
@@ -273,10 +301,10 @@ __global__ void __launch_bounds__(kNT) stage_kernel(const cx<R>* Y1, cx<R>* X1, 
                 if (s == 0) {
                     xn[q][c] = mn[q][c] + a.dt * k[q][c];
                 } else if (s < 4) {
-                    acc[q][c] = (s == 1 ? (R)0 : acc[q][c]) + bw[s - 1] * k[q][c];
-                    xn[q][c] = mn[q][c] + cw[s] * a.dt * k[q][c];
+                    acc[q][c] = (s == 1 ? (R)0 : acc[q][c]) + bws * k[q][c];
+                    xn[q][c] = mn[q][c] + cdt * k[q][c];
                 } else {
-                    xn[q][c] = mn[q][c] + a.dt * (acc[q][c] + bw[3] * k[q][c]);
+                    xn[q][c] = mn[q][c] + a.dt * (acc[q][c] + bws * k[q][c]);
                 }
             }
             nrm[q] = (R)1;
@@ -292,13 +320,13 @@ __global__ void __launch_bounds__(kNT) stage_kernel(const cx<R>* Y1, cx<R>* X1, 
         if (ph.nf)
             note_nonfinite(ph.nf, any_nonfinite<R, 3>(xn[0]) || any_nonfinite<R, 3>(H[0]) ||
                                       (two && (any_nonfinite<R, 3>(xn[1]) || any_nonfinite<R, 3>(H[1]))));
-        if (s >= 1 && s < 4) store_pair(a.acc, g.N, id, vec, two, acc[0], acc[1], stream);
+        if (s >= 1 && s < 4) store_pair32(a.acc, g.N, off, vec, two, acc[0], acc[1], stream);
         if (a.tapeNx) {
             if (vec) *reinterpret_cast<cx<R>*>(a.tapeNx + id) = mk<R>(nrm[0], nrm[1]);
             else { a.tapeNx[id] = nrm[0]; if (two) a.tapeNx[id + 1] = nrm[1]; }
         }
-        store_pair(a.yout, g.N, id, vec, two, xn[0], xn[1], stream);
-        if (a.yout2) store_pair(a.yout2, g.N, id, vec, two, xn[0], xn[1], stream);
+        store_pair32(a.yout, g.N, off, vec, two, xn[0], xn[1], stream);
+        if (a.yout2) store_pair32(a.yout2, g.N, off, vec, two, xn[0], xn[1], stream);
         if (fwd) {
             // demag source of the next stage: Ms(r) m = Ms s m
 #pragma unroll
@@ -406,7 +434,8 @@ __global__ void __launch_bounds__(kNT) bstart_kernel(cx<R>* __restrict__ X1, PG 
     r2c_lines<R, BIG, LN>(buf, X1, g, mb, pen0, npen);
 }
 
-template <typename R, bool BIG, int LN>
+// V: 0 with the non-finite check, 1 without (the reverse mode has no profile).
+template <typename R, bool BIG, int LN, int V>
 __global__ void __launch_bounds__(kNT) bstage_kernel(const cx<R>* Y1, cx<R>* X1, PG g,
                                                      Phys<R> ph, BackArgs<R> a, int has_demag,
                                                      double* __restrict__ partials) {
@@ -433,9 +462,11 @@ __global__ void __launch_bounds__(kNT) bstage_kernel(const cx<R>* Y1, cx<R>* X1,
     if (a.nxs) a.nxs += mo1;
     const bool vec = (g.nx & 1) == 0;
     if (has_demag) c2r_lines<R, BIG, LN>(buf, Y1, g, mb, pen0, npen);
-    const R bw[4] = {(R)(1.0 / 6.0), (R)(1.0 / 3.0), (R)(1.0 / 3.0), (R)(1.0 / 6.0)};
-    const R cw[4] = {(R)0, (R)0.5, (R)0.5, (R)1};
     const int s = a.stage;
+    // weights of stage s - 1: b_{s-1} dt and c_s dt
+    const R bdt = (s == 2 ? (R)(1.0 / 6.0) : (R)(1.0 / 3.0)) * a.dt;
+    const R cdt = (s == 4 ? (R)1 : (R)0.5) * a.dt;
+    if constexpr (V > 0) ph.nf = nullptr;
     const bool norm = ph.renorm == 2;
     double hs[3] = {0, 0, 0};
     // mu_{s-1} goes straight into this thread's own LDS line entries (read
@@ -459,10 +490,10 @@ __global__ void __launch_bounds__(kNT) bstage_kernel(const cx<R>* Y1, cx<R>* X1,
         const bool two = x0 + 1 < g.nx;
         int y, z;
         pen_coords<R>(g, pen0 + p, y, z);
-        const long long id = ((long long)z * g.ny + y) * g.nx + x0;
-        R mu[2][3], Kmu[2][3], ex[2], dm[2], an[2];
-        R sw[2];
-        local_field_pair<R>(a.mu, g, x0, y, z, vec, two, ph, mu, Kmu, ex, dm, an, false, sw);
+        const unsigned id = (unsigned)(pen0 + p) * (unsigned)g.nx + (unsigned)x0;
+        const unsigned off = id * (unsigned)sizeof(R);
+        R mu[2][3], Kmu[2][3];
+        local_field_plain<R>(a.mu, g, x0, y, z, off, vec, two, ph, mu, Kmu);
         if (has_demag) {
 #pragma unroll
             for (int q = 0; q < 2; ++q)
@@ -470,10 +501,10 @@ __global__ void __launch_bounds__(kNT) bstage_kernel(const cx<R>* Y1, cx<R>* X1,
                 for (int c = 0; c < 3; ++c) Kmu[q][c] += demag_at<R>(buf, 3 * p + c, g.Lh, n, q);
         }
         R ys[2][3], Hs[2][3], kap[2][3], lam[2][3], yb[2][3];
-        load_pair(a.ys, g.N, id, vec, two, ys[0], ys[1]);
-        load_pair(a.Hs, g.N, id, vec, two, Hs[0], Hs[1]);
-        load_pair(a.kap, g.N, id, vec, two, kap[0], kap[1]);
-        load_pair(a.gm, g.N, id, vec, two, lam[0], lam[1]);
+        load_pair32(a.ys, g.N, off, vec, two, ys[0], ys[1]);
+        load_pair32(a.Hs, g.N, off, vec, two, Hs[0], Hs[1]);
+        load_pair32(a.kap, g.N, off, vec, two, kap[0], kap[1]);
+        load_pair32(a.gm, g.N, off, vec, two, lam[0], lam[1]);
         // ybar = a [H x kappa + alpha (H (y.kappa) + kappa (y.H) - 2 y (H.kappa))] + K mu
 #pragma unroll
         for (int q = 0; q < 2; ++q) {
@@ -505,21 +536,21 @@ __global__ void __launch_bounds__(kNT) bstage_kernel(const cx<R>* Y1, cx<R>* X1,
 #pragma unroll
                     for (int c = 0; c < 3; ++c) xi[q][c] = yb[q][c];
             }
-            load_pair(a.xi5, g.N, id, vec, two, x5[0], x5[1]);
-            load_pair(a.yprev, g.N, id, vec, two, yp[0], yp[1]);
+            load_pair32(a.xi5, g.N, off, vec, two, x5[0], x5[1]);
+            load_pair32(a.yprev, g.N, off, vec, two, yp[0], yp[1]);
 #pragma unroll
             for (int q = 0; q < 2; ++q) {
 #pragma unroll
                 for (int c = 0; c < 3; ++c) {
                     lam[q][c] += xi[q][c];
-                    kp[q][c] = bw[s - 2] * a.dt * x5[q][c] + cw[s - 1] * a.dt * xi[q][c];
+                    kp[q][c] = bdt * x5[q][c] + cdt * xi[q][c];
                 }
                 rhs_mu<R>(yp[q], kp[q], ph.a, ph.alpha, mup[q]);
             }
             if (ph.nf) note_nonfinite(ph.nf, any_nonfinite<R, 3>(lam[0]) || (two && any_nonfinite<R, 3>(lam[1])));
-            store_pair(a.gm, g.N, id, vec, two, lam[0], lam[1], stream);
-            store_pair(a.kap, g.N, id, vec, two, kp[0], kp[1], stream);
-            store_pair(a.muout, g.N, id, vec, two, mup[0], mup[1], stream);
+            store_pair32(a.gm, g.N, off, vec, two, lam[0], lam[1], stream);
+            store_pair32(a.kap, g.N, off, vec, two, kp[0], kp[1], stream);
+            store_pair32(a.muout, g.N, off, vec, two, mup[0], mup[1], stream);
 #pragma unroll
             for (int c = 0; c < 3; ++c) {
                 const R m1 = two ? mup[1][c] : (R)0;
@@ -532,7 +563,7 @@ __global__ void __launch_bounds__(kNT) bstage_kernel(const cx<R>* Y1, cx<R>* X1,
 #pragma unroll
                 for (int c = 0; c < 3; ++c) lam[q][c] += yb[q][c];
             if (ph.nf) note_nonfinite(ph.nf, any_nonfinite<R, 3>(lam[0]) || (two && any_nonfinite<R, 3>(lam[1])));
-            store_pair(a.gm, g.N, id, vec, two, lam[0], lam[1], stream);
+            store_pair32(a.gm, g.N, off, vec, two, lam[0], lam[1], stream);
         }
     }
     if (s > 1 && (ph.terms & MAGX_ZEEMAN)) {
@@ -616,27 +647,40 @@ __global__ void copy_kernel(const R* __restrict__ src, R* __restrict__ dst, long
 
 // Pencil kernel launch: the line lengths of pencil_line with compile-time
 // geometry, every other size with runtime geometry.
-#define MAGX_PENCIL_LAUNCH(KERNEL, ...)                                                                     \
-    do {                                                                                                    \
-        const dim3 grid_((unsigned)pl.pencil_blocks), block_(kNT);                                          \
-        const size_t lds_ = pencil_lds(pl);                                                                 \
-        switch (pencil_line(pl)) {                                                                          \
-            MAGX_ODD_LINES(KERNEL, lds_, __VA_ARGS__)                                                       \
-            case 128: hipLaunchKernelGGL((KERNEL<R, false, 128>), grid_, block_, lds_, s, __VA_ARGS__); break;   \
-            case 256: hipLaunchKernelGGL((KERNEL<R, false, 256>), grid_, block_, lds_, s, __VA_ARGS__); break;   \
-            case 512: hipLaunchKernelGGL((KERNEL<R, false, 512>), grid_, block_, lds_, s, __VA_ARGS__); break;   \
-            case 1024: hipLaunchKernelGGL((KERNEL<R, false, 1024>), grid_, block_, lds_, s, __VA_ARGS__); break; \
-            default:                                                                                        \
-                if (pencil_big(pl))                                                                         \
-                    hipLaunchKernelGGL((KERNEL<R, true, 0>), grid_, block_, lds_, s, __VA_ARGS__);          \
-                else                                                                                        \
-                    hipLaunchKernelGGL((KERNEL<R, false, 0>), grid_, block_, lds_, s, __VA_ARGS__);         \
-        }                                                                                                   \
+#define MAGX_UNWRAP(...) __VA_ARGS__
+#define MAGX_PENCIL_CASE(LN, KERNEL, VV, ...)                                                              \
+    case LN:                                                                                               \
+        hipLaunchKernelGGL((KERNEL<R, false, LN MAGX_UNWRAP VV>), grid_, block_, lds_, s, __VA_ARGS__);    \
+        break;
+// VV: further template arguments in parentheses, "()" or "(, value)"
+#define MAGX_PENCIL_LAUNCH(KERNEL, VV, ...)                                                                \
+    do {                                                                                                   \
+        const dim3 grid_((unsigned)pl.pencil_blocks), block_(kNT);                                         \
+        const size_t lds_ = pencil_lds(pl);                                                                \
+        switch (pencil_line(pl)) {                                                                         \
+            MAGX_PENCIL_CASE(80, KERNEL, VV, __VA_ARGS__)                                                  \
+            MAGX_PENCIL_CASE(96, KERNEL, VV, __VA_ARGS__)                                                  \
+            MAGX_PENCIL_CASE(128, KERNEL, VV, __VA_ARGS__)                                                 \
+            MAGX_PENCIL_CASE(160, KERNEL, VV, __VA_ARGS__)                                                 \
+            MAGX_PENCIL_CASE(192, KERNEL, VV, __VA_ARGS__)                                                 \
+            MAGX_PENCIL_CASE(256, KERNEL, VV, __VA_ARGS__)                                                 \
+            MAGX_PENCIL_CASE(320, KERNEL, VV, __VA_ARGS__)                                                 \
+            MAGX_PENCIL_CASE(384, KERNEL, VV, __VA_ARGS__)                                                 \
+            MAGX_PENCIL_CASE(512, KERNEL, VV, __VA_ARGS__)                                                 \
+            MAGX_PENCIL_CASE(640, KERNEL, VV, __VA_ARGS__)                                                 \
+            MAGX_PENCIL_CASE(768, KERNEL, VV, __VA_ARGS__)                                                 \
+            MAGX_PENCIL_CASE(1024, KERNEL, VV, __VA_ARGS__)                                                \
+            default:                                                                                       \
+                if (pencil_big(pl))                                                                        \
+                    hipLaunchKernelGGL((KERNEL<R, true, 0 MAGX_UNWRAP VV>), grid_, block_, lds_, s, __VA_ARGS__);  \
+                else                                                                                       \
+                    hipLaunchKernelGGL((KERNEL<R, false, 0 MAGX_UNWRAP VV>), grid_, block_, lds_, s, __VA_ARGS__); \
+        }                                                                                                  \
     } while (0)
 
 template <typename R>
 hipError_t launch_xfwd(const Plan& pl, const R* f, void* X1, const R* msp, hipStream_t s) {
-    MAGX_PENCIL_LAUNCH(xfwd_kernel, f, static_cast<cx<R>*>(X1), make_pg(pl), msp);
+    MAGX_PENCIL_LAUNCH(xfwd_kernel, (), f, static_cast<cx<R>*>(X1), make_pg(pl), msp);
     return hipGetLastError();
 }
 
@@ -644,10 +688,17 @@ template <typename R>
 hipError_t launch_field(const Plan& pl, const Phys<R>& ph, const void* Y1, const R* f, R* H, int with_bias,
                         int energy, int sum_input, double* partials, hipStream_t s) {
     const int has_demag = (ph.terms & MAGX_DEMAG) ? 1 : 0;
-    if (energy || sum_input)
-        MAGX_PENCIL_LAUNCH(field_reduce_kernel, static_cast<const cx<R>*>(Y1), f, H, make_pg(pl), ph, has_demag, with_bias, energy, sum_input, partials);
+    const PG g = make_pg(pl);
+    const cx<R>* y = static_cast<const cx<R>*>(Y1);
+    const bool plain = !ph.msp && !ph.nf;
+    if (energy || (sum_input && !plain))
+        MAGX_PENCIL_LAUNCH(field_reduce_kernel, (, 0), y, f, H, g, ph, has_demag, with_bias, energy, sum_input, partials);
+    else if (sum_input)
+        MAGX_PENCIL_LAUNCH(field_reduce_kernel, (, 1), y, f, H, g, ph, has_demag, with_bias, energy, sum_input, partials);
+    else if (plain)
+        MAGX_PENCIL_LAUNCH(field_kernel, (, 1), y, f, H, g, ph, has_demag, with_bias, energy, sum_input, partials);
     else
-        MAGX_PENCIL_LAUNCH(field_kernel, static_cast<const cx<R>*>(Y1), f, H, make_pg(pl), ph, has_demag, with_bias, energy, sum_input, partials);
+        MAGX_PENCIL_LAUNCH(field_kernel, (, 0), y, f, H, g, ph, has_demag, with_bias, energy, sum_input, partials);
     return hipGetLastError();
 }
 
@@ -655,7 +706,12 @@ template <typename R>
 hipError_t launch_stage(const Plan& pl, const Phys<R>& ph, const void* Y1, void* X1, const StageArgs<R>& a,
                         hipStream_t s) {
     const int has_demag = (ph.terms & MAGX_DEMAG) ? 1 : 0;
-    MAGX_PENCIL_LAUNCH(stage_kernel, static_cast<const cx<R>*>(Y1), static_cast<cx<R>*>(X1), make_pg(pl), ph, a, has_demag);
+    const PG g = make_pg(pl);
+    const cx<R>* y = static_cast<const cx<R>*>(Y1);
+    cx<R>* x = static_cast<cx<R>*>(X1);
+    if (ph.msp || ph.nf) MAGX_PENCIL_LAUNCH(stage_kernel, (, 0), y, x, g, ph, a, has_demag);
+    else if (a.tapeH) MAGX_PENCIL_LAUNCH(stage_kernel, (, 2), y, x, g, ph, a, has_demag);
+    else MAGX_PENCIL_LAUNCH(stage_kernel, (, 1), y, x, g, ph, a, has_demag);
     return hipGetLastError();
 }
 
@@ -663,7 +719,7 @@ template <typename R>
 hipError_t launch_bstart(const Plan& pl, const Phys<R>& ph, void* X1, const StartArgs<R>& a, double* partials,
                          hipStream_t s) {
     const int has_demag = (ph.terms & MAGX_DEMAG) ? 1 : 0;
-    MAGX_PENCIL_LAUNCH(bstart_kernel, static_cast<cx<R>*>(X1), make_pg(pl), ph, a, has_demag, partials);
+    MAGX_PENCIL_LAUNCH(bstart_kernel, (), static_cast<cx<R>*>(X1), make_pg(pl), ph, a, has_demag, partials);
     return hipGetLastError();
 }
 
@@ -671,7 +727,11 @@ template <typename R>
 hipError_t launch_bstage(const Plan& pl, const Phys<R>& ph, const void* Y1, void* X1, const BackArgs<R>& a,
                          double* partials, hipStream_t s) {
     const int has_demag = (ph.terms & MAGX_DEMAG) ? 1 : 0;
-    MAGX_PENCIL_LAUNCH(bstage_kernel, static_cast<const cx<R>*>(Y1), static_cast<cx<R>*>(X1), make_pg(pl), ph, a, has_demag, partials);
+    const PG g = make_pg(pl);
+    const cx<R>* y = static_cast<const cx<R>*>(Y1);
+    cx<R>* x = static_cast<cx<R>*>(X1);
+    if (ph.nf) MAGX_PENCIL_LAUNCH(bstage_kernel, (, 0), y, x, g, ph, a, has_demag, partials);
+    else MAGX_PENCIL_LAUNCH(bstage_kernel, (, 1), y, x, g, ph, a, has_demag, partials);
     return hipGetLastError();
 }
 
