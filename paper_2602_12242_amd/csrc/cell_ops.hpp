@@ -425,80 +425,106 @@ __device__ __forceinline__ void store_pair32(R* __restrict__ f, long long N, uns
     }
 }
 
+// The values of the pair and of its neighbours, their loads and the exchange and
+// DMI field computed from them (h; both only with an exchange or DMI term).
+template <typename R> struct Stencil {
+    R m[2][3], xl[3], xr[3], yp[2][3], ym[2][3], zp[2][3], zm[2][3];
+};
+
 template <typename R>
-__device__ __forceinline__ void local_field_plain(const R* __restrict__ f, const PG& g, int x0, int y, int z,
-                                                  unsigned off, bool vec, bool two, const Phys<R>& ph, R m[2][3],
-                                                  R h[2][3]) {
+__device__ __forceinline__ void neighbours_load(Stencil<R>& t, const R* __restrict__ f, const PG& g, int x0, int y,
+                                                int z, unsigned off, bool vec, bool two) {
     constexpr unsigned es = (unsigned)sizeof(R);
     const long long N = g.N;
-    load_pair32(f, N, off, vec, two, m[0], m[1]);
+    const unsigned rowb = (unsigned)g.nx * es, planeb = (unsigned)g.ny * rowb;
+    const unsigned ol = x0 > 0 ? off - es : off;
+    const unsigned orr = off + ((two ? 1u : 0u) + (x0 + (two ? 2 : 1) < g.nx ? 1u : 0u)) * es;
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        const char* p = reinterpret_cast<const char*>(f + c * N);
+        t.xl[c] = *reinterpret_cast<const R*>(p + ol);
+        t.xr[c] = *reinterpret_cast<const R*>(p + orr);
+    }
+    load_pair32(f, N, y + 1 < g.ny ? off + rowb : off, vec, two, t.yp[0], t.yp[1]);
+    load_pair32(f, N, y > 0 ? off - rowb : off, vec, two, t.ym[0], t.ym[1]);
+    load_pair32(f, N, z + 1 < g.nz ? off + planeb : off, vec, two, t.zp[0], t.zp[1]);
+    load_pair32(f, N, z > 0 ? off - planeb : off, vec, two, t.zm[0], t.zm[1]);
+}
+
+template <typename R>
+__device__ __forceinline__ void neighbours_field(Stencil<R>& t, const PG& g, int x0, int y, bool two,
+                                                 const Phys<R>& ph, R h[2][3]) {
+    if (ph.terms & MAGX_DMI) {
+        const R kdx = ph.kap * ph.dx, kdy = ph.kap * ph.dy;
+        if (x0 == 0) ghost_xm<R>(t.m[0], kdx, t.xl);
+        if (x0 + (two ? 2 : 1) >= g.nx) {
+            if (two) ghost_xp<R>(t.m[1], kdx, t.xr);
+            else ghost_xp<R>(t.m[0], kdx, t.xr);
+        }
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            if (y + 1 >= g.ny) ghost_yp<R>(t.m[q], kdy, t.yp[q]);
+            if (y == 0) ghost_ym<R>(t.m[q], kdy, t.ym[q]);
+        }
+    }
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        const R* mc = t.m[q];
+        R xp[3], xm[3], hx[3] = {(R)0, (R)0, (R)0}, hd[3] = {(R)0, (R)0, (R)0};
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            xm[c] = q == 0 ? t.xl[c] : t.m[0][c];
+            xp[c] = q == 1 || !two ? t.xr[c] : t.m[1][c];
+        }
+        if (ph.terms & MAGX_EXCH) {
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                const R m2 = (R)2 * mc[c];
+                hx[c] = ph.cex * ((xp[c] - m2 + xm[c]) * ph.idx2 + (t.yp[q][c] - m2 + t.ym[q][c]) * ph.idy2 +
+                                  (t.zp[q][c] - m2 + t.zm[q][c]) * ph.idz2);
+            }
+        }
+        if (ph.terms & MAGX_DMI) {
+            hd[0] = ph.cdmi * (xp[2] - xm[2]) * ph.h2x;
+            hd[1] = ph.cdmi * (t.yp[q][2] - t.ym[q][2]) * ph.h2y;
+            hd[2] = -ph.cdmi * ((xp[0] - xm[0]) * ph.h2x + (t.yp[q][1] - t.ym[q][1]) * ph.h2y);
+        }
+#pragma unroll
+        for (int c = 0; c < 3; ++c) h[q][c] = hx[c] + hd[c];
+    }
+}
+
+// Exchange, DMI and anisotropy field of the pair.  LOADED: t holds the pair and
+// its neighbours already (loaded ahead, with stencil_load); otherwise they are
+// loaded here, next to their use, which keeps fewer registers live.
+template <typename R, bool LOADED = false>
+__device__ __forceinline__ void local_field_plain(Stencil<R>& t, const R* __restrict__ f, const PG& g, int x0, int y,
+                                                  int z, unsigned off, bool vec, bool two, const Phys<R>& ph,
+                                                  R h[2][3]) {
+    if constexpr (!LOADED) load_pair32(f, g.N, off, vec, two, t.m[0], t.m[1]);
 #pragma unroll
     for (int q = 0; q < 2; ++q)
 #pragma unroll
         for (int c = 0; c < 3; ++c) h[q][c] = (R)0;
     if (ph.terms & (MAGX_EXCH | MAGX_DMI)) {
-        const unsigned rowb = (unsigned)g.nx * es, planeb = (unsigned)g.ny * rowb;
-        const bool gxl = x0 > 0, gxr = x0 + (two ? 2 : 1) < g.nx;
-        const bool gyp = y + 1 < g.ny, gym = y > 0, gzp = z + 1 < g.nz, gzm = z > 0;
-        const unsigned ol = gxl ? off - es : off, orr = off + ((two ? 1u : 0u) + (gxr ? 1u : 0u)) * es;
-        R xl[3], xr[3], yp[2][3], ym[2][3], zp[2][3], zm[2][3];
-#pragma unroll
-        for (int c = 0; c < 3; ++c) {
-            const char* p = reinterpret_cast<const char*>(f + c * N);
-            xl[c] = *reinterpret_cast<const R*>(p + ol);
-            xr[c] = *reinterpret_cast<const R*>(p + orr);
-        }
-        load_pair32(f, N, gyp ? off + rowb : off, vec, two, yp[0], yp[1]);
-        load_pair32(f, N, gym ? off - rowb : off, vec, two, ym[0], ym[1]);
-        load_pair32(f, N, gzp ? off + planeb : off, vec, two, zp[0], zp[1]);
-        load_pair32(f, N, gzm ? off - planeb : off, vec, two, zm[0], zm[1]);
-        if (ph.terms & MAGX_DMI) {
-            const R kdx = ph.kap * ph.dx, kdy = ph.kap * ph.dy;
-            if (!gxl) ghost_xm<R>(m[0], kdx, xl);
-            if (!gxr) {
-                if (two) ghost_xp<R>(m[1], kdx, xr);
-                else ghost_xp<R>(m[0], kdx, xr);
-            }
-#pragma unroll
-            for (int q = 0; q < 2; ++q) {
-                if (!gyp) ghost_yp<R>(m[q], kdy, yp[q]);
-                if (!gym) ghost_ym<R>(m[q], kdy, ym[q]);
-            }
-        }
-#pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            const R* mc = m[q];
-            R xp[3], xm[3], hx[3] = {(R)0, (R)0, (R)0}, hd[3] = {(R)0, (R)0, (R)0};
-#pragma unroll
-            for (int c = 0; c < 3; ++c) {
-                xm[c] = q == 0 ? xl[c] : m[0][c];
-                xp[c] = q == 1 || !two ? xr[c] : m[1][c];
-            }
-            if (ph.terms & MAGX_EXCH) {
-#pragma unroll
-                for (int c = 0; c < 3; ++c) {
-                    const R m2 = (R)2 * mc[c];
-                    hx[c] = ph.cex * ((xp[c] - m2 + xm[c]) * ph.idx2 + (yp[q][c] - m2 + ym[q][c]) * ph.idy2 +
-                                      (zp[q][c] - m2 + zm[q][c]) * ph.idz2);
-                }
-            }
-            if (ph.terms & MAGX_DMI) {
-                hd[0] = ph.cdmi * (xp[2] - xm[2]) * ph.h2x;
-                hd[1] = ph.cdmi * (yp[q][2] - ym[q][2]) * ph.h2y;
-                hd[2] = -ph.cdmi * ((xp[0] - xm[0]) * ph.h2x + (yp[q][1] - ym[q][1]) * ph.h2y);
-            }
-#pragma unroll
-            for (int c = 0; c < 3; ++c) h[q][c] = hx[c] + hd[c];
-        }
+        if constexpr (!LOADED) neighbours_load<R>(t, f, g, x0, y, z, off, vec, two);
+        neighbours_field<R>(t, g, x0, y, two, ph, h);
     }
     if (ph.terms & MAGX_ANIS) {
 #pragma unroll
         for (int q = 0; q < 2; ++q) {
-            const R pr = m[q][0] * ph.eK[0] + m[q][1] * ph.eK[1] + m[q][2] * ph.eK[2];
+            const R pr = t.m[q][0] * ph.eK[0] + t.m[q][1] * ph.eK[1] + t.m[q][2] * ph.eK[2];
 #pragma unroll
             for (int c = 0; c < 3; ++c) h[q][c] += ph.cani * pr * ph.eK[c];
         }
     }
+}
+
+template <typename R>
+__device__ __forceinline__ void stencil_load(Stencil<R>& t, const R* __restrict__ f, const PG& g, int x0, int y, int z,
+                                             unsigned off, bool vec, bool two, unsigned terms) {
+    load_pair32(f, g.N, off, vec, two, t.m[0], t.m[1]);
+    if (terms & (MAGX_EXCH | MAGX_DMI)) neighbours_load<R>(t, f, g, x0, y, z, off, vec, two);
 }
 
 // Non-finite detection (calls made with check_finite): true if any of the

@@ -19,6 +19,8 @@
 // Boundary condition (Eq. (10) with the outward normal n): one ghost per face,
 // m_ghost = m_b + h (-D/2A) (e_z x n) x m_b, shared by the exchange and DMI
 // stencils; on z faces and without DMI it is plain zero-flux Neumann.
+#include <algorithm>
+
 #include "cell_ops.hpp"
 
 namespace magx {
@@ -84,7 +86,8 @@ __global__ void __launch_bounds__(kNT) xfwd_kernel(const R* __restrict__ f, cx<R
 // which keeps it within the registers of five waves per SIMD.
 // V: 0 the general kernel, 1 without a magnetisation profile and the non-finite
 // check (energies, whose densities the plain local field does not split, are general).
-template <typename R, bool BIG, int LN, bool RED, int V>
+// PRE: the stencil of a thread's single cell pair is loaded before the inverse x pass.
+template <typename R, bool BIG, int LN, bool RED, int V, bool PRE>
 __device__ __forceinline__ void field_body(const cx<R>* __restrict__ Y1, const R* __restrict__ f,
                                            R* __restrict__ H, PG g, Phys<R> ph, int has_demag,
                                            int with_bias, int energy, int sum_input,
@@ -112,6 +115,16 @@ __device__ __forceinline__ void field_body(const cx<R>* __restrict__ Y1, const R
 #pragma unroll
     for (int c = 0; c < 3; ++c) hbv[c] = ph.hbm ? ph.hbm[mb * 3 + c] : ph.hb[c];
     const bool vec = (g.nx & 1) == 0;
+    Stencil<R> t;
+    if constexpr (PRE) {
+        int p, n, y, z;
+        slot_of<LN>(g, threadIdx.x, p, n);
+        if ((int)threadIdx.x < slots_of<LN>(g, npen) && 2 * n < g.nx) {
+            pen_coords<R>(g, pen0 + p, y, z);
+            const unsigned id = (unsigned)(pen0 + p) * (unsigned)g.nx + (unsigned)(2 * n);
+            stencil_load<R>(t, f, g, 2 * n, y, z, id * (unsigned)sizeof(R), vec, 2 * n + 1 < g.nx, ph.terms);
+        }
+    }
     if (has_demag) c2r_lines<R, BIG, LN>(buf, Y1, g, mb, pen0, npen);
     double acc[6] = {0, 0, 0, 0, 0, 0};
     for (int e = threadIdx.x; e < slots_of<LN>(g, npen); e += kNT) {
@@ -124,10 +137,15 @@ __device__ __forceinline__ void field_body(const cx<R>* __restrict__ Y1, const R
         pen_coords<R>(g, pen0 + p, y, z);
         const unsigned id = (unsigned)(pen0 + p) * (unsigned)g.nx + (unsigned)x0;
         R m[2][3], hl[2][3], ex[2], dm[2], an[2], out[2][3], sw[2] = {(R)1, (R)1};
-        if constexpr (V > 0)
-            local_field_plain<R>(f, g, x0, y, z, id * (unsigned)sizeof(R), vec, two, ph, m, hl);
-        else
+        if constexpr (V > 0) {
+            local_field_plain<R, PRE>(t, f, g, x0, y, z, id * (unsigned)sizeof(R), vec, two, ph, hl);
+#pragma unroll
+            for (int q = 0; q < 2; ++q)
+#pragma unroll
+                for (int c = 0; c < 3; ++c) m[q][c] = t.m[q][c];
+        } else {
             local_field_pair<R>(f, g, x0, y, z, vec, two, ph, m, hl, ex, dm, an, energy != 0, sw);
+        }
 #pragma unroll
         for (int q = 0; q < 2; ++q) {
             R hd[3];
@@ -177,12 +195,12 @@ __device__ __forceinline__ void field_body(const cx<R>* __restrict__ Y1, const R
     }
 }
 
-template <typename R, bool BIG, int LN, int V>
+template <typename R, bool BIG, int LN, int V, bool PRE>
 __global__ void __launch_bounds__(kNT) field_kernel(const cx<R>* __restrict__ Y1, const R* __restrict__ f,
                                                     R* __restrict__ H, PG g, Phys<R> ph, int has_demag,
                                                     int with_bias, int energy, int sum_input,
                                                     double* __restrict__ partials) {
-    field_body<R, BIG, LN, false, V>(Y1, f, H, g, ph, has_demag, with_bias, energy, sum_input, partials);
+    field_body<R, BIG, LN, false, V, PRE>(Y1, f, H, g, ph, has_demag, with_bias, energy, sum_input, partials);
 }
 
 template <typename R, bool BIG, int LN, int V>
@@ -190,14 +208,16 @@ __global__ void __launch_bounds__(kNT) field_reduce_kernel(const cx<R>* __restri
                                                            R* __restrict__ H, PG g, Phys<R> ph, int has_demag,
                                                            int with_bias, int energy, int sum_input,
                                                            double* __restrict__ partials) {
-    field_body<R, BIG, LN, true, V>(Y1, f, H, g, ph, has_demag, with_bias, energy, sum_input, partials);
+    field_body<R, BIG, LN, true, V, false>(Y1, f, H, g, ph, has_demag, with_bias, energy, sum_input, partials);
 }
 
 // V: 0 the general kernel (magnetisation profile, non-finite check), 1 without
 // either and without a tape, 2 the same with a tape.  The plain kernels carry
 // fewer uniform values (the general one spills about 60 scalar registers to
 // vector lanes, a lane read each time one is used) and no ghost selects.
-template <typename R, bool BIG, int LN, int V>
+// PRE (a thread's single cell pair on grids of few blocks, see ahead()): the
+// stencil and the RK4 registers are loaded before the inverse x pass.
+template <typename R, bool BIG, int LN, int V, bool PRE>
 __global__ void __launch_bounds__(kNT) stage_kernel(const cx<R>* Y1, cx<R>* X1, PG g,
                                                     Phys<R> ph, StageArgs<R> a, int has_demag) {
     pg_fix<LN>(g);
@@ -231,9 +251,25 @@ __global__ void __launch_bounds__(kNT) stage_kernel(const cx<R>* Y1, cx<R>* X1, 
 #pragma unroll
     for (int c = 0; c < 3; ++c) hbv[c] = ph.hbm ? ph.hbm[mb * 3 + c] : ph.hb[c];
     const bool vec = (g.nx & 1) == 0;
+    const int s = a.stage;
+    Stencil<R> t;
+    R mn[2][3], acc[2][3];
+    if constexpr (PRE) {
+        int p, n, y, z;
+        slot_of<LN>(g, threadIdx.x, p, n);
+        if ((int)threadIdx.x < slots_of<LN>(g, npen) && 2 * n < g.nx) {
+            const bool two = 2 * n + 1 < g.nx;
+            pen_coords<R>(g, pen0 + p, y, z);
+            const unsigned off = ((unsigned)(pen0 + p) * (unsigned)g.nx + (unsigned)(2 * n)) * (unsigned)sizeof(R);
+            stencil_load<R>(t, a.yin, g, 2 * n, y, z, off, vec, two, ph.terms);
+            if (s > 1) {
+                load_pair32(a.mn, g.N, off, vec, two, mn[0], mn[1], stream);
+                load_pair32(a.acc, g.N, off, vec, two, acc[0], acc[1], stream);
+            }
+        }
+    }
     if (has_demag) c2r_lines<R, BIG, LN>(buf, Y1, g, mb, pen0, npen);
     // classical RK4 tableau
-    const int s = a.stage;
     const R bws = s == 2 || s == 3 ? (R)(1.0 / 3.0) : (R)(1.0 / 6.0);
     const R cdt = (s == 3 ? (R)1 : (R)0.5) * a.dt;
     // stage 0 is a forward Euler step: m_{n+1} = y + dt k, renormalised like a new state
@@ -243,7 +279,7 @@ __global__ void __launch_bounds__(kNT) stage_kernel(const cx<R>* Y1, cx<R>* X1, 
     const bool fwd = a.want_next && has_demag;
     // one slot (cell pair) per iteration; kept rolled to keep the kernel small
 #pragma unroll 1
-    for (int i = 0; i < maxslot<BIG>(); ++i) {
+    for (int i = 0; i < (PRE ? 1 : maxslot<BIG>()); ++i) {
         const int e = threadIdx.x + i * kNT;
         if (e >= slots_of<LN>(g, npen)) continue;
         int p, n;
@@ -262,14 +298,18 @@ __global__ void __launch_bounds__(kNT) stage_kernel(const cx<R>* Y1, cx<R>* X1, 
         const unsigned id = (unsigned)(pen0 + p) * (unsigned)g.nx + (unsigned)x0;
         const unsigned off = id * (unsigned)sizeof(R);
         // RK4 registers first, so their loads are in flight with the stencil's
-        R k[2][3], mn[2][3], acc[2][3], xn[2][3], nrm[2];
-        if (s > 1) {
+        R k[2][3], xn[2][3], nrm[2];
+        if (!PRE && s > 1) {
             load_pair32(a.mn, g.N, off, vec, two, mn[0], mn[1], stream);
             load_pair32(a.acc, g.N, off, vec, two, acc[0], acc[1], stream);
         }
         R ys[2][3], H[2][3], sw[2] = {(R)1, (R)1};
         if constexpr (V > 0) {
-            local_field_plain<R>(a.yin, g, x0, y, z, off, vec, two, ph, ys, H);
+            local_field_plain<R, PRE>(t, a.yin, g, x0, y, z, off, vec, two, ph, H);
+#pragma unroll
+            for (int q = 0; q < 2; ++q)
+#pragma unroll
+                for (int c = 0; c < 3; ++c) ys[q][c] = t.m[q][c];
         } else {
             R ex[2], dm[2], an[2];
             local_field_pair<R>(a.yin, g, x0, y, z, vec, two, ph, ys, H, ex, dm, an, false, sw);
@@ -493,7 +533,14 @@ __global__ void __launch_bounds__(kNT) bstage_kernel(const cx<R>* Y1, cx<R>* X1,
         const unsigned id = (unsigned)(pen0 + p) * (unsigned)g.nx + (unsigned)x0;
         const unsigned off = id * (unsigned)sizeof(R);
         R mu[2][3], Kmu[2][3];
-        local_field_plain<R>(a.mu, g, x0, y, z, off, vec, two, ph, mu, Kmu);
+        {
+            Stencil<R> t;
+            local_field_plain<R>(t, a.mu, g, x0, y, z, off, vec, two, ph, Kmu);
+#pragma unroll
+            for (int q = 0; q < 2; ++q)
+#pragma unroll
+                for (int c = 0; c < 3; ++c) mu[q][c] = t.m[q][c];
+        }
         if (has_demag) {
 #pragma unroll
             for (int q = 0; q < 2; ++q)
@@ -678,6 +725,14 @@ __global__ void copy_kernel(const R* __restrict__ src, R* __restrict__ dst, long
         }                                                                                                  \
     } while (0)
 
+// Loads ahead of the inverse x pass: on grids of at most two pencil blocks per
+// CU with at most one cell pair per thread, where nothing else hides the second
+// wait for memory: 10 RK4 steps at 128x32x1 in double precision 616 -> 577 us, 16
+// such films in single precision 722 -> 706.  With more blocks the registers
+// (74 -> 117 in single precision) cost more than the wait: a gradient at
+// 256x256x8, 1024 blocks, 7060 -> 7328 us, RK4 at 301x187x13 1540 -> 1818.
+static bool ahead(const Plan& pl) { return pl.pencil_blocks <= 512 && pl.np * std::max(1, pl.Lh / 2) <= kNT; }
+
 template <typename R>
 hipError_t launch_xfwd(const Plan& pl, const R* f, void* X1, const R* msp, hipStream_t s) {
     MAGX_PENCIL_LAUNCH(xfwd_kernel, (), f, static_cast<cx<R>*>(X1), make_pg(pl), msp);
@@ -695,10 +750,12 @@ hipError_t launch_field(const Plan& pl, const Phys<R>& ph, const void* Y1, const
         MAGX_PENCIL_LAUNCH(field_reduce_kernel, (, 0), y, f, H, g, ph, has_demag, with_bias, energy, sum_input, partials);
     else if (sum_input)
         MAGX_PENCIL_LAUNCH(field_reduce_kernel, (, 1), y, f, H, g, ph, has_demag, with_bias, energy, sum_input, partials);
+    else if (plain && ahead(pl))
+        MAGX_PENCIL_LAUNCH(field_kernel, (, 1, true), y, f, H, g, ph, has_demag, with_bias, energy, sum_input, partials);
     else if (plain)
-        MAGX_PENCIL_LAUNCH(field_kernel, (, 1), y, f, H, g, ph, has_demag, with_bias, energy, sum_input, partials);
+        MAGX_PENCIL_LAUNCH(field_kernel, (, 1, false), y, f, H, g, ph, has_demag, with_bias, energy, sum_input, partials);
     else
-        MAGX_PENCIL_LAUNCH(field_kernel, (, 0), y, f, H, g, ph, has_demag, with_bias, energy, sum_input, partials);
+        MAGX_PENCIL_LAUNCH(field_kernel, (, 0, false), y, f, H, g, ph, has_demag, with_bias, energy, sum_input, partials);
     return hipGetLastError();
 }
 
@@ -709,9 +766,10 @@ hipError_t launch_stage(const Plan& pl, const Phys<R>& ph, const void* Y1, void*
     const PG g = make_pg(pl);
     const cx<R>* y = static_cast<const cx<R>*>(Y1);
     cx<R>* x = static_cast<cx<R>*>(X1);
-    if (ph.msp || ph.nf) MAGX_PENCIL_LAUNCH(stage_kernel, (, 0), y, x, g, ph, a, has_demag);
-    else if (a.tapeH) MAGX_PENCIL_LAUNCH(stage_kernel, (, 2), y, x, g, ph, a, has_demag);
-    else MAGX_PENCIL_LAUNCH(stage_kernel, (, 1), y, x, g, ph, a, has_demag);
+    if (ph.msp || ph.nf) MAGX_PENCIL_LAUNCH(stage_kernel, (, 0, false), y, x, g, ph, a, has_demag);
+    else if (a.tapeH) MAGX_PENCIL_LAUNCH(stage_kernel, (, 2, false), y, x, g, ph, a, has_demag);
+    else if (ahead(pl)) MAGX_PENCIL_LAUNCH(stage_kernel, (, 1, true), y, x, g, ph, a, has_demag);
+    else MAGX_PENCIL_LAUNCH(stage_kernel, (, 1, false), y, x, g, ph, a, has_demag);
     return hipGetLastError();
 }
 
