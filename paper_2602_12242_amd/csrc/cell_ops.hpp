@@ -64,15 +64,21 @@ __device__ __forceinline__ void pg_fix(PG& g) {
 }
 
 // Cases of a launch switch over the line length: the lengths with an odd factor.
-#define MAGX_ODD_LINES(KERNEL, LDS, ...)                                                                  \
-    case 80: hipLaunchKernelGGL((KERNEL<R, false, 80>), grid_, block_, LDS, s, __VA_ARGS__); break;      \
-    case 96: hipLaunchKernelGGL((KERNEL<R, false, 96>), grid_, block_, LDS, s, __VA_ARGS__); break;      \
-    case 160: hipLaunchKernelGGL((KERNEL<R, false, 160>), grid_, block_, LDS, s, __VA_ARGS__); break;    \
-    case 192: hipLaunchKernelGGL((KERNEL<R, false, 192>), grid_, block_, LDS, s, __VA_ARGS__); break;    \
-    case 320: hipLaunchKernelGGL((KERNEL<R, false, 320>), grid_, block_, LDS, s, __VA_ARGS__); break;    \
-    case 384: hipLaunchKernelGGL((KERNEL<R, false, 384>), grid_, block_, LDS, s, __VA_ARGS__); break;    \
-    case 640: hipLaunchKernelGGL((KERNEL<R, false, 640>), grid_, block_, LDS, s, __VA_ARGS__); break;    \
-    case 768: hipLaunchKernelGGL((KERNEL<R, false, 768>), grid_, block_, LDS, s, __VA_ARGS__); break;
+// VV: further template arguments in parentheses, "()" or "(, value)".
+#define MAGX_UNWRAP(...) __VA_ARGS__
+#define MAGX_LINE_CASE(LN, KERNEL, VV, LDS, ...)                                                          \
+    case LN:                                                                                              \
+        hipLaunchKernelGGL((KERNEL<R, false, LN MAGX_UNWRAP VV>), grid_, block_, LDS, s, __VA_ARGS__);    \
+        break;
+#define MAGX_ODD_LINES(KERNEL, VV, LDS, ...)       \
+    MAGX_LINE_CASE(80, KERNEL, VV, LDS, __VA_ARGS__)  \
+    MAGX_LINE_CASE(96, KERNEL, VV, LDS, __VA_ARGS__)  \
+    MAGX_LINE_CASE(160, KERNEL, VV, LDS, __VA_ARGS__) \
+    MAGX_LINE_CASE(192, KERNEL, VV, LDS, __VA_ARGS__) \
+    MAGX_LINE_CASE(320, KERNEL, VV, LDS, __VA_ARGS__) \
+    MAGX_LINE_CASE(384, KERNEL, VV, LDS, __VA_ARGS__) \
+    MAGX_LINE_CASE(640, KERNEL, VV, LDS, __VA_ARGS__) \
+    MAGX_LINE_CASE(768, KERNEL, VV, LDS, __VA_ARGS__)
 
 // Cell-pair slots of npen lines (Lh/2 each) and the line p and pair n of slot e.
 template <int LN> constexpr int line_odd() { return LN > 0 ? odd_part(LN) : 1; }

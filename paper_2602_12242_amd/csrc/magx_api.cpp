@@ -811,7 +811,21 @@ static int do_step_mri(magx_ctx* c, R* m, const magx_params* p, double dt, doubl
             if (launch_mri_slow<R>(pl, pslow_t, X1, cur, demag ? 1 : 0, Sout, Sa, Sb, (R)kw.w[i][0],
                                    (R)kw.w[i][1], (R)kw.w[i][i], rf, s) != hipSuccess)
                 return MAGX_EHIP;
-            for (long long sub = 0; sub < nsub[i]; ++sub) {
+            // thin grids: a substep is one kernel; the forward x pass of the next
+            // slow evaluation is then a kernel of its own
+            const bool whole = pl.nz <= mri_substep_planes<R>() && !pfast.msp && !pfast.nf;
+            for (long long sub = 0; whole && sub < nsub[i]; ++sub) {
+                const bool last = sub == nsub[i] - 1;
+                const int norm = last && (p->renorm == 2 || (i == 2 && p->renorm >= 1)) ? 1 : 0;
+                if (launch_mri_substep<R>(pl, pfast, cur, oth, rf, kw.A2, kw.B2, (R)hsub[i], norm, s) != hipSuccess)
+                    return MAGX_EHIP;
+                std::swap(cur, oth);
+                if (last && demag && !(n == nsteps - 1 && i == 2)) {
+                    ProfScope ps(c, kProfXfwd, s);
+                    if (launch_xfwd<R>(pl, cur, X1, nullptr, s) != hipSuccess) return MAGX_EHIP;
+                }
+            }
+            for (long long sub = 0; !whole && sub < nsub[i]; ++sub) {
                 for (int k = 0; k < 3; ++k) {
                     const bool last = sub == nsub[i] - 1 && k == 2;
                     const int norm = last && (p->renorm == 2 || (i == 2 && p->renorm >= 1)) ? 1 : 0;

@@ -181,6 +181,12 @@ hipError_t launch_copy(const R* src, R* dst, long long n, hipStream_t s);
 template <typename R>
 hipError_t launch_mri_slow(const Plan& pl, const Phys<R>& ph, const void* Y1, const R* y, int has_demag, R* S_out,
                            const R* Sa, const R* Sb, R wa, R wb, R wn, R* r_out, hipStream_t s);
+// largest nz of launch_mri_substep (in double precision its tiles of 7 and 8
+// planes leave one block per CU: 26x10x8 264 -> 287 us a step, 27x11x6 402 -> 371)
+template <typename R> constexpr int mri_substep_planes() { return sizeof(R) == 4 ? 8 : 6; }
+template <typename R>
+hipError_t launch_mri_substep(const Plan& pl, const Phys<R>& ph, const R* v, R* vout, const R* r, const double A[3],
+                              const double B[3], R h, int norm, hipStream_t s);
 template <typename R>
 hipError_t launch_mri_fast(const Plan& pl, const Phys<R>& ph, const R* v, R* vout, R* q, const R* r, R Ak, R Bk,
                            R h, int first, int norm, void* X1, hipStream_t s);

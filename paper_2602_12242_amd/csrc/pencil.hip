@@ -215,7 +215,7 @@ __global__ void __launch_bounds__(kNT) field_reduce_kernel(const cx<R>* __restri
 // either and without a tape, 2 the same with a tape.  The plain kernels carry
 // fewer uniform values (the general one spills about 60 scalar registers to
 // vector lanes, a lane read each time one is used) and no ghost selects.
-// PRE (a thread's single cell pair on grids of few blocks, see ahead()): the
+// PRE (a thread's single cell pair on small systems, see ahead()): the
 // stencil and the RK4 registers are loaded before the inverse x pass.
 template <typename R, bool BIG, int LN, int V, bool PRE>
 __global__ void __launch_bounds__(kNT) stage_kernel(const cx<R>* Y1, cx<R>* X1, PG g,
@@ -694,29 +694,16 @@ __global__ void copy_kernel(const R* __restrict__ src, R* __restrict__ dst, long
 
 // Pencil kernel launch: the line lengths of pencil_line with compile-time
 // geometry, every other size with runtime geometry.
-#define MAGX_UNWRAP(...) __VA_ARGS__
-#define MAGX_PENCIL_CASE(LN, KERNEL, VV, ...)                                                              \
-    case LN:                                                                                               \
-        hipLaunchKernelGGL((KERNEL<R, false, LN MAGX_UNWRAP VV>), grid_, block_, lds_, s, __VA_ARGS__);    \
-        break;
-// VV: further template arguments in parentheses, "()" or "(, value)"
 #define MAGX_PENCIL_LAUNCH(KERNEL, VV, ...)                                                                \
     do {                                                                                                   \
         const dim3 grid_((unsigned)pl.pencil_blocks), block_(kNT);                                         \
         const size_t lds_ = pencil_lds(pl);                                                                \
         switch (pencil_line(pl)) {                                                                         \
-            MAGX_PENCIL_CASE(80, KERNEL, VV, __VA_ARGS__)                                                  \
-            MAGX_PENCIL_CASE(96, KERNEL, VV, __VA_ARGS__)                                                  \
-            MAGX_PENCIL_CASE(128, KERNEL, VV, __VA_ARGS__)                                                 \
-            MAGX_PENCIL_CASE(160, KERNEL, VV, __VA_ARGS__)                                                 \
-            MAGX_PENCIL_CASE(192, KERNEL, VV, __VA_ARGS__)                                                 \
-            MAGX_PENCIL_CASE(256, KERNEL, VV, __VA_ARGS__)                                                 \
-            MAGX_PENCIL_CASE(320, KERNEL, VV, __VA_ARGS__)                                                 \
-            MAGX_PENCIL_CASE(384, KERNEL, VV, __VA_ARGS__)                                                 \
-            MAGX_PENCIL_CASE(512, KERNEL, VV, __VA_ARGS__)                                                 \
-            MAGX_PENCIL_CASE(640, KERNEL, VV, __VA_ARGS__)                                                 \
-            MAGX_PENCIL_CASE(768, KERNEL, VV, __VA_ARGS__)                                                 \
-            MAGX_PENCIL_CASE(1024, KERNEL, VV, __VA_ARGS__)                                                \
+            MAGX_ODD_LINES(KERNEL, VV, lds_, __VA_ARGS__)                                                  \
+            MAGX_LINE_CASE(128, KERNEL, VV, lds_, __VA_ARGS__)                                             \
+            MAGX_LINE_CASE(256, KERNEL, VV, lds_, __VA_ARGS__)                                             \
+            MAGX_LINE_CASE(512, KERNEL, VV, lds_, __VA_ARGS__)                                             \
+            MAGX_LINE_CASE(1024, KERNEL, VV, lds_, __VA_ARGS__)                                            \
             default:                                                                                       \
                 if (pencil_big(pl))                                                                        \
                     hipLaunchKernelGGL((KERNEL<R, true, 0 MAGX_UNWRAP VV>), grid_, block_, lds_, s, __VA_ARGS__);  \
@@ -725,13 +712,16 @@ __global__ void copy_kernel(const R* __restrict__ src, R* __restrict__ dst, long
         }                                                                                                  \
     } while (0)
 
-// Loads ahead of the inverse x pass: on grids of at most two pencil blocks per
-// CU with at most one cell pair per thread, where nothing else hides the second
-// wait for memory: 10 RK4 steps at 128x32x1 in double precision 616 -> 577 us, 16
-// such films in single precision 722 -> 706.  With more blocks the registers
-// (74 -> 117 in single precision) cost more than the wait: a gradient at
-// 256x256x8, 1024 blocks, 7060 -> 7328 us, RK4 at 301x187x13 1540 -> 1818.
-static bool ahead(const Plan& pl) { return pl.pencil_blocks <= 512 && pl.np * std::max(1, pl.Lh / 2) <= kNT; }
+// Loads ahead of the inverse x pass: at most one cell pair per thread and at most
+// 64 blocks per system, where nothing else hides the second wait for memory: 10
+// RK4 steps at 128x32x1 in double precision 616 -> 577 us, 16 such films in
+// single precision 722 -> 706.  The line depends on the system alone, since a
+// member of a batch gets the bits of a single system and the two kernels round
+// differently (fused multiply-adds); it lies this low for the batches: the
+// registers (74 -> 117 in single precision) cost a full GPU more than the wait,
+// 24 systems of 128x128x2 5491 -> 5943 us with it, 64 films 1607 -> 1616, while
+// one 128x128x2 system would gain 2 %.
+static bool ahead(const Plan& pl) { return pl.blocks_per_member <= 64 && pl.np * std::max(1, pl.Lh / 2) <= kNT; }
 
 template <typename R>
 hipError_t launch_xfwd(const Plan& pl, const R* f, void* X1, const R* msp, hipStream_t s) {
