@@ -80,6 +80,15 @@ __device__ __forceinline__ void pg_fix(PG& g) {
     MAGX_LINE_CASE(640, KERNEL, VV, LDS, __VA_ARGS__) \
     MAGX_LINE_CASE(768, KERNEL, VV, LDS, __VA_ARGS__)
 
+// log2 of the largest radix of a line transform.  Radix 8 in place of 16 costs a
+// pass at 256 (4 8 8 in place of 16 16) but spreads over twice the threads: a
+// gradient at 256x256x8 7100 -> 6870 us, at 190x75x9 in double precision (lines of
+// 192: 8 8 3 in place of 4 16 3) 2610 -> 2567; films (128) and 1024-cell lines were
+// 2 and 1 % slower with it, 320 and 512 equal.
+template <bool BIG, int LN> constexpr int line_lgm() {
+    return BIG ? 5 : (LN == 256 || LN == 192 || LN == 160 || LN == 96 ? 3 : 4);
+}
+
 // Cell-pair slots of npen lines (Lh/2 each) and the line p and pair n of slot e.
 template <int LN> constexpr int line_odd() { return LN > 0 ? odd_part(LN) : 1; }
 template <int LN> __device__ __forceinline__ int slots_of(const PG& g, int npen) {
@@ -729,7 +738,7 @@ __device__ void c2r_lines(cx<R>* buf, const cx<R>* Y1, const PG& g, int mb, int 
     __syncthreads();
     auto none_load = [&](int, int) -> cx<R> { return mk<R>(0, 0); };
     auto none_store = [&](int, int, cx<R>) {};
-    fft_io<R, true, pemax<BIG>(), true, true, kLines, 1, false, true, lgmax<pemax<BIG>()>(), kNT, true, ODD>(
+    fft_io<R, true, pemax<BIG>(), true, true, kLines, 1, false, true, line_lgm<BIG, LN>(), kNT, true, ODD>(
         buf, g.lgLh, 0, npen * 3, none_load, none_store);
 }
 
@@ -747,7 +756,7 @@ __device__ void r2c_lines(cx<R>* buf, cx<R>* X1, const PG& g, int mb, int pen0, 
     auto none_store = [&](int, int, cx<R>) {};
     tw_lds_fill<R, ODD>();   // pass twiddles (same values if c2r_lines filled them)
     __syncthreads();
-    fft_io<R, false, pemax<BIG>(), true, true, kLines, 1, true, false, lgmax<pemax<BIG>()>(), kNT, true, ODD>(
+    fft_io<R, false, pemax<BIG>(), true, true, kLines, 1, true, false, line_lgm<BIG, LN>(), kNT, true, ODD>(
         buf, g.lgLh, 0, npen * 3, none_load, none_store);
     const R half = (R)0.5;
     if (ODD == 1 && (1 << lgq) >= kNT) {
