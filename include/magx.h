@@ -301,7 +301,8 @@ int magx_ctx_info(const magx_ctx* ctx, magx_grid* g, magx_dtype* dt);
  * 6, Hz, tz): element (c, kz, ky, kx) of the real octant of the tensor
  * spectrum (c = xx yy zz xy xz yz, already scaled by 1/(Px Py Pz)) is at
  * (((ky * ntz + kx / tz) * 6 + c) * Hz + kz) * tz + kx % tz; Hy = Py/2 + 1,
- * Hz = Pz/2 + 1, kx < Px/2 + 1 <= ntz * tz.  Host only. */
+ * Hz = Pz/2 + 1, kx < Px/2 + 1 <= ntz * tz.  (Copies of parts of it in other
+ * orders may follow.)  Host only. */
 int magx_spectrum_layout(const magx_ctx* ctx, int dims[5]);
 
 /* Diagnostics: from magx_profile_start until magx_profile_stop, every launch
@@ -310,8 +311,10 @@ int magx_spectrum_layout(const magx_ctx* ctx, int dims[5]);
  * 3 z pass with the spectral product, 4 inverse y pass, 5 RK4 stage (inverse
  * x pass + local field + LLG + stage update + next forward x pass), 6 field
  * output (inverse x pass + local field), 7 reverse-step start, 8 reverse RK4
- * stage.  magx_profile_stop waits for the recorded events and returns the
- * number of timed launches and their summed duration in milliseconds. */
+ * stage.  On thin grids and films one kernel does the work of kinds 2, 3 and 4;
+ * it is timed as kind 3, and kinds 2 and 4 have no launches.  magx_profile_stop
+ * waits for the recorded events and returns the number of timed launches and
+ * their summed duration in milliseconds. */
 int magx_profile_start(magx_ctx* ctx, int kind);
 int magx_profile_stop(magx_ctx* ctx, long long* launches, double* total_ms);
 

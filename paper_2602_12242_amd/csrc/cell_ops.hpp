@@ -11,11 +11,15 @@
 
 namespace magx {
 
-// Two register budgets: BIG = false holds 16 FFT elements and 4 cell-pair
-// slots per thread (np * Lh <= 1024, every grid with nx <= 1024); BIG = true
-// holds 32 and 8 (nx up to 2048, float only).
-template <bool BIG> constexpr int pemax() { return BIG ? 32 : 16; }
-template <bool BIG> constexpr int maxslot() { return BIG ? 8 : 4; }
+// ORD: order of X1/Y1 and register budget of a pencil kernel.  kRows and kColumns
+// hold 16 FFT elements and 4 cell-pair slots per thread (np * Lh <= 1024, every
+// grid with nx <= 1024); kBigRows holds 32 and 8 (nx up to 2048, float only).
+// kColumns is the order of the column convolution (see x_row); it is a constant
+// of the kernel because an order chosen at run time cost the small row-order
+// grids 4 % (10 RK4 steps at 128x32x1 in double precision 577 -> 600 us).
+constexpr int kRows = 0, kBigRows = 1, kColumns = 2;
+template <int ORD> constexpr int pemax() { return ORD == kBigRows ? 32 : 16; }
+template <int ORD> constexpr int maxslot() { return ORD == kBigRows ? 8 : 4; }
 
 struct PG {
     int nx, ny, nz, Lh, lgLh, Hx, Sx, lgPx, np, npen_total;   // npen_total: pencils of one member
@@ -26,6 +30,7 @@ struct PG {
     int lgLq;
     int bpm;                                                 // blocks per member
     int zmajor;                                              // block order: z fastest (see block_pencils)
+    int ks;                                                  // column order of X1: stride of four kx
     int stream;                                              // streaming cell-pair stores (see store_pair;
                                                              // kernels read it once, as stream_of)
     long long N;                                             // cells of one member
@@ -66,27 +71,27 @@ __device__ __forceinline__ void pg_fix(PG& g) {
 // Cases of a launch switch over the line length: the lengths with an odd factor.
 // VV: further template arguments in parentheses, "()" or "(, value)".
 #define MAGX_UNWRAP(...) __VA_ARGS__
-#define MAGX_LINE_CASE(LN, KERNEL, VV, LDS, ...)                                                          \
+#define MAGX_LINE_CASE(ORD, LN, KERNEL, VV, LDS, ...)                                                     \
     case LN:                                                                                              \
-        hipLaunchKernelGGL((KERNEL<R, false, LN MAGX_UNWRAP VV>), grid_, block_, LDS, s, __VA_ARGS__);    \
+        hipLaunchKernelGGL((KERNEL<R, ORD, LN MAGX_UNWRAP VV>), grid_, block_, LDS, s, __VA_ARGS__);      \
         break;
-#define MAGX_ODD_LINES(KERNEL, VV, LDS, ...)       \
-    MAGX_LINE_CASE(80, KERNEL, VV, LDS, __VA_ARGS__)  \
-    MAGX_LINE_CASE(96, KERNEL, VV, LDS, __VA_ARGS__)  \
-    MAGX_LINE_CASE(160, KERNEL, VV, LDS, __VA_ARGS__) \
-    MAGX_LINE_CASE(192, KERNEL, VV, LDS, __VA_ARGS__) \
-    MAGX_LINE_CASE(320, KERNEL, VV, LDS, __VA_ARGS__) \
-    MAGX_LINE_CASE(384, KERNEL, VV, LDS, __VA_ARGS__) \
-    MAGX_LINE_CASE(640, KERNEL, VV, LDS, __VA_ARGS__) \
-    MAGX_LINE_CASE(768, KERNEL, VV, LDS, __VA_ARGS__)
+#define MAGX_ODD_LINES(ORD, KERNEL, VV, LDS, ...)          \
+    MAGX_LINE_CASE(ORD, 80, KERNEL, VV, LDS, __VA_ARGS__)  \
+    MAGX_LINE_CASE(ORD, 96, KERNEL, VV, LDS, __VA_ARGS__)  \
+    MAGX_LINE_CASE(ORD, 160, KERNEL, VV, LDS, __VA_ARGS__) \
+    MAGX_LINE_CASE(ORD, 192, KERNEL, VV, LDS, __VA_ARGS__) \
+    MAGX_LINE_CASE(ORD, 320, KERNEL, VV, LDS, __VA_ARGS__) \
+    MAGX_LINE_CASE(ORD, 384, KERNEL, VV, LDS, __VA_ARGS__) \
+    MAGX_LINE_CASE(ORD, 640, KERNEL, VV, LDS, __VA_ARGS__) \
+    MAGX_LINE_CASE(ORD, 768, KERNEL, VV, LDS, __VA_ARGS__)
 
 // log2 of the largest radix of a line transform.  Radix 8 in place of 16 costs a
 // pass at 256 (4 8 8 in place of 16 16) but spreads over twice the threads: a
 // gradient at 256x256x8 7100 -> 6870 us, at 190x75x9 in double precision (lines of
 // 192: 8 8 3 in place of 4 16 3) 2610 -> 2567; films (128) and 1024-cell lines were
 // 2 and 1 % slower with it, 320 and 512 equal.
-template <bool BIG, int LN> constexpr int line_lgm() {
-    return BIG ? 5 : (LN == 256 || LN == 192 || LN == 160 || LN == 96 ? 3 : 4);
+template <int ORD, int LN> constexpr int line_lgm() {
+    return ORD == kBigRows ? 5 : (LN == 256 || LN == 192 || LN == 160 || LN == 96 ? 3 : 4);
 }
 
 // Cell-pair slots of npen lines (Lh/2 each) and the line p and pair n of slot e.
@@ -105,11 +110,11 @@ template <int LN> __device__ __forceinline__ void slot_of(const PG& g, int e, in
 }
 
 // The streaming flag of a kernel, read once into a register: the 32-element
-// register budget (BIG) leaves no room for the second store path, so those
+// register budget (kBigRows) leaves no room for the second store path, so those
 // kernels never stream.
-template <bool BIG>
+template <int ORD>
 __device__ __forceinline__ bool stream_of(const PG& g) {
-    return !BIG && g.stream != 0;
+    return ORD != kBigRows && g.stream != 0;
 }
 
 inline PG make_pg(const Plan& pl) {
@@ -121,6 +126,7 @@ inline PG make_pg(const Plan& pl) {
     g.div_ny = make_fastdiv(pl.ny);
     g.div_hx = make_fastdiv(pl.Hx);
     g.zmajor = pl.pencil_zmajor;
+    g.ks = 12 * g.npen_total;
     // fields of 64 MiB and more (a batch counts whole) are far larger than the caches
     g.stream = !pencil_big(pl) && 3.0 * (double)pl.ncell * pl.nbatch * pl.esize >= 64.0 * (1 << 20) ? 1 : 0;
     return g;
@@ -604,13 +610,24 @@ __device__ __forceinline__ void pen_coords(const PG& g, int pen, int& y, int& z)
 // for np Lh <= 1024).
 constexpr int kXIt = 6;
 
-// Row of X1/Y1 holding component c of pencil p (32-bit element offset: the
-// spectral arrays of a whole batch stay below 2^31 elements).
-__device__ __forceinline__ unsigned x_row(const PG& g, int mb, int c, int pen) {
-    return ((unsigned)(mb * 3 + c) * (unsigned)g.npen_total + (unsigned)pen) * (unsigned)g.Sx;
+// Offset of kx in a row of X1/Y1.
+template <int ORD>
+__device__ __forceinline__ unsigned col_off(const PG& g, int kx) {
+    return ORD == kColumns ? umul24((unsigned)kx >> 2, (unsigned)g.ks) + ((unsigned)kx & 3u) : (unsigned)kx;
 }
 
-template <int V> struct IntC { static constexpr int value = V; };
+// Row of X1/Y1 holding component c of pencil p (32-bit element offset: the
+// spectral arrays of a whole batch stay below 2^31 elements).
+// Column order: [kx / 4][y][c][z][kx % 4], the real X[0] and X[Lh] stored together
+// at kx = 0.
+template <int ORD>
+__device__ __forceinline__ unsigned x_row(const PG& g, int mb, int c, int pen) {
+    if constexpr (ORD == kColumns) {
+        const int z = fdiv(pen, g.div_ny), y = pen - z * g.ny;
+        return (unsigned)mb * (unsigned)(g.Lh >> 2) * (unsigned)g.ks + 4u * (unsigned)((y * 3 + c) * g.nz + z);
+    }
+    return ((unsigned)(mb * 3 + c) * (unsigned)g.npen_total + (unsigned)pen) * (unsigned)g.Sx;
+}
 
 // The half-length real-FFT split and merge steps pair bin k with its mirror
 // Lh - k: both come from the same two values and the same twiddle
@@ -622,7 +639,7 @@ template <int V> struct IntC { static constexpr int value = V; };
 // of line l is buf[l*Lh + x/2].x (x even) or .y (x odd).  Split step of the
 // half-length inverse, Z[k] = (X[k] + X*[Lh-k]) + i (X[k] - X*[Lh-k]) w^-k
 // (w^-k = conj(W^k)), into LDS; then the inverse FFT of every line in LDS.
-template <typename R, bool BIG, int LN>
+template <typename R, int ORD, int LN>
 __device__ void c2r_lines(cx<R>* buf, const cx<R>* Y1, const PG& g, int mb, int pen0, int npen) {
     constexpr int ODD = line_odd<LN>();
     const int Lh = g.Lh;
@@ -655,16 +672,17 @@ __device__ void c2r_lines(cx<R>* buf, const cx<R>* Y1, const PG& g, int mb, int 
                 for (int i = 0; i < LC; ++i) {
                     const int l = min(l0 + i, nl - 1);
                     const int p = l / 3, c = l - 3 * p;
-                    const cx<R>* row = Y1 + x_row(g, mb, c, pen0 + p);
+                    const cx<R>* row = Y1 + x_row<ORD>(g, mb, c, pen0 + p);
 #pragma unroll
                     for (int k = 0; k < IPL; ++k) {
                         const int t = (int)threadIdx.x + k * kNT;
-                        A[i][k] = row[t];
-                        B[i][k] = row[Lh - t];
+                        A[i][k] = row[col_off<ORD>(g, t)];
+                        // column order: X[0] and X[Lh] are real and stored together
+                        B[i][k] = row[col_off<ORD>(g, ORD == kColumns && t == 0 ? 0 : Lh - t)];
                     }
                     // X[Lh/2] for item 0 of a line (loaded by the first wave only)
                     C[i] = mk<R>((R)0, (R)0);
-                    if (threadIdx.x < 64) C[i] = row[threadIdx.x == 0 ? (Lh >> 1) : (int)threadIdx.x];
+                    if (threadIdx.x < 64) C[i] = row[col_off<ORD>(g, threadIdx.x == 0 ? (Lh >> 1) : (int)threadIdx.x)];
                 }
 #pragma unroll
                 for (int i = 0; i < LC; ++i) {
@@ -675,6 +693,10 @@ __device__ void c2r_lines(cx<R>* buf, const cx<R>* Y1, const PG& g, int mb, int 
                     for (int k = 0; k < IPL; ++k) {
                         const int t = (int)threadIdx.x + k * kNT;
                         if (t == 0) {
+                            if (ORD == kColumns) {
+                                B[i][k] = mk<R>(A[i][k].y, (R)0);
+                                A[i][k].y = (R)0;
+                            }
                             out[0] = split(A[i][k], B[i][k], mk<R>((R)1, (R)0));
                             out[Lh >> 1] = split(C[i], C[i], mk<R>((R)0, (R)1));   // conj(W^(Lh/2)) = i
                         } else {
@@ -702,9 +724,9 @@ __device__ void c2r_lines(cx<R>* buf, const cx<R>* Y1, const PG& g, int mb, int 
             int line, t;
             slot_of<LN>(g, e, line, t);
             const int p = line / 3, c = line - 3 * p;
-            const cx<R>* row = Y1 + x_row(g, mb, c, pen0 + p);
-            A[i] = row[t];
-            B[i] = row[Lh - t];
+            const cx<R>* row = Y1 + x_row<ORD>(g, mb, c, pen0 + p);
+            A[i] = row[col_off<ORD>(g, t)];
+            B[i] = row[col_off<ORD>(g, ORD == kColumns && t == 0 ? 0 : Lh - t)];
             W[i] = tw_fwd<R, ODD>(t << twsh);
             C[i] = mk<R>((R)0, (R)0);
             // X[Lh/2] for item 0 of a line, loaded only by waves holding such an item
@@ -715,7 +737,7 @@ __device__ void c2r_lines(cx<R>* buf, const cx<R>* Y1, const PG& g, int mb, int 
             } else {
                 has0 = lgq < 6 || ((wave0 + i * kNT) & ((1 << lgq) - 1)) == 0;
             }
-            if (has0) C[i] = row[t == 0 ? (Lh >> 1) : t];
+            if (has0) C[i] = row[col_off<ORD>(g, t == 0 ? (Lh >> 1) : t)];
         }
 #pragma unroll
         for (int i = 0; i < kXIt; ++i) {
@@ -725,6 +747,10 @@ __device__ void c2r_lines(cx<R>* buf, const cx<R>* Y1, const PG& g, int mb, int 
             slot_of<LN>(g, e, line, t);
             cx<R>* out = buf + line * Lh;
             if (t == 0) {
+                if (ORD == kColumns) {
+                    B[i] = mk<R>(A[i].y, (R)0);
+                    A[i].y = (R)0;
+                }
                 out[0] = split(A[i], B[i], mk<R>((R)1, (R)0));
                 if (Lh > 1) out[Lh >> 1] = split(C[i], C[i], mk<R>((R)0, (R)1));   // conj(W^(Lh/2)) = i
             } else {
@@ -738,7 +764,7 @@ __device__ void c2r_lines(cx<R>* buf, const cx<R>* Y1, const PG& g, int mb, int 
     __syncthreads();
     auto none_load = [&](int, int) -> cx<R> { return mk<R>(0, 0); };
     auto none_store = [&](int, int, cx<R>) {};
-    fft_io<R, true, pemax<BIG>(), true, true, kLines, 1, false, true, line_lgm<BIG, LN>(), kNT, true, ODD>(
+    fft_io<R, true, pemax<ORD>(), true, true, kLines, 1, false, true, line_lgm<ORD, LN>(), kNT, true, ODD>(
         buf, g.lgLh, 0, npen * 3, none_load, none_store);
 }
 
@@ -746,7 +772,7 @@ __device__ void c2r_lines(cx<R>* buf, const cx<R>* Y1, const PG& g, int mb, int 
 // Hx-column half spectrum of every line to X1.  Merge step: with P = Z[k],
 // Q = Z[Lh-k], E = (P + Q*)/2, O = (P - Q*)/(2i) and T = W^k O,
 // X[k] = E + T and X[Lh-k] = (E - T)*.
-template <typename R, bool BIG, int LN>
+template <typename R, int ORD, int LN>
 __device__ void r2c_lines(cx<R>* buf, cx<R>* X1, const PG& g, int mb, int pen0, int npen) {
     constexpr int ODD = line_odd<LN>();
     const int Lh = g.Lh;
@@ -756,7 +782,7 @@ __device__ void r2c_lines(cx<R>* buf, cx<R>* X1, const PG& g, int mb, int pen0, 
     auto none_store = [&](int, int, cx<R>) {};
     tw_lds_fill<R, ODD>();   // pass twiddles (same values if c2r_lines filled them)
     __syncthreads();
-    fft_io<R, false, pemax<BIG>(), true, true, kLines, 1, true, false, line_lgm<BIG, LN>(), kNT, true, ODD>(
+    fft_io<R, false, pemax<ORD>(), true, true, kLines, 1, true, false, line_lgm<ORD, LN>(), kNT, true, ODD>(
         buf, g.lgLh, 0, npen * 3, none_load, none_store);
     const R half = (R)0.5;
     if (ODD == 1 && (1 << lgq) >= kNT) {
@@ -770,23 +796,23 @@ __device__ void r2c_lines(cx<R>* buf, cx<R>* X1, const PG& g, int mb, int pen0, 
             const int nl = npen * 3;
             for (int l = 0; l < nl; ++l) {
                 const int p = l / 3, c = l - 3 * p;
-                cx<R>* row = X1 + x_row(g, mb, c, pen0 + p);
+                cx<R>* row = X1 + x_row<ORD>(g, mb, c, pen0 + p);
                 const cx<R>* in = buf + l * Lh;
 #pragma unroll
                 for (int k = 0; k < IPL; ++k) {
                     const int t = (int)threadIdx.x + k * kNT;
                     if (t == 0) {
                         const cx<R> P = in[0];
-                        row[0] = mk<R>(P.x + P.y, (R)0);
-                        row[Lh] = mk<R>(P.x - P.y, (R)0);
-                        row[Lh >> 1] = cconj<R>(in[Lh >> 1]);   // W^(Lh/2) = -i
+                        row[0] = mk<R>(P.x + P.y, ORD == kColumns ? P.x - P.y : (R)0);
+                        if (ORD != kColumns) row[Lh] = mk<R>(P.x - P.y, (R)0);
+                        row[col_off<ORD>(g, Lh >> 1)] = cconj<R>(in[Lh >> 1]);   // W^(Lh/2) = -i
                     } else {
                         const cx<R> P = in[t], Q = in[Lh - t];
                         const cx<R> E = mk<R>(half * (P.x + Q.x), half * (P.y - Q.y));
                         const cx<R> O = mk<R>(half * (P.y + Q.y), half * (Q.x - P.x));
                         const cx<R> T = cmul<R>(W[k], O);
-                        row[t] = cadd<R>(E, T);
-                        row[Lh - t] = mk<R>(E.x - T.x, T.y - E.y);
+                        row[col_off<ORD>(g, t)] = cadd<R>(E, T);
+                        row[col_off<ORD>(g, Lh - t)] = mk<R>(E.x - T.x, T.y - E.y);
                     }
                 }
             }
@@ -813,20 +839,20 @@ __device__ void r2c_lines(cx<R>* buf, cx<R>* X1, const PG& g, int mb, int pen0, 
             int line, t;
             slot_of<LN>(g, e, line, t);
             const int p = line / 3, c = line - 3 * p;
-            cx<R>* row = X1 + x_row(g, mb, c, pen0 + p);
+            cx<R>* row = X1 + x_row<ORD>(g, mb, c, pen0 + p);
             const cx<R>* in = buf + line * Lh;
             if (t == 0) {
                 const cx<R> P = in[0];
-                row[0] = mk<R>(P.x + P.y, (R)0);
-                row[Lh] = mk<R>(P.x - P.y, (R)0);
-                if (Lh > 1) row[Lh >> 1] = cconj<R>(in[Lh >> 1]);   // W^(Lh/2) = -i
+                row[0] = mk<R>(P.x + P.y, ORD == kColumns ? P.x - P.y : (R)0);
+                if (ORD != kColumns) row[Lh] = mk<R>(P.x - P.y, (R)0);
+                if (Lh > 1) row[col_off<ORD>(g, Lh >> 1)] = cconj<R>(in[Lh >> 1]);   // W^(Lh/2) = -i
             } else {
                 const cx<R> P = in[t], Q = in[Lh - t];
                 const cx<R> E = mk<R>(half * (P.x + Q.x), half * (P.y - Q.y));
                 const cx<R> O = mk<R>(half * (P.y + Q.y), half * (Q.x - P.x));
                 const cx<R> T = cmul<R>(W[i], O);
-                row[t] = cadd<R>(E, T);
-                row[Lh - t] = mk<R>(E.x - T.x, T.y - E.y);
+                row[col_off<ORD>(g, t)] = cadd<R>(E, T);
+                row[col_off<ORD>(g, Lh - t)] = mk<R>(E.x - T.x, T.y - E.y);
             }
         }
     }

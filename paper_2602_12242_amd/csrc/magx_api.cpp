@@ -111,6 +111,25 @@ static int pow2_floor(long long v) {
     return p;
 }
 
+// Whether the column convolution takes the grid: one kernel in place of three where
+// a column fits in LDS and its z line in registers, and the film kernel does not
+// take it already.  Two RK4 steps, us, three kernels / one, single
+// and double precision: 300x300x1 450/188 533/249, 100x25x2 229/137 247/149,
+// 512x512x2 683/392 1001/603, 640x160x4 479/398 769/614, 500x500x4 849/694 (double
+// precision does not fit).  Five to eight planes hold 222 registers in single
+// precision, two waves per SIMD: faster where a block has 256 or 512 rows
+// (256x256x8 433/389, 250x250x6 474/384, 500x250x8 811/682, 200x100x5 301/273),
+// slower at other lengths (301x187x8 567/658, 190x75x8 279/297, 100x14x8 235/257).
+// More than 512 rows leave fewer registers per thread; lines of more than 1024
+// values have no pencil kernels in this order.
+static int column_plan(const Plan& p) {
+    const bool f32 = p.esize == 4;
+    if (p.yzfilm || p.Py < 32 || p.Py > 1024 || p.Lh < 16 || p.Lh % 4 != 0 || p.Lh > 1024) return 0;
+    const int maxPz = f32 ? (p.Py == 256 || p.Py == 512 ? 16 : 8) : (p.Py <= 768 ? 8 : 4);
+    if (p.Pz > maxPz || 12LL * p.ny * p.nz >= (1LL << 24)) return 0;   // (24-bit stride of kx in the x passes)
+    return (long long)((3 * p.nz * column_width(p.Py)) | 1) * p.Py * 2 * p.esize <= kColumnLds ? 1 : 0;
+}
+
 int make_plan(const magx_grid* g, magx_dtype dt, int nbatch, Plan* pl) {
     if (!g || !pl || nbatch < 1) return MAGX_EINVAL;
     if (dt != MAGX_F32 && dt != MAGX_F64) return MAGX_EDTYPE;
@@ -239,7 +258,9 @@ int make_plan(const magx_grid* g, magx_dtype dt, int nbatch, Plan* pl) {
                  p.Lh >= p.tz && p.Lh % p.tz == 0 && p.Sx == p.Lh + 16) ? 1 : 0;
     p.tn_off = (long long)p.Hy * p.ntz * 6 * p.Hz * p.tz;
     const long long tn_blocks = p.nyqpack ? (p.Py / 2 + p.tz - 1) / p.tz + 1 : 0;
-    p.spectrum_bytes = (size_t)(p.tn_off + tn_blocks * 6 * p.Hz * p.tz) * es;
+    p.tc_off = p.tn_off + tn_blocks * 6 * p.Hz * p.tz;
+    p.col = column_plan(p);
+    p.spectrum_bytes = (size_t)(p.tc_off + (p.col ? 6LL * p.Hx * p.Hy * p.Hz : 0)) * es;
     const long long a1 = 6 * p.ncell, a2 = 6LL * p.Hy * p.Hx * p.nz;
     p.scratch_a_elems = std::max(a1, a2);
     p.scratch_b_elems = 6LL * p.Hx * p.nz * p.ny;
@@ -334,7 +355,8 @@ static int ensure_twiddles(hipStream_t s, int* device) {
     if (dev < 0 || dev >= 64) return MAGX_EHIP;
     std::lock_guard<std::mutex> lk(g_tw_mutex);
     if (g_tw_ready[dev]) return MAGX_OK;
-    for (auto init : {init_tw_tensor, init_tw_conv32, init_tw_conv64, init_tw_pencil32, init_tw_pencil64, init_tw_mri})
+    for (auto init : {init_tw_tensor, init_tw_conv32, init_tw_conv64, init_tw_pencil32, init_tw_pencil64, init_tw_mri, init_tw_pencil_cols32, init_tw_pencil_cols64,
+                      init_tw_column32, init_tw_column64})
         if (init(s) != hipSuccess) return MAGX_EHIP;
     // other streams of this device may use the table right away
     if (hipStreamSynchronize(s) != hipSuccess) return MAGX_EHIP;
@@ -409,6 +431,12 @@ static int conv_passes(magx_ctx* c, void* ws, R Ms, hipStream_t s) {
     const Plan& pl = c->pl;
     void* X1 = bptr(ws, pl.off_x1);
     void* X2 = bptr(ws, pl.off_x2);
+    if (pl.col) {
+        ProfScope ps(c, kProfZconv, s);
+        if (launch_column<R>(pl, X1, c->spectrum, Ms, s) != hipSuccess) return MAGX_EHIP;
+        c->heff_count++;
+        return MAGX_OK;
+    }
     if (pl.yzfilm) {
         ProfScope ps(c, kProfZconv, s);
         if (launch_yzfilm<R>(pl, X1, c->spectrum, Ms, s) != hipSuccess) return MAGX_EHIP;
@@ -882,6 +910,9 @@ int magx_tensor_init_batched(magx_ctx** ctx, const magx_grid* g, magx_dtype dt, 
     rc = ensure_static_ws(dev);
     if (rc) return rc;
     if (build_tensor_spectrum(pl, spectrum, scratch, s) != hipSuccess) return MAGX_EHIP;
+    if (pl.col && (dt == MAGX_F32 ? launch_column_tensor<float>(pl, spectrum, s)
+                                  : launch_column_tensor<double>(pl, spectrum, s)) != hipSuccess)
+        return MAGX_EHIP;
     magx_ctx* c = new (std::nothrow) magx_ctx;
     if (!c) return MAGX_EINVAL;
     c->pl = pl;

@@ -198,6 +198,15 @@ __device__ __forceinline__ cx<R> mul_w32(cx<R> a) {
     }
 }
 
+// v[n] *= W_P^(q n), n < S, with compile-time exponents (P divides 32)
+template <typename R, bool INV, int Q, int P, int S, int N = 1>
+__device__ __forceinline__ void twist(cx<R>* v) {
+    if constexpr (N < S) {
+        v[N] = mul_w32<R, INV, Q * N * (32 / P)>(v[N]);
+        twist<R, INV, Q, P, S, N + 1>(v);
+    }
+}
+
 // Length 16 = 4 x 4 and 32 = 8 x 4 (Cooley-Tukey, n = 4 n1 + n2,
 // k = k1 + N1 k2): DFTs of length N1 over n1, twiddles W_N^(n2 k1), DFTs of
 // length 4 over n2.  Natural order in and out.
@@ -606,6 +615,8 @@ __device__ __forceinline__ void fft_reg(cx<R>* __restrict__ buf, int lgL, int lg
         stockham_io_pass<R, ODD, INV, EMAX, kSrcLds, DST_LDS, LAYOUT, NC, false, HALF_OUT, NT, TWL, ODD>(
             buf, lgL, lgL, lgT, nseq, none_load, store, noin);
 }
+
+template <int V> struct IntC { static constexpr int value = V; };
 
 // Division of 0 <= n < 2^31 by a divisor fixed at launch: with
 // l = ceil(log2 d) and m = floor(2^(32+l) / d) - 2^32 + 1,

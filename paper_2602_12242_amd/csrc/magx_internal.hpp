@@ -47,6 +47,10 @@ struct Plan {
     // the last block repeats block 0 with row Py/2 in column 0
     int nyqpack;
     long long tn_off;
+    // column convolution (column.hip): X1 in column order, and a copy of the
+    // tensor in column order at element tc_off of the spectrum
+    int col;
+    long long tc_off;
     int pencil_blocks;
     // workspace layout (bytes): the non-finite flag word first, then X1, X2,
     // five fields and the per-block partials
@@ -88,7 +92,11 @@ hipError_t init_tw_conv32(hipStream_t s);
 hipError_t init_tw_conv64(hipStream_t s);
 hipError_t init_tw_pencil32(hipStream_t s);
 hipError_t init_tw_pencil64(hipStream_t s);
+hipError_t init_tw_pencil_cols32(hipStream_t s);
+hipError_t init_tw_pencil_cols64(hipStream_t s);
 hipError_t init_tw_mri(hipStream_t s);
+hipError_t init_tw_column32(hipStream_t s);
+hipError_t init_tw_column64(hipStream_t s);
 hipError_t build_tensor_spectrum(const Plan& pl, void* spectrum, void* scratch, hipStream_t s);
 
 // FFT convolution passes (conv.hip)
@@ -101,6 +109,13 @@ hipError_t launch_yinv(const Plan& pl, const void* X2, void* Y1, hipStream_t s);
 // Films (plan.yzfilm): forward y pass, z pass and inverse y pass in one kernel, X1 -> Y1 in place.
 template <typename R>
 hipError_t launch_yzfilm(const Plan& pl, void* X1, const void* spec, R Ms, hipStream_t s);
+// Column convolution (plan.col): the three passes in one kernel, X1 -> Y1 in place.
+constexpr int kColumnLds = 156 << 10;      // largest column in LDS
+constexpr int column_width(int Py) { return Py >= 160 ? 1 : (Py == 128 ? 2 : 4); }   // columns per block
+template <typename R>
+hipError_t launch_column(const Plan& pl, void* X1, const void* spec, R Ms, hipStream_t s);
+template <typename R>
+hipError_t launch_column_tensor(const Plan& pl, void* spectrum, hipStream_t s);
 // Diagnostic memory patterns over X2 (single precision plans): 0 copy, 1 z tiling, 2 y tiling.
 hipError_t launch_memory_probe(const Plan& pl, int kind, void* X2, hipStream_t s, double* bytes);
 
@@ -147,22 +162,49 @@ struct StartArgs {
     R dt;
 };
 
+// The pencil kernels (pencil.hip, compiled by itself for each order of X1).
+template <typename R, bool COLS>
+hipError_t launch_xfwd_in(const Plan& pl, const R* f, void* X1, const R* msp, hipStream_t s);
 template <typename R>
-hipError_t launch_xfwd(const Plan& pl, const R* f, void* X1, const R* msp, hipStream_t s);
+inline hipError_t launch_xfwd(const Plan& pl, const R* f, void* X1, const R* msp, hipStream_t s) {
+    return pl.col ? launch_xfwd_in<R, true>(pl, f, X1, msp, s) : launch_xfwd_in<R, false>(pl, f, X1, msp, s);
+}
 // mode 0: H = field of f (with bias if with_bias); mode 1: energy partials of f;
 // if sum_input, per-block sums of f are added into partials (for dL/dH_bias).
+template <typename R, bool COLS>
+hipError_t launch_field_in(const Plan& pl, const Phys<R>& ph, const void* Y1, const R* f, R* H, int with_bias,
+                           int energy, int sum_input, double* partials, hipStream_t s);
 template <typename R>
-hipError_t launch_field(const Plan& pl, const Phys<R>& ph, const void* Y1, const R* f, R* H, int with_bias,
-                        int energy, int sum_input, double* partials, hipStream_t s);
+inline hipError_t launch_field(const Plan& pl, const Phys<R>& ph, const void* Y1, const R* f, R* H, int with_bias,
+                               int energy, int sum_input, double* partials, hipStream_t s) {
+    return pl.col ? launch_field_in<R, true>(pl, ph, Y1, f, H, with_bias, energy, sum_input, partials, s)
+                  : launch_field_in<R, false>(pl, ph, Y1, f, H, with_bias, energy, sum_input, partials, s);
+}
+template <typename R, bool COLS>
+hipError_t launch_stage_in(const Plan& pl, const Phys<R>& ph, const void* Y1, void* X1, const StageArgs<R>& a,
+                           hipStream_t s);
 template <typename R>
-hipError_t launch_stage(const Plan& pl, const Phys<R>& ph, const void* Y1, void* X1, const StageArgs<R>& a,
-                        hipStream_t s);
+inline hipError_t launch_stage(const Plan& pl, const Phys<R>& ph, const void* Y1, void* X1, const StageArgs<R>& a,
+                               hipStream_t s) {
+    return pl.col ? launch_stage_in<R, true>(pl, ph, Y1, X1, a, s) : launch_stage_in<R, false>(pl, ph, Y1, X1, a, s);
+}
+template <typename R, bool COLS>
+hipError_t launch_bstage_in(const Plan& pl, const Phys<R>& ph, const void* Y1, void* X1, const BackArgs<R>& a,
+                            double* partials, hipStream_t s);
 template <typename R>
-hipError_t launch_bstage(const Plan& pl, const Phys<R>& ph, const void* Y1, void* X1, const BackArgs<R>& a,
-                         double* partials, hipStream_t s);
+inline hipError_t launch_bstage(const Plan& pl, const Phys<R>& ph, const void* Y1, void* X1, const BackArgs<R>& a,
+                                double* partials, hipStream_t s) {
+    return pl.col ? launch_bstage_in<R, true>(pl, ph, Y1, X1, a, partials, s)
+                  : launch_bstage_in<R, false>(pl, ph, Y1, X1, a, partials, s);
+}
+template <typename R, bool COLS>
+hipError_t launch_bstart_in(const Plan& pl, const Phys<R>& ph, void* X1, const StartArgs<R>& a, double* partials,
+                            hipStream_t s);
 template <typename R>
-hipError_t launch_bstart(const Plan& pl, const Phys<R>& ph, void* X1, const StartArgs<R>& a, double* partials,
-                         hipStream_t s);
+inline hipError_t launch_bstart(const Plan& pl, const Phys<R>& ph, void* X1, const StartArgs<R>& a, double* partials,
+                                hipStream_t s) {
+    return pl.col ? launch_bstart_in<R, true>(pl, ph, X1, a, partials, s) : launch_bstart_in<R, false>(pl, ph, X1, a, partials, s);
+}
 template <typename R>
 hipError_t launch_rhs(const Plan& pl, const Phys<R>& ph, const R* m, const R* H, R* out, hipStream_t s);
 hipError_t launch_fill_zero(double* p, long long n, hipStream_t s);

@@ -21,13 +21,13 @@ namespace magx {
 // Slow stage: inverse x pass of the convolution output + slow local terms +
 // torque; r = wa*Sa + wb*Sb + wn*S (Sa, Sb earlier slow torques or null).
 // V: 0 general, 1 without a magnetisation profile and the non-finite check.
-template <typename R, bool BIG, int LN, int V>
+template <typename R, int ORD, int LN, int V>
 __global__ void __launch_bounds__(kNT) mri_slow_kernel(const cx<R>* __restrict__ Y1, const R* __restrict__ y,
                                                        PG g, Phys<R> ph, int has_demag, R* __restrict__ S_out,
                                                        const R* __restrict__ Sa, const R* __restrict__ Sb, R wa,
                                                        R wb, R wn, R* __restrict__ r_out) {
     pg_fix<LN>(g);
-    const bool stream = stream_of<BIG>(g);
+    const bool stream = stream_of<ORD>(g);
     extern __shared__ unsigned char smem_raw[];
     cx<R>* buf = reinterpret_cast<cx<R>*>(smem_raw);
     const int lb = xcd_logical_block(blockIdx.x, gridDim.x);
@@ -48,7 +48,7 @@ __global__ void __launch_bounds__(kNT) mri_slow_kernel(const cx<R>* __restrict__
 #pragma unroll
     for (int c = 0; c < 3; ++c) hbv[c] = ph.hbm ? ph.hbm[mb * 3 + c] : ph.hb[c];
     const bool vec = (g.nx & 1) == 0;
-    if (has_demag) c2r_lines<R, BIG, LN>(buf, Y1, g, mb, pen0, npen);
+    if (has_demag) c2r_lines<R, ORD, LN>(buf, Y1, g, mb, pen0, npen);
     for (int e = threadIdx.x; e < slots_of<LN>(g, npen); e += kNT) {
         int p, n;
         slot_of<LN>(g, e, p, n);
@@ -103,13 +103,13 @@ __global__ void __launch_bounds__(kNT) mri_slow_kernel(const cx<R>* __restrict__
 
 // One fast stage: F = R(v, H_exch(v)) + r; q <- Ak q + h F (q not read when
 // first); v_out = v + Bk q, renormalised if norm; r2c of v_out into X1 if fwd.
-template <typename R, bool BIG, int LN>
+template <typename R, int ORD, int LN>
 __global__ void __launch_bounds__(kNT) mri_fast_kernel(const R* __restrict__ v, R* __restrict__ vout,
                                                        R* __restrict__ qbuf, const R* __restrict__ rbuf, PG g,
                                                        Phys<R> ph, R Ak, R Bk, R h, int first, int norm, int fwd,
                                                        cx<R>* __restrict__ X1) {
     pg_fix<LN>(g);
-    const bool stream = stream_of<BIG>(g);
+    const bool stream = stream_of<ORD>(g);
     extern __shared__ unsigned char smem_raw[];
     cx<R>* buf = reinterpret_cast<cx<R>*>(smem_raw);
     const int lb = xcd_logical_block(blockIdx.x, gridDim.x);
@@ -125,7 +125,7 @@ __global__ void __launch_bounds__(kNT) mri_fast_kernel(const R* __restrict__ v, 
     // v_out also goes into this thread's LDS line entries for the forward x pass
     // one slot (cell pair) per iteration; kept rolled to keep the kernel small
 #pragma unroll 1
-    for (int i = 0; i < maxslot<BIG>(); ++i) {
+    for (int i = 0; i < maxslot<ORD>(); ++i) {
         const int e = threadIdx.x + i * kNT;
         if (e >= slots_of<LN>(g, npen)) continue;
         int p, n;
@@ -175,7 +175,7 @@ __global__ void __launch_bounds__(kNT) mri_fast_kernel(const R* __restrict__ v, 
         }
     }
     if (!fwd) return;
-    r2c_lines<R, BIG, LN>(buf, X1, g, mb, pen0, npen);
+    r2c_lines<R, ORD, LN>(buf, X1, g, mb, pen0, npen);
 }
 
 // One fast substep, all three stages, on thin grids (nz <= NZM): a block loads a
@@ -286,17 +286,25 @@ __global__ void __launch_bounds__(kSubX* kSubY)
 
 // lines with an odd factor are compile-time lengths, the others runtime ones
 static int odd_line(const Plan& pl) { return odd_part(pl.Lh) > 1 ? pl.Lh : 0; }
-#define MAGX_LINE_LAUNCH(KERNEL, VV, LINE, ...)                                                          \
-    do {                                                                                             \
-        const dim3 grid_((unsigned)pl.pencil_blocks), block_(kNT);                                   \
-        switch (LINE) {                                                                              \
-            MAGX_ODD_LINES(KERNEL, VV, lds, __VA_ARGS__)                                             \
-            default:                                                                                 \
-                if (pencil_big(pl))                                                                  \
-                    hipLaunchKernelGGL((KERNEL<R, true, 0 MAGX_UNWRAP VV>), grid_, block_, lds, s, __VA_ARGS__);    \
-                else                                                                                 \
-                    hipLaunchKernelGGL((KERNEL<R, false, 0 MAGX_UNWRAP VV>), grid_, block_, lds, s, __VA_ARGS__);   \
-        }                                                                                            \
+#define MAGX_LINE_LAUNCH(KERNEL, VV, LINE, ...)                                                                    \
+    do {                                                                                                           \
+        const dim3 grid_((unsigned)pl.pencil_blocks), block_(kNT);                                                 \
+        if (pl.col) {                                                                                              \
+            switch (LINE) {                                                                                        \
+                MAGX_ODD_LINES(kColumns, KERNEL, VV, lds, __VA_ARGS__)                                             \
+                default:                                                                                           \
+                    hipLaunchKernelGGL((KERNEL<R, kColumns, 0 MAGX_UNWRAP VV>), grid_, block_, lds, s, __VA_ARGS__); \
+            }                                                                                                      \
+            break;                                                                                                 \
+        }                                                                                                          \
+        switch (LINE) {                                                                                            \
+            MAGX_ODD_LINES(kRows, KERNEL, VV, lds, __VA_ARGS__)                                                    \
+            default:                                                                                               \
+                if (pencil_big(pl))                                                                                \
+                    hipLaunchKernelGGL((KERNEL<R, kBigRows, 0 MAGX_UNWRAP VV>), grid_, block_, lds, s, __VA_ARGS__); \
+                else                                                                                               \
+                    hipLaunchKernelGGL((KERNEL<R, kRows, 0 MAGX_UNWRAP VV>), grid_, block_, lds, s, __VA_ARGS__);  \
+        }                                                                                                          \
     } while (0)
 
 template <typename R>

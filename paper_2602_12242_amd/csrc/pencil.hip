@@ -27,7 +27,7 @@ namespace magx {
 
 // ---- kernels -------------------------------------------------------------------
 
-template <typename R, bool BIG, int LN>
+template <typename R, int ORD, int LN>
 __global__ void __launch_bounds__(kNT) xfwd_kernel(const R* __restrict__ f, cx<R>* __restrict__ X1, PG g,
                                                    const R* __restrict__ msp) {
     pg_fix<LN>(g);
@@ -45,9 +45,9 @@ __global__ void __launch_bounds__(kNT) xfwd_kernel(const R* __restrict__ f, cx<R
     // every cell pair of this thread is loaded first (one 8-byte load per
     // component when nx is even), so that their latencies overlap; the LDS
     // line entries are written afterwards
-    R va[maxslot<BIG>()][3], vb[maxslot<BIG>()][3], s0[maxslot<BIG>()], s1[maxslot<BIG>()];
+    R va[maxslot<ORD>()][3], vb[maxslot<ORD>()][3], s0[maxslot<ORD>()], s1[maxslot<ORD>()];
 #pragma unroll
-    for (int i = 0; i < maxslot<BIG>(); ++i) {
+    for (int i = 0; i < maxslot<ORD>(); ++i) {
         const int e = threadIdx.x + i * kNT;
         s0[i] = s1[i] = (R)1;
 #pragma unroll
@@ -69,7 +69,7 @@ __global__ void __launch_bounds__(kNT) xfwd_kernel(const R* __restrict__ f, cx<R
         }
     }
 #pragma unroll
-    for (int i = 0; i < maxslot<BIG>(); ++i) {
+    for (int i = 0; i < maxslot<ORD>(); ++i) {
         const int e = threadIdx.x + i * kNT;
         if (e >= nitem) continue;
         int p, n;
@@ -77,7 +77,7 @@ __global__ void __launch_bounds__(kNT) xfwd_kernel(const R* __restrict__ f, cx<R
 #pragma unroll
         for (int c = 0; c < 3; ++c) buf[(3 * p + c) * g.Lh + n] = mk<R>(s0[i] * va[i][c], s1[i] * vb[i][c]);
     }
-    r2c_lines<R, BIG, LN>(buf, X1, g, mb, pen0, npen);
+    r2c_lines<R, ORD, LN>(buf, X1, g, mb, pen0, npen);
 }
 
 // mode: 0 -> write H (with bias if with_bias); 1 -> energy partials (m.H_term).
@@ -87,7 +87,7 @@ __global__ void __launch_bounds__(kNT) xfwd_kernel(const R* __restrict__ f, cx<R
 // V: 0 the general kernel, 1 without a magnetisation profile and the non-finite
 // check (energies, whose densities the plain local field does not split, are general).
 // PRE: the stencil of a thread's single cell pair is loaded before the inverse x pass.
-template <typename R, bool BIG, int LN, bool RED, int V, bool PRE>
+template <typename R, int ORD, int LN, bool RED, int V, bool PRE>
 __device__ __forceinline__ void field_body(const cx<R>* __restrict__ Y1, const R* __restrict__ f,
                                            R* __restrict__ H, PG g, Phys<R> ph, int has_demag,
                                            int with_bias, int energy, int sum_input,
@@ -99,7 +99,7 @@ __device__ __forceinline__ void field_body(const cx<R>* __restrict__ Y1, const R
         ph.nf = nullptr;
     }
     pg_fix<LN>(g);
-    const bool stream = stream_of<BIG>(g);
+    const bool stream = stream_of<ORD>(g);
     extern __shared__ unsigned char smem_raw[];
     cx<R>* buf = reinterpret_cast<cx<R>*>(smem_raw);
     __shared__ double red[kNT];
@@ -125,7 +125,7 @@ __device__ __forceinline__ void field_body(const cx<R>* __restrict__ Y1, const R
             stencil_load<R>(t, f, g, 2 * n, y, z, id * (unsigned)sizeof(R), vec, 2 * n + 1 < g.nx, ph.terms);
         }
     }
-    if (has_demag) c2r_lines<R, BIG, LN>(buf, Y1, g, mb, pen0, npen);
+    if (has_demag) c2r_lines<R, ORD, LN>(buf, Y1, g, mb, pen0, npen);
     double acc[6] = {0, 0, 0, 0, 0, 0};
     for (int e = threadIdx.x; e < slots_of<LN>(g, npen); e += kNT) {
         int p, n;
@@ -195,20 +195,20 @@ __device__ __forceinline__ void field_body(const cx<R>* __restrict__ Y1, const R
     }
 }
 
-template <typename R, bool BIG, int LN, int V, bool PRE>
+template <typename R, int ORD, int LN, int V, bool PRE>
 __global__ void __launch_bounds__(kNT) field_kernel(const cx<R>* __restrict__ Y1, const R* __restrict__ f,
                                                     R* __restrict__ H, PG g, Phys<R> ph, int has_demag,
                                                     int with_bias, int energy, int sum_input,
                                                     double* __restrict__ partials) {
-    field_body<R, BIG, LN, false, V, PRE>(Y1, f, H, g, ph, has_demag, with_bias, energy, sum_input, partials);
+    field_body<R, ORD, LN, false, V, PRE>(Y1, f, H, g, ph, has_demag, with_bias, energy, sum_input, partials);
 }
 
-template <typename R, bool BIG, int LN, int V>
+template <typename R, int ORD, int LN, int V>
 __global__ void __launch_bounds__(kNT) field_reduce_kernel(const cx<R>* __restrict__ Y1, const R* __restrict__ f,
                                                            R* __restrict__ H, PG g, Phys<R> ph, int has_demag,
                                                            int with_bias, int energy, int sum_input,
                                                            double* __restrict__ partials) {
-    field_body<R, BIG, LN, true, V, false>(Y1, f, H, g, ph, has_demag, with_bias, energy, sum_input, partials);
+    field_body<R, ORD, LN, true, V, false>(Y1, f, H, g, ph, has_demag, with_bias, energy, sum_input, partials);
 }
 
 // V: 0 the general kernel (magnetisation profile, non-finite check), 1 without
@@ -217,11 +217,11 @@ __global__ void __launch_bounds__(kNT) field_reduce_kernel(const cx<R>* __restri
 // vector lanes, a lane read each time one is used) and no ghost selects.
 // PRE (a thread's single cell pair on small systems, see ahead()): the
 // stencil and the RK4 registers are loaded before the inverse x pass.
-template <typename R, bool BIG, int LN, int V, bool PRE>
+template <typename R, int ORD, int LN, int V, bool PRE>
 __global__ void __launch_bounds__(kNT) stage_kernel(const cx<R>* Y1, cx<R>* X1, PG g,
                                                     Phys<R> ph, StageArgs<R> a, int has_demag) {
     pg_fix<LN>(g);
-    const bool stream = stream_of<BIG>(g);
+    const bool stream = stream_of<ORD>(g);
     extern __shared__ unsigned char smem_raw[];
     cx<R>* buf = reinterpret_cast<cx<R>*>(smem_raw);
     // logical block -> member mb and its first pencil; members own contiguous block ranges
@@ -268,7 +268,7 @@ __global__ void __launch_bounds__(kNT) stage_kernel(const cx<R>* Y1, cx<R>* X1, 
             }
         }
     }
-    if (has_demag) c2r_lines<R, BIG, LN>(buf, Y1, g, mb, pen0, npen);
+    if (has_demag) c2r_lines<R, ORD, LN>(buf, Y1, g, mb, pen0, npen);
     // classical RK4 tableau
     const R bws = s == 2 || s == 3 ? (R)(1.0 / 3.0) : (R)(1.0 / 6.0);
     const R cdt = (s == 3 ? (R)1 : (R)0.5) * a.dt;
@@ -279,7 +279,7 @@ __global__ void __launch_bounds__(kNT) stage_kernel(const cx<R>* Y1, cx<R>* X1, 
     const bool fwd = a.want_next && has_demag;
     // one slot (cell pair) per iteration; kept rolled to keep the kernel small
 #pragma unroll 1
-    for (int i = 0; i < (PRE ? 1 : maxslot<BIG>()); ++i) {
+    for (int i = 0; i < (PRE ? 1 : maxslot<ORD>()); ++i) {
         const int e = threadIdx.x + i * kNT;
         if (e >= slots_of<LN>(g, npen)) continue;
         int p, n;
@@ -375,14 +375,14 @@ __global__ void __launch_bounds__(kNT) stage_kernel(const cx<R>* Y1, cx<R>* X1, 
         }
     }
     if (!fwd) return;
-    r2c_lines<R, BIG, LN>(buf, X1, g, mb, pen0, npen);
+    r2c_lines<R, ORD, LN>(buf, X1, g, mb, pen0, npen);
 }
 
-template <typename R, bool BIG, int LN>
+template <typename R, int ORD, int LN>
 __global__ void __launch_bounds__(kNT) bstart_kernel(cx<R>* __restrict__ X1, PG g, Phys<R> ph, StartArgs<R> a,
                                                      int has_demag, double* __restrict__ partials) {
     pg_fix<LN>(g);
-    const bool stream = stream_of<BIG>(g);
+    const bool stream = stream_of<ORD>(g);
     extern __shared__ unsigned char smem_raw[];
     cx<R>* buf = reinterpret_cast<cx<R>*>(smem_raw);
     __shared__ double red[kNT];
@@ -407,7 +407,7 @@ __global__ void __launch_bounds__(kNT) bstart_kernel(cx<R>* __restrict__ X1, PG 
     // mu_4 goes straight into this thread's LDS line entries for the forward x pass
     // one slot (cell pair) per iteration; kept rolled to keep the kernel small
 #pragma unroll 1
-    for (int i = 0; i < maxslot<BIG>(); ++i) {
+    for (int i = 0; i < maxslot<ORD>(); ++i) {
         const int e = threadIdx.x + i * kNT;
         if (e >= slots_of<LN>(g, npen)) continue;
         int p, n;
@@ -471,16 +471,16 @@ __global__ void __launch_bounds__(kNT) bstart_kernel(cx<R>* __restrict__ X1, PG 
         }
     }
     if (!has_demag) return;
-    r2c_lines<R, BIG, LN>(buf, X1, g, mb, pen0, npen);
+    r2c_lines<R, ORD, LN>(buf, X1, g, mb, pen0, npen);
 }
 
 // V: 0 with the non-finite check, 1 without (the reverse mode has no profile).
-template <typename R, bool BIG, int LN, int V>
+template <typename R, int ORD, int LN, int V>
 __global__ void __launch_bounds__(kNT) bstage_kernel(const cx<R>* Y1, cx<R>* X1, PG g,
                                                      Phys<R> ph, BackArgs<R> a, int has_demag,
                                                      double* __restrict__ partials) {
     pg_fix<LN>(g);
-    const bool stream = stream_of<BIG>(g);
+    const bool stream = stream_of<ORD>(g);
     extern __shared__ unsigned char smem_raw[];
     cx<R>* buf = reinterpret_cast<cx<R>*>(smem_raw);
     __shared__ double red[kNT];
@@ -501,7 +501,7 @@ __global__ void __launch_bounds__(kNT) bstage_kernel(const cx<R>* Y1, cx<R>* X1,
     if (a.yprev) a.yprev += mo;
     if (a.nxs) a.nxs += mo1;
     const bool vec = (g.nx & 1) == 0;
-    if (has_demag) c2r_lines<R, BIG, LN>(buf, Y1, g, mb, pen0, npen);
+    if (has_demag) c2r_lines<R, ORD, LN>(buf, Y1, g, mb, pen0, npen);
     const int s = a.stage;
     // weights of stage s - 1: b_{s-1} dt and c_s dt
     const R bdt = (s == 2 ? (R)(1.0 / 6.0) : (R)(1.0 / 3.0)) * a.dt;
@@ -514,7 +514,7 @@ __global__ void __launch_bounds__(kNT) bstage_kernel(const cx<R>* Y1, cx<R>* X1,
     const bool fwd = s > 1 && has_demag;
     // one slot (cell pair) per iteration; kept rolled to keep the kernel small
 #pragma unroll 1
-    for (int i = 0; i < maxslot<BIG>(); ++i) {
+    for (int i = 0; i < maxslot<ORD>(); ++i) {
         const int e = threadIdx.x + i * kNT;
         if (e >= slots_of<LN>(g, npen)) continue;
         int p, n;
@@ -620,7 +620,7 @@ __global__ void __launch_bounds__(kNT) bstage_kernel(const cx<R>* Y1, cx<R>* X1,
         }
     }
     if (!fwd) return;
-    r2c_lines<R, BIG, LN>(buf, X1, g, mb, pen0, npen);
+    r2c_lines<R, ORD, LN>(buf, X1, g, mb, pen0, npen);
 }
 
 template <typename R>
@@ -693,23 +693,26 @@ __global__ void copy_kernel(const R* __restrict__ src, R* __restrict__ dst, long
 // ---- launchers -----------------------------------------------------------------
 
 // Pencil kernel launch: the line lengths of pencil_line with compile-time
-// geometry, every other size with runtime geometry.
-#define MAGX_PENCIL_LAUNCH(KERNEL, VV, ...)                                                                \
-    do {                                                                                                   \
-        const dim3 grid_((unsigned)pl.pencil_blocks), block_(kNT);                                         \
-        const size_t lds_ = pencil_lds(pl);                                                                \
-        switch (pencil_line(pl)) {                                                                         \
-            MAGX_ODD_LINES(KERNEL, VV, lds_, __VA_ARGS__)                                                  \
-            MAGX_LINE_CASE(128, KERNEL, VV, lds_, __VA_ARGS__)                                             \
-            MAGX_LINE_CASE(256, KERNEL, VV, lds_, __VA_ARGS__)                                             \
-            MAGX_LINE_CASE(512, KERNEL, VV, lds_, __VA_ARGS__)                                             \
-            MAGX_LINE_CASE(1024, KERNEL, VV, lds_, __VA_ARGS__)                                            \
-            default:                                                                                       \
-                if (pencil_big(pl))                                                                        \
-                    hipLaunchKernelGGL((KERNEL<R, true, 0 MAGX_UNWRAP VV>), grid_, block_, lds_, s, __VA_ARGS__);  \
-                else                                                                                       \
-                    hipLaunchKernelGGL((KERNEL<R, false, 0 MAGX_UNWRAP VV>), grid_, block_, lds_, s, __VA_ARGS__); \
-        }                                                                                                  \
+// geometry, every other size with runtime geometry.  This file is compiled once
+// per element type and order of X1 (MAGX_COLS).
+constexpr int kOrder = MAGX_COLS ? kColumns : kRows;
+#define MAGX_PENCIL_LAUNCH(KERNEL, VV, ...)                                                                        \
+    do {                                                                                                           \
+        const dim3 grid_((unsigned)pl.pencil_blocks), block_(kNT);                                                 \
+        const size_t lds_ = pencil_lds(pl);                                                                        \
+        switch (pencil_line(pl)) {                                                                                 \
+            MAGX_ODD_LINES(kOrder, KERNEL, VV, lds_, __VA_ARGS__)                                                  \
+            MAGX_LINE_CASE(kOrder, 128, KERNEL, VV, lds_, __VA_ARGS__)                                             \
+            MAGX_LINE_CASE(kOrder, 256, KERNEL, VV, lds_, __VA_ARGS__)                                             \
+            MAGX_LINE_CASE(kOrder, 512, KERNEL, VV, lds_, __VA_ARGS__)                                             \
+            MAGX_LINE_CASE(kOrder, 1024, KERNEL, VV, lds_, __VA_ARGS__)                                            \
+            default:                                                                                               \
+                if (kOrder == kRows && pencil_big(pl))                                                             \
+                    hipLaunchKernelGGL((KERNEL<R, kOrder == kRows ? kBigRows : kOrder, 0 MAGX_UNWRAP VV>), grid_,  \
+                                       block_, lds_, s, __VA_ARGS__);                                              \
+                else                                                                                               \
+                    hipLaunchKernelGGL((KERNEL<R, kOrder, 0 MAGX_UNWRAP VV>), grid_, block_, lds_, s, __VA_ARGS__); \
+        }                                                                                                          \
     } while (0)
 
 // Loads ahead of the inverse x pass: at most one cell pair per thread and at most
@@ -723,14 +726,14 @@ __global__ void copy_kernel(const R* __restrict__ src, R* __restrict__ dst, long
 // one 128x128x2 system would gain 2 %.
 static bool ahead(const Plan& pl) { return pl.blocks_per_member <= 64 && pl.np * std::max(1, pl.Lh / 2) <= kNT; }
 
-template <typename R>
-hipError_t launch_xfwd(const Plan& pl, const R* f, void* X1, const R* msp, hipStream_t s) {
+template <typename R, bool COLS>
+hipError_t launch_xfwd_in(const Plan& pl, const R* f, void* X1, const R* msp, hipStream_t s) {
     MAGX_PENCIL_LAUNCH(xfwd_kernel, (), f, static_cast<cx<R>*>(X1), make_pg(pl), msp);
     return hipGetLastError();
 }
 
-template <typename R>
-hipError_t launch_field(const Plan& pl, const Phys<R>& ph, const void* Y1, const R* f, R* H, int with_bias,
+template <typename R, bool COLS>
+hipError_t launch_field_in(const Plan& pl, const Phys<R>& ph, const void* Y1, const R* f, R* H, int with_bias,
                         int energy, int sum_input, double* partials, hipStream_t s) {
     const int has_demag = (ph.terms & MAGX_DEMAG) ? 1 : 0;
     const PG g = make_pg(pl);
@@ -749,8 +752,8 @@ hipError_t launch_field(const Plan& pl, const Phys<R>& ph, const void* Y1, const
     return hipGetLastError();
 }
 
-template <typename R>
-hipError_t launch_stage(const Plan& pl, const Phys<R>& ph, const void* Y1, void* X1, const StageArgs<R>& a,
+template <typename R, bool COLS>
+hipError_t launch_stage_in(const Plan& pl, const Phys<R>& ph, const void* Y1, void* X1, const StageArgs<R>& a,
                         hipStream_t s) {
     const int has_demag = (ph.terms & MAGX_DEMAG) ? 1 : 0;
     const PG g = make_pg(pl);
@@ -763,16 +766,16 @@ hipError_t launch_stage(const Plan& pl, const Phys<R>& ph, const void* Y1, void*
     return hipGetLastError();
 }
 
-template <typename R>
-hipError_t launch_bstart(const Plan& pl, const Phys<R>& ph, void* X1, const StartArgs<R>& a, double* partials,
+template <typename R, bool COLS>
+hipError_t launch_bstart_in(const Plan& pl, const Phys<R>& ph, void* X1, const StartArgs<R>& a, double* partials,
                          hipStream_t s) {
     const int has_demag = (ph.terms & MAGX_DEMAG) ? 1 : 0;
     MAGX_PENCIL_LAUNCH(bstart_kernel, (), static_cast<cx<R>*>(X1), make_pg(pl), ph, a, has_demag, partials);
     return hipGetLastError();
 }
 
-template <typename R>
-hipError_t launch_bstage(const Plan& pl, const Phys<R>& ph, const void* Y1, void* X1, const BackArgs<R>& a,
+template <typename R, bool COLS>
+hipError_t launch_bstage_in(const Plan& pl, const Phys<R>& ph, const void* Y1, void* X1, const BackArgs<R>& a,
                          double* partials, hipStream_t s) {
     const int has_demag = (ph.terms & MAGX_DEMAG) ? 1 : 0;
     const PG g = make_pg(pl);
@@ -791,7 +794,7 @@ hipError_t launch_rhs(const Plan& pl, const Phys<R>& ph, const R* m, const R* H,
     return hipGetLastError();
 }
 
-#if MAGX_REAL == 32
+#if MAGX_REAL == 32 && !MAGX_COLS
 hipError_t launch_fill_zero(double* p, long long n, hipStream_t s) {
     hipLaunchKernelGGL(fill_zero_kernel, dim3((unsigned)((n + kNT - 1) / kNT)), dim3(kNT), 0, s, p, n);
     return hipGetLastError();
@@ -806,7 +809,7 @@ hipError_t launch_reduce_partials(const double* partials, int nbatch, int blocks
     return hipGetLastError();
 }
 
-#if MAGX_REAL == 32
+#if MAGX_REAL == 32 && !MAGX_COLS
 hipError_t launch_energy_finish(const double* partials, int nbatch, int blocks_per_member, double pref,
                                 double vku_cell, double* e_out, hipStream_t s) {
     hipLaunchKernelGGL(energy_finish_kernel, dim3(nbatch), dim3(kNT), 0, s, partials, blocks_per_member, pref,
@@ -822,24 +825,36 @@ hipError_t launch_copy(const R* src, R* dst, long long n, hipStream_t s) {
 }
 
 #define MAGX_INST(R)                                                                                            \
-    template hipError_t launch_xfwd<R>(const Plan&, const R*, void*, const R*, hipStream_t);                               \
-    template hipError_t launch_field<R>(const Plan&, const Phys<R>&, const void*, const R*, R*, int, int, int,   \
+    template hipError_t launch_xfwd_in<R, MAGX_COLS>(const Plan&, const R*, void*, const R*, hipStream_t);                               \
+    template hipError_t launch_field_in<R, MAGX_COLS>(const Plan&, const Phys<R>&, const void*, const R*, R*, int, int, int,   \
                                         double*, hipStream_t);                                                  \
-    template hipError_t launch_stage<R>(const Plan&, const Phys<R>&, const void*, void*, const StageArgs<R>&,   \
+    template hipError_t launch_stage_in<R, MAGX_COLS>(const Plan&, const Phys<R>&, const void*, void*, const StageArgs<R>&,   \
                                         hipStream_t);                                                           \
-    template hipError_t launch_bstart<R>(const Plan&, const Phys<R>&, void*, const StartArgs<R>&, double*,      \
+    template hipError_t launch_bstart_in<R, MAGX_COLS>(const Plan&, const Phys<R>&, void*, const StartArgs<R>&, double*,      \
                                          hipStream_t);                                                          \
-    template hipError_t launch_bstage<R>(const Plan&, const Phys<R>&, const void*, void*, const BackArgs<R>&,   \
-                                         double*, hipStream_t);                                                 \
+    template hipError_t launch_bstage_in<R, MAGX_COLS>(const Plan&, const Phys<R>&, const void*, void*, const BackArgs<R>&,   \
+                                         double*, hipStream_t);
+#define MAGX_INST_COMMON(R)                                                                                     \
     template hipError_t launch_rhs<R>(const Plan&, const Phys<R>&, const R*, const R*, R*, hipStream_t);         \
     template hipError_t launch_reduce_partials<R>(const double*, int, int, int, R*, int, hipStream_t);          \
     template hipError_t launch_copy<R>(const R*, R*, long long, hipStream_t);
 
 #if MAGX_REAL == 32
 MAGX_INST(float)
-MAGX_TW_INIT(init_tw_pencil32)
 #else
 MAGX_INST(double)
+#endif
+#if MAGX_COLS
+#if MAGX_REAL == 32
+MAGX_TW_INIT(init_tw_pencil_cols32)
+#else
+MAGX_TW_INIT(init_tw_pencil_cols64)
+#endif
+#elif MAGX_REAL == 32
+MAGX_INST_COMMON(float)
+MAGX_TW_INIT(init_tw_pencil32)
+#else
+MAGX_INST_COMMON(double)
 MAGX_TW_INIT(init_tw_pencil64)
 #endif
 

@@ -1,0 +1,87 @@
+"""GPU parity of the column convolution (thin grids: y and z passes of a column in one
+kernel, X1 in column order): every power-of-two column length and plane count of its
+instances at the edges of their ranges, against the FP64 oracle; the lengths with an
+odd factor are in test_gpu_lengths.py.  The first grids beyond its rule (three
+kernels) are here as well, and a profile, a batch and the multirate step on it.
+
+Bars as in test_gpu_parity.py: double precision 1e-11, single precision 1e-5 (ten
+times that for the step's reverse mode)."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+pytestmark = pytest.mark.gpu
+
+from oracle import adjoint as oadj  # noqa: E402
+from oracle import field as ofield  # noqa: E402
+from oracle import llg as ollg  # noqa: E402
+from oracle import newell as onewell  # noqa: E402
+from oracle.params import Grid, Params  # noqa: E402
+from workloads import random_unit_field, random_vector_field  # noqa: E402
+
+MAT = dict(Ms=1e6, A=1.6e-11, D=2.5e-3, Ku=8e5, eK=(0.0, 0.6, 0.8), alpha=0.1, Hbias=(1e3, -2e3, 5e3), terms=31)
+D = (2e-9, 2.5e-9, 1.5e-9)
+# Py = 32, 64, 128, 256, 512, 1024 with Pz = 2, 4, 8, 16
+GRIDS = [(33, 9, 2), (9, 16, 4), (20, 17, 3), (32, 32, 2), (16, 33, 4), (17, 64, 2), (40, 65, 1), (40, 128, 3),
+         (18, 129, 4), (65, 250, 1), (12, 257, 2), (9, 500, 4), (24, 100, 5), (13, 128, 8), (11, 129, 8), (70, 200, 6),
+         (8, 16, 4), (9, 100, 9), (9, 60, 5), (300, 12, 2)]
+
+
+def _magx():
+    from paper_2602_12242_amd import magx
+    return magx
+
+
+def _dev(a, dtype):
+    return torch.from_numpy(np.ascontiguousarray(a)).to("cuda", torch.float32 if dtype == 0 else torch.float64)
+
+
+def _err(a, b):
+    a, b = np.asarray(a, dtype=np.float64), np.asarray(b, dtype=np.float64)
+    return np.sqrt(((a - b) ** 2).sum(0)).max() / np.sqrt((b ** 2).sum(0)).max()
+
+
+@pytest.mark.parametrize("n", GRIDS)
+@pytest.mark.parametrize("dtype", [1, 0])
+def test_field_step_and_reverse_match_oracle(n, dtype):
+    magx = _magx()
+    g, p = Grid(*n, *D), Params(**MAT)
+    spec = onewell.spectrum(g)
+    tol = 1e-11 if dtype == 1 else 1e-5
+    ctx, q = magx.Context(n, D, dtype=dtype), magx.make_params(**MAT)
+    m = random_unit_field(n, 801, 2).astype(np.float32)
+    m64 = m.astype(np.float64)
+    assert _err(ctx.heff(_dev(m, dtype), q).cpu().numpy(), ofield.heff(g, p, m64, spec)) <= tol
+    gH = random_vector_field(n, 802).astype(np.float32)
+    gm, _ = ctx.heff_backward(_dev(gH, dtype), q)
+    assert _err(gm.cpu().numpy(), ofield.linear_part(g, p, gH.astype(np.float64), spec)) <= tol
+    dt = 5e-14
+    mg, tape = _dev(m, dtype), ctx.tape(1)
+    ctx.step(mg, q, dt, 1, tape=tape)
+    assert np.abs(mg.cpu().numpy() - ollg.rk4_step(g, p, m64, dt, spec)).max() <= tol
+    ref, refh = oadj.rk4_step_vjp(g, p, m64, dt, gH.astype(np.float64), spec)
+    lam, gh = _dev(gH, dtype), torch.zeros(3, dtype=mg.dtype, device="cuda")
+    ctx.step_backward(tape, 1, q, dt, lam, gh)
+    assert _err(lam.cpu().numpy(), ref) <= 10 * tol
+    assert np.abs(gh.cpu().numpy() - refh).max() <= 10 * tol * np.abs(refh).max()
+
+
+@pytest.mark.parametrize("n", [(33, 20, 3), (24, 70, 2)])
+@pytest.mark.parametrize("dtype", [1, 0])
+def test_batch_equals_members_and_empty_profile_regions(n, dtype):
+    magx = _magx()
+    B = 3
+    q = magx.make_params(**MAT)
+    m = np.stack([random_unit_field(n, 810 + b, 2) for b in range(B)]).astype(np.float32)
+    mb = _dev(m, dtype)
+    magx.Context(n, D, dtype=dtype, nbatch=B).step(mb, q, 5e-14, 2)
+    for b in range(B):
+        one = _dev(m[b], dtype)
+        magx.Context(n, D, dtype=dtype).step(one, q, 5e-14, 2)
+        assert torch.equal(one, mb[b])
+    # a profile of ones is the uniform magnet (the general kernels on column order)
+    ctx, full = magx.Context(n, D, dtype=dtype), _dev(m[0], dtype)
+    ctx.set_ms_profile(_dev(np.ones((n[2], n[1], n[0]), np.float32), dtype))
+    ctx.step(full, q, 5e-14, 2)
+    assert float((full - mb[0]).abs().max()) <= (1e-13 if dtype == 1 else 1e-6)
