@@ -1460,6 +1460,7 @@ hipError_t launch_zconv(const Plan& pl, void* X2, const void* spec, R Ms, hipStr
 }
 
 // ---- films: the y and z passes fused ---------------------------------------------
+// (films the column convolution does not take)
 // With nz = 1 (Pz = 2) the z transform of the single input row is that row
 // for both kz = 0 and 1, and the inverse adds the two products, so the z pass
 // is the product with N(kz = 0) + N(kz = 1).  One block takes T columns of all

@@ -112,19 +112,21 @@ static int pow2_floor(long long v) {
 }
 
 // Whether the column convolution takes the grid: one kernel in place of three where
-// a column fits in LDS and its z line in registers, and the film kernel does not
-// take it already.  Two RK4 steps, us, three kernels / one, single
-// and double precision: 300x300x1 450/188 533/249, 100x25x2 229/137 247/149,
+// a column fits in LDS and its z line in registers.  Two RK4 steps, us, three
+// kernels / one, single and double precision: 300x300x1 450/188 533/249, 100x25x2 229/137 247/149,
 // 512x512x2 683/392 1001/603, 640x160x4 479/398 769/614, 500x500x4 849/694 (double
 // precision does not fit).  Five to eight planes hold 222 registers in single
 // precision, two waves per SIMD: faster where a block has 256 or 512 rows
 // (256x256x8 433/389, 250x250x6 474/384, 500x250x8 811/682, 200x100x5 301/273),
 // slower at other lengths (301x187x8 567/658, 190x75x8 279/297, 100x14x8 235/257).
+// Films against the film kernel, whose tile of 8 to 16 columns is one block:
+// 128x32x1 116/110 124/116, 64 of them 326/242 478/382, 128x128x1 141/120,
+// 512x128x1 225/153, 1000x64x1 265/202 265/234, 40x14x1 127/119 135/122.
 // More than 512 rows leave fewer registers per thread; lines of more than 1024
 // values have no pencil kernels in this order.
 static int column_plan(const Plan& p) {
     const bool f32 = p.esize == 4;
-    if (p.yzfilm || p.Py < 32 || p.Py > 1024 || p.Lh < 16 || p.Lh % 4 != 0 || p.Lh > 1024) return 0;
+    if (p.Py < 32 || p.Py > 1024 || p.Lh < 16 || p.Lh % 4 != 0 || p.Lh > 1024) return 0;
     const int maxPz = f32 ? (p.Py == 256 || p.Py == 512 ? 16 : 8) : (p.Py <= 768 ? 8 : 4);
     if (p.Pz > maxPz || 12LL * p.ny * p.nz >= (1LL << 24)) return 0;   // (24-bit stride of kx in the x passes)
     return (long long)((3 * p.nz * column_width(p.Py)) | 1) * p.Py * 2 * p.esize <= kColumnLds ? 1 : 0;
@@ -164,8 +166,8 @@ int make_plan(const magx_grid* g, magx_dtype dt, int nbatch, Plan* pl) {
             return MAGX_ESIZE;
     }
     p.Px = extended_length(p.nx, p.ncell, 1536);
-    // films whose power-of-two tile keeps the fused y and z kernel stay there
-    if (p.nz > 1 || 3LL * p.Py * 8 * 2 * p.esize > 65536) p.Py = extended_length(p.ny, p.ncell, 768);
+    // (films of more than 1024 cells along x: the film kernel's lengths are powers of two)
+    if (p.nz > 1 || p.nx <= 1024) p.Py = extended_length(p.ny, p.ncell, 768);
     p.lgPx = ilog2(p.Px / odd_part(p.Px)); p.lgPy = ilog2(p.Py / odd_part(p.Py)); p.lgPz = ilog2(p.Pz);
     p.Lh = p.Px / 2; p.lgLh = p.lgPx - 1;
     p.Hx = p.Lh + 1; p.Hy = p.Py / 2 + 1; p.Hz = p.Pz / 2 + 1;
@@ -205,11 +207,13 @@ int make_plan(const magx_grid* g, magx_dtype dt, int nbatch, Plan* pl) {
         p.ntz = (p.Hx + tz - 1) / tz;
         if ((long long)p.Hy * p.ntz * 6 * p.Hz * tz >= (1LL << 31)) return MAGX_ESIZE;
     }
-    // films: y and z passes fused when a tile of 3 Py ty values with ty >= 8
+    p.col = column_plan(p);
+    // other films (at most 8 rows, at most 8 cells along x or more than 1024):
+    // y and z passes fused when a tile of 3 Py ty values with ty >= 8
     // columns (8 ... 16, whole 64- to 128-byte row segments) fits in 64 KiB;
     // on small films the tiles narrow (down to 4 columns) until there are 64
     // of them, since there the kernel's latency, not its traffic, counts
-    if (p.nz == 1 && odd_part(p.Py) == 1) {
+    if (p.nz == 1 && !p.col && odd_part(p.Py) == 1) {
         int t = 16;
         while (t >= 8 && 3LL * p.Py * t * 2 * p.esize > 65536) t >>= 1;
         if (t >= 8) {
@@ -259,7 +263,6 @@ int make_plan(const magx_grid* g, magx_dtype dt, int nbatch, Plan* pl) {
     p.tn_off = (long long)p.Hy * p.ntz * 6 * p.Hz * p.tz;
     const long long tn_blocks = p.nyqpack ? (p.Py / 2 + p.tz - 1) / p.tz + 1 : 0;
     p.tc_off = p.tn_off + tn_blocks * 6 * p.Hz * p.tz;
-    p.col = column_plan(p);
     p.spectrum_bytes = (size_t)(p.tc_off + (p.col ? 6LL * p.Hx * p.Hy * p.Hz : 0)) * es;
     const long long a1 = 6 * p.ncell, a2 = 6LL * p.Hy * p.Hx * p.nz;
     p.scratch_a_elems = std::max(a1, a2);

@@ -25,7 +25,9 @@ D = (2e-9, 2.5e-9, 1.5e-9)
 # Py = 32, 64, 128, 256, 512, 1024 with Pz = 2, 4, 8, 16
 GRIDS = [(33, 9, 2), (9, 16, 4), (20, 17, 3), (32, 32, 2), (16, 33, 4), (17, 64, 2), (40, 65, 1), (40, 128, 3),
          (18, 129, 4), (65, 250, 1), (12, 257, 2), (9, 500, 4), (24, 100, 5), (13, 128, 8), (11, 129, 8), (70, 200, 6),
-         (8, 16, 4), (9, 100, 9), (9, 60, 5), (300, 12, 2)]
+         (8, 16, 4), (9, 100, 9), (9, 60, 5), (300, 12, 2),
+         # films: the first ones of the column convolution and the last ones of the film kernel
+         (9, 9, 1), (40, 9, 1), (9, 40, 1), (500, 20, 1), (300, 250, 1), (40, 8, 1), (8, 40, 1)]
 
 
 def _magx():
