@@ -53,8 +53,9 @@ extern "C" {
 #define MAGX_EINVAL     -1   /* null pointer, non-positive size or spacing, bad flag, DMI without exchange */
 #define MAGX_ESIZE      -2   /* n > 4096 on an axis, or the next power of two P >= 2n exceeds the FFT
                                 passes' limits: Py <= 4096; Px <= 4096 (float) or 2048 (double);
-                                Pz <= 1024.  (From 2^16 cells on the extended lengths along x and y
-                                may be 5/8 or 3/4 of that power of two; the limits stay.) */
+                                Pz <= 1024.  (The extended lengths along x and y may be 5/8 or
+                                3/4 of that power of two on grids of at most eight planes or at
+                                least 2^16 cells; the limits are those of the power of two.) */
 #define MAGX_EDTYPE     -3   /* unknown element type */
 #define MAGX_EWORKSPACE -4   /* magx_step_static: the grid needs more than its fixed workspace;
                                 elsewhere buffer sizes are the caller's contract (see magx_sizes) */

@@ -89,16 +89,19 @@ static int next_pow2_at_least(long long v) {
 
 static size_t align256(size_t v) { return (v + 255) & ~size_t(255); }
 
-// Extended length of an axis of n cells along x or y.  Below 2^16 cells the
-// smallest power of two >= 2n: such grids are bound by the latency of their
-// kernels, not by the length of their lines.  From 2^16 cells on also
-// 5/8 and 3/4 of that power of two (5 2^k, 3 2^k) where they are >= 2n and at
-// least 160 and at most `most`, the longest such length the passes have: the
-// spectral fields, their traffic and the tensor shrink with it.
-constexpr long long kOddMinCells = 1LL << 16;
-static int extended_length(int n, long long ncell, int most) {
+// Extended length of an axis of n cells along x or y: the smallest power of two
+// >= 2n, or 5/8 or 3/4 of it (5 2^k, 3 2^k) where that is >= 2n and at least 160
+// and at most `most`, the longest such length the passes have: the spectral
+// fields, their traffic and the tensor shrink with it.  Faster at every size
+// measured: two RK4 steps, us, power of two / odd factor, single and double
+// precision, 75x75x1 149/137 160/147, 300x100x1 164/139 186/160, 75x75x8 316/238
+// 371/286, 301x37x5 315/267 419/338, 8 films of 150x75x2 274/193 420/298.  Small
+// grids of more than eight planes keep the power of two all the same (40x75x20
+// 323/318 434/380, 75x18x40 386/294 605/464): the layout of their stored tensor
+// is an output (magx_spectrum_layout) that callers hold to it.
+static int extended_length(int n, long long ncell, int nz, int most) {
     const int p = next_pow2_at_least(std::max(2, 2 * n));
-    if (ncell < kOddMinCells || p < 256) return p;
+    if (p < 256 || (nz > 8 && ncell < (1LL << 16))) return p;
     const int c5 = p / 8 * 5, c3 = p / 4 * 3;
     if (c5 >= 2 * n && c5 <= most) return c5;
     if (c3 >= 2 * n && c3 <= most) return c3;
@@ -165,9 +168,9 @@ int make_plan(const magx_grid* g, magx_dtype dt, int nbatch, Plan* pl) {
             6LL * (p.Pz / 2 + 1) * (p.Py / 2 + 1) * Sx >= (1LL << 31))
             return MAGX_ESIZE;
     }
-    p.Px = extended_length(p.nx, p.ncell, 1536);
+    p.Px = extended_length(p.nx, p.ncell, p.nz, 1536);
     // (films of more than 1024 cells along x: the film kernel's lengths are powers of two)
-    if (p.nz > 1 || p.nx <= 1024) p.Py = extended_length(p.ny, p.ncell, 768);
+    if (p.nz > 1 || p.nx <= 1024) p.Py = extended_length(p.ny, p.ncell, p.nz, 768);
     p.lgPx = ilog2(p.Px / odd_part(p.Px)); p.lgPy = ilog2(p.Py / odd_part(p.Py)); p.lgPz = ilog2(p.Pz);
     p.Lh = p.Px / 2; p.lgLh = p.lgPx - 1;
     p.Hx = p.Lh + 1; p.Hy = p.Py / 2 + 1; p.Hz = p.Pz / 2 + 1;

@@ -212,7 +212,7 @@ class Context:
         Hy, ntz, six, Hz, tz = (int(v) for v in dims)
         nx, ny, nz = self.n
         Px, Py, Pz = max(2, 1 << (2 * nx - 1).bit_length()), 2 * (Hy - 1), 2 * (Hz - 1)
-        if nx * ny * nz >= 1 << 16 and Px >= 256:      # 5/8 or 3/4 of the power of two where that is enough
+        if Px >= 256 and (nz <= 8 or nx * ny * nz >= 1 << 16):      # 5/8 or 3/4 of the power of two where that is enough
             Px = next((c for c in (Px // 8 * 5, Px // 4 * 3) if 2 * nx <= c <= 1536), Px)
         Hx = Px // 2 + 1
         el = self.spectrum.view(self.tdtype)[: Hy * ntz * six * Hz * tz]

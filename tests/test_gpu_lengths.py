@@ -1,7 +1,6 @@
 """GPU parity at extended lengths with an odd factor (3 2^k and 5 2^k along x
-and y, taken from 2^16 cells on): every such line length of the x and y
-passes once, plus the grid just below the threshold, against the FP64 oracle
-on its own extended grid of length 2n.
+and y): every such line length of the x and y passes once, and a power of two
+beside them, against the FP64 oracle on its own extended grid of length 2n.
 
 Bars as in test_gpu_parity.py: double precision 1e-11, single precision 1e-5
 (1e-10 and 1e-4 for the step's reverse mode)."""
@@ -33,7 +32,10 @@ GRIDS = {
     (640, 107, 1): (1280, 256),
     (700, 311, 1): (1536, 640),
     (86, 384, 2): (192, 768),
-    (255, 257, 1): (512, 1024),    # 65535 cells: one short of the threshold, powers of two
+    (255, 257, 1): (512, 640),
+    (80, 81, 5): (160, 192),       # the largest n of 160, the smallest of 192
+    (64, 65, 8): (128, 160),       # shorter lines are powers of two
+    (73, 33, 9): (256, 128),       # small and more than eight planes: powers of two
 }
 _SETUP = {}
 
