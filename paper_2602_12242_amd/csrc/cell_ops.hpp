@@ -610,10 +610,12 @@ __device__ __forceinline__ void pen_coords(const PG& g, int pen, int& y, int& z)
 // for np Lh <= 1024).
 constexpr int kXIt = 6;
 
-// Offset of kx in a row of X1/Y1.
+// Offset of kx in a row of X1/Y1 (signed: the row order's Lh - t then splits into
+// an immediate offset and the thread's address; as an unsigned number it cost the
+// 512x512x32 stage 211 -> 216 us and the double-precision field kernel 186 -> 216).
 template <int ORD>
-__device__ __forceinline__ unsigned col_off(const PG& g, int kx) {
-    return ORD == kColumns ? umul24((unsigned)kx >> 2, (unsigned)g.ks) + ((unsigned)kx & 3u) : (unsigned)kx;
+__device__ __forceinline__ int col_off(const PG& g, int kx) {
+    return ORD == kColumns ? (int)(umul24((unsigned)kx >> 2, (unsigned)g.ks) + ((unsigned)kx & 3u)) : kx;
 }
 
 // Row of X1/Y1 holding component c of pencil p (32-bit element offset: the
