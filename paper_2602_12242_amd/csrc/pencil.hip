@@ -212,7 +212,8 @@ __global__ void __launch_bounds__(kNT) field_reduce_kernel(const cx<R>* __restri
 }
 
 // V: 0 the general kernel (magnetisation profile, non-finite check), 1 without
-// either and without a tape, 2 the same with a tape.  The plain kernels carry
+// either and without a tape, 2 the same with a tape, 3 with a profile but without
+// the check and a tape (4 steps of a 251x251x10 disc 1484 -> 1466 us).  The plain kernels carry
 // fewer uniform values (the general one spills about 60 scalar registers to
 // vector lanes, a lane read each time one is used) and no ghost selects.
 // PRE (a thread's single cell pair on small systems, see ahead()): the
@@ -235,7 +236,7 @@ __global__ void __launch_bounds__(kNT) stage_kernel(const cx<R>* Y1, cx<R>* X1, 
     a.mn += mo;
     a.acc += mo;
     a.yout += mo;
-    if constexpr (V == 1) {
+    if constexpr (V == 1 || V == 3) {
         a.yout2 = a.tapeH = a.tapeYin = a.tapeNx = nullptr;
     } else {
         if (a.yout2) a.yout2 += mo;
@@ -243,10 +244,8 @@ __global__ void __launch_bounds__(kNT) stage_kernel(const cx<R>* Y1, cx<R>* X1, 
         if (a.tapeYin) a.tapeYin += mo;
         if (a.tapeNx) a.tapeNx += mo1;
     }
-    if constexpr (V > 0) {
-        ph.msp = nullptr;
-        ph.nf = nullptr;
-    }
+    if constexpr (V > 0) ph.nf = nullptr;
+    if constexpr (V == 1 || V == 2) ph.msp = nullptr;
     R hbv[3];
 #pragma unroll
     for (int c = 0; c < 3; ++c) hbv[c] = ph.hbm ? ph.hbm[mb * 3 + c] : ph.hb[c];
@@ -304,7 +303,7 @@ __global__ void __launch_bounds__(kNT) stage_kernel(const cx<R>* Y1, cx<R>* X1, 
             load_pair32(a.acc, g.N, off, vec, two, acc[0], acc[1], stream);
         }
         R ys[2][3], H[2][3], sw[2] = {(R)1, (R)1};
-        if constexpr (V > 0) {
+        if constexpr (V == 1 || V == 2) {
             local_field_plain<R, PRE>(t, a.yin, g, x0, y, z, off, vec, two, ph, H);
 #pragma unroll
             for (int q = 0; q < 2; ++q)
@@ -759,7 +758,8 @@ hipError_t launch_stage_in(const Plan& pl, const Phys<R>& ph, const void* Y1, vo
     const PG g = make_pg(pl);
     const cx<R>* y = static_cast<const cx<R>*>(Y1);
     cx<R>* x = static_cast<cx<R>*>(X1);
-    if (ph.msp || ph.nf) MAGX_PENCIL_LAUNCH(stage_kernel, (, 0, false), y, x, g, ph, a, has_demag);
+    if (ph.msp && !ph.nf && !a.tapeH) MAGX_PENCIL_LAUNCH(stage_kernel, (, 3, false), y, x, g, ph, a, has_demag);
+    else if (ph.msp || ph.nf) MAGX_PENCIL_LAUNCH(stage_kernel, (, 0, false), y, x, g, ph, a, has_demag);
     else if (a.tapeH) MAGX_PENCIL_LAUNCH(stage_kernel, (, 2, false), y, x, g, ph, a, has_demag);
     else if (ahead(pl)) MAGX_PENCIL_LAUNCH(stage_kernel, (, 1, true), y, x, g, ph, a, has_demag);
     else MAGX_PENCIL_LAUNCH(stage_kernel, (, 1, false), y, x, g, ph, a, has_demag);
