@@ -269,27 +269,31 @@ static hipError_t run_column(const Plan& pl, void* X1, const void* spec, R Ms, h
 
 template <typename R, int PZ>
 static hipError_t run_column_py(const Plan& pl, void* X1, const void* spec, R Ms, hipStream_t s) {
-    switch (pl.Py) {
-        case 32: return run_column<R, 32, PZ>(pl, X1, spec, Ms, s);
-        case 64: return run_column<R, 64, PZ>(pl, X1, spec, Ms, s);
-        case 128: return run_column<R, 128, PZ>(pl, X1, spec, Ms, s);
-        case 160: return run_column<R, 160, PZ>(pl, X1, spec, Ms, s);
-        case 192: return run_column<R, 192, PZ>(pl, X1, spec, Ms, s);
-        case 256: return run_column<R, 256, PZ>(pl, X1, spec, Ms, s);
-        case 320: return run_column<R, 320, PZ>(pl, X1, spec, Ms, s);
-        case 384: return run_column<R, 384, PZ>(pl, X1, spec, Ms, s);
-        case 512: return run_column<R, 512, PZ>(pl, X1, spec, Ms, s);
-        default: break;
-    }
-    // longer columns: more than 512 threads leave 128 (1024) or 168 registers
-    if constexpr (PZ <= 8) {
+    if constexpr (PZ == 16) {   // the lengths it is the faster path at
+        if (pl.Py == 256) return run_column<R, 256, PZ>(pl, X1, spec, Ms, s);
+        if (pl.Py == 512) return run_column<R, 512, PZ>(pl, X1, spec, Ms, s);
+        return hipErrorInvalidValue;
+    } else {
+        switch (pl.Py) {
+            case 32: return run_column<R, 32, PZ>(pl, X1, spec, Ms, s);
+            case 64: return run_column<R, 64, PZ>(pl, X1, spec, Ms, s);
+            case 128: return run_column<R, 128, PZ>(pl, X1, spec, Ms, s);
+            case 160: return run_column<R, 160, PZ>(pl, X1, spec, Ms, s);
+            case 192: return run_column<R, 192, PZ>(pl, X1, spec, Ms, s);
+            case 256: return run_column<R, 256, PZ>(pl, X1, spec, Ms, s);
+            case 320: return run_column<R, 320, PZ>(pl, X1, spec, Ms, s);
+            case 384: return run_column<R, 384, PZ>(pl, X1, spec, Ms, s);
+            case 512: return run_column<R, 512, PZ>(pl, X1, spec, Ms, s);
+            default: break;
+        }
+        // longer columns: more than 512 threads leave 128 (1024) or 168 registers
         if (pl.Py == 640) return run_column<R, 640, PZ>(pl, X1, spec, Ms, s);
         if (pl.Py == 768) return run_column<R, 768, PZ>(pl, X1, spec, Ms, s);
+        if constexpr (PZ <= (sizeof(R) == 4 ? 8 : 4)) {
+            if (pl.Py == 1024) return run_column<R, 1024, PZ>(pl, X1, spec, Ms, s);
+        }
+        return hipErrorInvalidValue;
     }
-    if constexpr (PZ <= (sizeof(R) == 4 ? 8 : 4)) {
-        if (pl.Py == 1024) return run_column<R, 1024, PZ>(pl, X1, spec, Ms, s);
-    }
-    return hipErrorInvalidValue;
 }
 
 template <typename R>
