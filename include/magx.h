@@ -90,12 +90,13 @@ typedef struct {
  *   renorm 0: never renormalise; 1: renormalise the new state only;
  *          2: renormalise every RK stage input and the new state (default)
  *   check_finite  0 or 1.  With 1, the call clears a flag word at the start of
- *          its workspace and every kernel that writes a field, a state or a
- *          gradient sets it when one of its outputs is NaN or infinite
- *          (renormalisation keeps |m| = 1, so a non-finite value means the
- *          step size or the input was unusable); magx_status reads it.  The
- *          computation itself is unchanged.  magx_llg_rhs (no workspace)
- *          ignores the flag. */
+ *          its workspace and sets it when an output is NaN or infinite: a
+ *          field, an energy, or the state or gradient that the call advances
+ *          (every stage adds to a cell's own value, so what a stage makes
+ *          non-finite still is at the end of the call; renormalisation keeps
+ *          |m| = 1, so it means the step size or the input was unusable).
+ *          magx_status reads it.  The computation itself is unchanged, bit
+ *          for bit.  magx_llg_rhs (no workspace) ignores the flag. */
 typedef struct {
     double Ms, A, D, Ku;
     double eK[3];
@@ -281,8 +282,8 @@ int magx_energy(magx_ctx* ctx, const void* m, const magx_params* p, void* e_out,
                 void* ws, void* stream);
 
 /* Outcome of the last call on ctx made with check_finite = 1: waits for the
- * stream of that call, then returns MAGX_ENONFINITE if one of its kernels met
- * a NaN or infinite output, MAGX_OK if none did (or if no call on ctx has
+ * stream of that call, then returns MAGX_ENONFINITE if one of its outputs was
+ * NaN or infinite, MAGX_OK if none was (or if no call on ctx has
  * asked for the check yet), MAGX_EHIP if the wait or the read failed, and
  * MAGX_EINVAL for a NULL ctx.  The workspace of that call must still be
  * allocated.  A checked call clears the flag at its start, so the outcome

@@ -399,10 +399,14 @@ static void* static_ws(int dev) {
 }
 
 // Non-finite check of a call made with check_finite = 1: the flag word at the
-// start of its workspace is cleared on the call's stream (by a kernel) and
-// handed to the kernels, which set it on a NaN or infinite output; magx_status
-// reads the flag of the last such call.  Inside a compound call (chk_hold) the
-// flag armed at its start is kept.
+// start of its workspace is cleared on the call's stream (by a kernel) and set on
+// a NaN or infinite output; magx_status reads the flag of the last such call.
+// Inside a compound call (chk_hold) the flag armed at its start is kept.  A call
+// that writes a field or energies hands the flag to its field kernel.  One that
+// advances a state or a gradient looks at its result once, after its last kernel:
+// within the call every update adds to the cell's own value, so a value that was
+// NaN or infinite at any stage is not finite at the end.  Either way the kernels
+// are those of an unchecked call.
 template <typename R>
 static int arm_finite_check(magx_ctx* c, const magx_params* p, void* ws, hipStream_t s, Phys<R>& ph) {
     ph.nf = nullptr;
@@ -415,6 +419,13 @@ static int arm_finite_check(magx_ctx* c, const magx_params* p, void* ws, hipStre
     }
     ph.nf = flag;
     return MAGX_OK;
+}
+
+// The check of a call that advanced f (a state or a gradient).
+template <typename R>
+static int check_result(const magx_ctx* c, const R* f, const Phys<R>& ph, hipStream_t s) {
+    if (!ph.nf) return MAGX_OK;
+    return launch_check_finite<R>(f, 3 * c->pl.ncell * c->pl.nbatch, ph.nf, s) == hipSuccess ? MAGX_OK : MAGX_EHIP;
 }
 
 // Arms the check once for a compound call and holds it until destruction.
@@ -548,13 +559,12 @@ static int do_step(magx_ctx* c, R* m, const magx_params* p, double dt, int nstep
             a.dt = (R)dt;
             a.want_next = !(n == nsteps - 1 && st == 4);
             ProfScope ps(c, kProfStage, s);
-            Phys<R> phs = timed ? phys_at<R>(c, p, c->time + (n + kC[st - 1]) * dt) : ph;
-            phs.nf = ph.nf;
+            const Phys<R> phs = timed ? phys_at<R>(c, p, c->time + (n + kC[st - 1]) * dt) : ph;
             if (launch_stage<R>(pl, phs, X1, X1, a, s) != hipSuccess) return MAGX_EHIP;
         }
     }
     if (timed) c->time += nsteps * dt;
-    return MAGX_OK;
+    return check_result<R>(c, m, ph, s);
 }
 
 // ---- HIP graph replay of RK4 steps on small grids ------------------------------
@@ -673,15 +683,14 @@ static int do_step_euler(magx_ctx* c, R* m, const magx_params* p, double dt, int
         a.stage = 0;
         a.dt = (R)dt;
         a.want_next = n < nsteps - 1;
-        Phys<R> ph = phys_at<R>(c, p, c->time + n * dt);
-        ph.nf = ph0.nf;
+        const Phys<R> ph = phys_at<R>(c, p, c->time + n * dt);
         ProfScope ps(c, kProfStage, s);
         if (launch_stage<R>(pl, ph, X1, X1, a, s) != hipSuccess) return MAGX_EHIP;
         std::swap(cur, oth);
     }
     if (cur != m && launch_copy<R>(cur, m, 3 * pl.ncell * pl.nbatch, s) != hipSuccess) return MAGX_EHIP;
     if (timed) c->time += nsteps * dt;
-    return MAGX_OK;
+    return check_result<R>(c, m, ph0, s);
 }
 
 template <typename R>
@@ -741,7 +750,7 @@ static int do_step_backward(magx_ctx* c, const R* tape, int nsteps, const magx_p
             hipSuccess)
             return MAGX_EHIP;
     }
-    return MAGX_OK;
+    return check_result<R>(c, gm, ph, s);
 }
 
 template <typename R>
@@ -840,14 +849,13 @@ static int do_step_mri(magx_ctx* c, R* m, const magx_params* p, double dt, doubl
             if (timed) {
                 pslow_t = phys_at<R>(c, p, c->time + (n + kw.c[i]) * dt);
                 pslow_t.terms = ph.terms & ~MAGX_EXCH;
-                pslow_t.nf = ph.nf;
             }
             if (launch_mri_slow<R>(pl, pslow_t, X1, cur, demag ? 1 : 0, Sout, Sa, Sb, (R)kw.w[i][0],
                                    (R)kw.w[i][1], (R)kw.w[i][i], rf, s) != hipSuccess)
                 return MAGX_EHIP;
             // thin grids: a substep is one kernel; the forward x pass of the next
             // slow evaluation is then a kernel of its own
-            const bool whole = pl.nz <= mri_substep_planes<R>() && !pfast.msp && !pfast.nf;
+            const bool whole = pl.nz <= mri_substep_planes<R>() && !pfast.msp;
             for (long long sub = 0; whole && sub < nsub[i]; ++sub) {
                 const bool last = sub == nsub[i] - 1;
                 const int norm = last && (p->renorm == 2 || (i == 2 && p->renorm >= 1)) ? 1 : 0;
@@ -874,7 +882,7 @@ static int do_step_mri(magx_ctx* c, R* m, const magx_params* p, double dt, doubl
     }
     if (cur != m && launch_copy<R>(cur, m, 3 * pl.ncell * pl.nbatch, s) != hipSuccess) return MAGX_EHIP;
     if (timed) c->time += nsteps * dt;
-    return MAGX_OK;
+    return check_result<R>(c, m, ph, s);
 }
 
 }  // namespace magx

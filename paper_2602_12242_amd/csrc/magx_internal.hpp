@@ -82,8 +82,8 @@ struct Phys {
     R dx, dy;             // ghost offsets
     unsigned terms;
     int renorm;
-    unsigned* nf;         // non-finite flag (device word, set to 1 by any wave that meets a
-                          // non-finite output), or null when the call does not check
+    unsigned* nf;         // field kernels: non-finite flag (device word, set to 1 by any wave that
+                          // meets a non-finite output), or null when the call does not check
 };
 
 // twiddle tables of the translation units
@@ -216,6 +216,9 @@ hipError_t launch_reduce_partials(const double* partials, int nbatch, int blocks
 // vku_cell = V Ku per magnetic cell; their count is partial 5 of every block.
 hipError_t launch_energy_finish(const double* partials, int nbatch, int blocks_per_member, double pref,
                                 double vku_cell, double* e_out, hipStream_t s);
+// Sets *flag if one of the n values is NaN or infinite.
+template <typename R>
+hipError_t launch_check_finite(const R* f, long long n, unsigned* flag, hipStream_t s);
 template <typename R>
 hipError_t launch_copy(const R* src, R* dst, long long n, hipStream_t s);
 

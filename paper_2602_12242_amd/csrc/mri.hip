@@ -20,7 +20,7 @@ namespace magx {
 
 // Slow stage: inverse x pass of the convolution output + slow local terms +
 // torque; r = wa*Sa + wb*Sb + wn*S (Sa, Sb earlier slow torques or null).
-// V: 0 general, 1 without a magnetisation profile and the non-finite check.
+// V: 0 with a magnetisation profile, 1 without.
 template <typename R, int ORD, int LN, int V>
 __global__ void __launch_bounds__(kNT) mri_slow_kernel(const cx<R>* __restrict__ Y1, const R* __restrict__ y,
                                                        PG g, Phys<R> ph, int has_demag, R* __restrict__ S_out,
@@ -40,10 +40,7 @@ __global__ void __launch_bounds__(kNT) mri_slow_kernel(const cx<R>* __restrict__
     if (S_out) S_out += mo;
     if (Sa) Sa += mo;
     if (Sb) Sb += mo;
-    if constexpr (V > 0) {
-        ph.msp = nullptr;
-        ph.nf = nullptr;
-    }
+    if constexpr (V > 0) ph.msp = nullptr;
     R hbv[3];
 #pragma unroll
     for (int c = 0; c < 3; ++c) hbv[c] = ph.hbm ? ph.hbm[mb * 3 + c] : ph.hb[c];
@@ -95,7 +92,6 @@ __global__ void __launch_bounds__(kNT) mri_slow_kernel(const cx<R>* __restrict__
 #pragma unroll
             for (int c = 0; c < 3; ++c) { r[0][c] += wb * b0[c]; r[1][c] += wb * b1[c]; }
         }
-        if (ph.nf) note_nonfinite(ph.nf, any_nonfinite<R, 3>(r[0]) || (two && any_nonfinite<R, 3>(r[1])));
         if (S_out) store_pair(S_out, g.N, id, vec, two, S[0], S[1], stream);
         store_pair(r_out, g.N, id, vec, two, r[0], r[1], stream);
     }
@@ -164,7 +160,6 @@ __global__ void __launch_bounds__(kNT) mri_fast_kernel(const R* __restrict__ v, 
                 }
             }
         }
-        if (ph.nf) note_nonfinite(ph.nf, any_nonfinite<R, 3>(xn[0]) || (two && any_nonfinite<R, 3>(xn[1])));
         store_pair(qbuf, g.N, id, vec, two, q[0], q[1], stream);
         store_pair(vout, g.N, id, vec, two, xn[0], xn[1], stream);
         if (fwd) {
@@ -313,7 +308,7 @@ hipError_t launch_mri_slow(const Plan& pl, const Phys<R>& ph, const void* Y1, co
     const PG g = make_pg(pl);
     const size_t lds = has_demag ? pencil_lds(pl) : 0;
     const cx<R>* Y = static_cast<const cx<R>*>(Y1);
-    if (ph.msp || ph.nf)
+    if (ph.msp)
         MAGX_LINE_LAUNCH(mri_slow_kernel, (, 0), odd_line(pl), Y, y, g, ph, has_demag, S_out, Sa, Sb, wa, wb, wn, r_out);
     else
         MAGX_LINE_LAUNCH(mri_slow_kernel, (, 1), odd_line(pl), Y, y, g, ph, has_demag, S_out, Sa, Sb, wa, wb, wn, r_out);
@@ -331,12 +326,11 @@ hipError_t launch_mri_fast(const Plan& pl, const Phys<R>& ph, const R* v, R* vou
 }
 
 // One substep of three stages (A[0] = 0): grids of at most mri_substep_planes
-// planes without a profile and the non-finite check; hipErrorNotSupported
-// otherwise.
+// planes without a profile; hipErrorNotSupported otherwise.
 template <typename R>
 hipError_t launch_mri_substep(const Plan& pl, const Phys<R>& ph, const R* v, R* vout, const R* r, const double A[3],
                               const double B[3], R h, int norm, hipStream_t s) {
-    if (pl.nz > mri_substep_planes<R>() || ph.msp || ph.nf || A[0] != 0.0 || v == vout) return hipErrorNotSupported;
+    if (pl.nz > mri_substep_planes<R>() || ph.msp || A[0] != 0.0 || v == vout) return hipErrorNotSupported;
     const int ntx = (pl.nx + kSubX - 2 * kSubH - 1) / (kSubX - 2 * kSubH);
     const int nty = (pl.ny + kSubY - 2 * kSubH - 1) / (kSubY - 2 * kSubH);
     const dim3 grid((unsigned)(ntx * nty * pl.nbatch)), block(kSubX * kSubY);

@@ -84,8 +84,8 @@ __global__ void __launch_bounds__(kNT) xfwd_kernel(const R* __restrict__ f, cx<R
 // RED: the block sums (energy, or the sum of the input field) are wanted; the
 // plain field evaluation is a kernel of its own without their accumulators,
 // which keeps it within the registers of five waves per SIMD.
-// V: 0 the general kernel, 1 without a magnetisation profile and the non-finite
-// check (energies, whose densities the plain local field does not split, are general).
+// V: 0 the general kernel, 1 without a magnetisation profile (energies, whose
+// densities the plain local field does not split, are general).
 // PRE: the stencil of a thread's single cell pair is loaded before the inverse x pass.
 template <typename R, int ORD, int LN, bool RED, int V, bool PRE>
 __device__ __forceinline__ void field_body(const cx<R>* __restrict__ Y1, const R* __restrict__ f,
@@ -96,7 +96,6 @@ __device__ __forceinline__ void field_body(const cx<R>* __restrict__ Y1, const R
     if constexpr (V > 0) {
         energy = 0;
         ph.msp = nullptr;
-        ph.nf = nullptr;
     }
     pg_fix<LN>(g);
     const bool stream = stream_of<ORD>(g);
@@ -211,9 +210,9 @@ __global__ void __launch_bounds__(kNT) field_reduce_kernel(const cx<R>* __restri
     field_body<R, ORD, LN, true, V, false>(Y1, f, H, g, ph, has_demag, with_bias, energy, sum_input, partials);
 }
 
-// V: 0 the general kernel (magnetisation profile, non-finite check), 1 without
-// either and without a tape, 2 the same with a tape, 3 with a profile but without
-// the check and a tape (4 steps of a 251x251x10 disc 1484 -> 1466 us).  The plain kernels carry
+// V: 0 the general kernel (magnetisation profile and tape), 1 without either,
+// 2 without a profile but with a tape, 3 with a profile but without a tape (4 steps
+// of a 251x251x10 disc 1484 -> 1466 us).  The plain kernels carry
 // fewer uniform values (the general one spills about 60 scalar registers to
 // vector lanes, a lane read each time one is used) and no ghost selects.
 // PRE (a thread's single cell pair on small systems, see ahead()): the
@@ -244,7 +243,6 @@ __global__ void __launch_bounds__(kNT) stage_kernel(const cx<R>* Y1, cx<R>* X1, 
         if (a.tapeYin) a.tapeYin += mo;
         if (a.tapeNx) a.tapeNx += mo1;
     }
-    if constexpr (V > 0) ph.nf = nullptr;
     if constexpr (V == 1 || V == 2) ph.msp = nullptr;
     R hbv[3];
 #pragma unroll
@@ -356,9 +354,6 @@ __global__ void __launch_bounds__(kNT) stage_kernel(const cx<R>* Y1, cx<R>* X1, 
                 }
             }
         }
-        if (ph.nf)
-            note_nonfinite(ph.nf, any_nonfinite<R, 3>(xn[0]) || any_nonfinite<R, 3>(H[0]) ||
-                                      (two && (any_nonfinite<R, 3>(xn[1]) || any_nonfinite<R, 3>(H[1]))));
         if (s >= 1 && s < 4) store_pair32(a.acc, g.N, off, vec, two, acc[0], acc[1], stream);
         if (a.tapeNx) {
             if (vec) *reinterpret_cast<cx<R>*>(a.tapeNx + id) = mk<R>(nrm[0], nrm[1]);
@@ -451,7 +446,6 @@ __global__ void __launch_bounds__(kNT) bstart_kernel(cx<R>* __restrict__ X1, PG 
             for (int c = 0; c < 3; ++c) kap[q][c] = b4 * a.dt * xi[q][c];
             rhs_mu<R>(y4[q], kap[q], ph.a, ph.alpha, mu[q]);
         }
-        if (ph.nf) note_nonfinite(ph.nf, any_nonfinite<R, 3>(xi[0]) || (two && any_nonfinite<R, 3>(xi[1])));
         store_pair(a.xi5, g.N, id, vec, two, xi[0], xi[1], stream);
         store_pair(a.gm, g.N, id, vec, two, xi[0], xi[1], stream);
         store_pair(a.kap, g.N, id, vec, two, kap[0], kap[1], stream);
@@ -473,8 +467,8 @@ __global__ void __launch_bounds__(kNT) bstart_kernel(cx<R>* __restrict__ X1, PG 
     r2c_lines<R, ORD, LN>(buf, X1, g, mb, pen0, npen);
 }
 
-// V: 0 with the non-finite check, 1 without (the reverse mode has no profile).
-template <typename R, int ORD, int LN, int V>
+// (The reverse mode has no profile.)
+template <typename R, int ORD, int LN>
 __global__ void __launch_bounds__(kNT) bstage_kernel(const cx<R>* Y1, cx<R>* X1, PG g,
                                                      Phys<R> ph, BackArgs<R> a, int has_demag,
                                                      double* __restrict__ partials) {
@@ -505,7 +499,6 @@ __global__ void __launch_bounds__(kNT) bstage_kernel(const cx<R>* Y1, cx<R>* X1,
     // weights of stage s - 1: b_{s-1} dt and c_s dt
     const R bdt = (s == 2 ? (R)(1.0 / 6.0) : (R)(1.0 / 3.0)) * a.dt;
     const R cdt = (s == 4 ? (R)1 : (R)0.5) * a.dt;
-    if constexpr (V > 0) ph.nf = nullptr;
     const bool norm = ph.renorm == 2;
     double hs[3] = {0, 0, 0};
     // mu_{s-1} goes straight into this thread's own LDS line entries (read
@@ -593,7 +586,6 @@ __global__ void __launch_bounds__(kNT) bstage_kernel(const cx<R>* Y1, cx<R>* X1,
                 }
                 rhs_mu<R>(yp[q], kp[q], ph.a, ph.alpha, mup[q]);
             }
-            if (ph.nf) note_nonfinite(ph.nf, any_nonfinite<R, 3>(lam[0]) || (two && any_nonfinite<R, 3>(lam[1])));
             store_pair32(a.gm, g.N, off, vec, two, lam[0], lam[1], stream);
             store_pair32(a.kap, g.N, off, vec, two, kp[0], kp[1], stream);
             store_pair32(a.muout, g.N, off, vec, two, mup[0], mup[1], stream);
@@ -608,7 +600,6 @@ __global__ void __launch_bounds__(kNT) bstage_kernel(const cx<R>* Y1, cx<R>* X1,
             for (int q = 0; q < 2; ++q)
 #pragma unroll
                 for (int c = 0; c < 3; ++c) lam[q][c] += yb[q][c];
-            if (ph.nf) note_nonfinite(ph.nf, any_nonfinite<R, 3>(lam[0]) || (two && any_nonfinite<R, 3>(lam[1])));
             store_pair32(a.gm, g.N, off, vec, two, lam[0], lam[1], stream);
         }
     }
@@ -689,6 +680,18 @@ __global__ void copy_kernel(const R* __restrict__ src, R* __restrict__ dst, long
     if (i < n) dst[i] = src[i];
 }
 
+// The non-finite check of a call that advances a state or a gradient, on its result:
+// eight values per thread.
+constexpr int kCheckPer = 8;
+template <typename R>
+__global__ void __launch_bounds__(kNT) check_finite_kernel(const R* __restrict__ f, long long n, unsigned* flag) {
+    const long long i0 = (long long)blockIdx.x * (kNT * kCheckPer) + threadIdx.x;
+    R v[kCheckPer];
+#pragma unroll
+    for (int k = 0; k < kCheckPer; ++k) v[k] = i0 + k * kNT < n ? f[i0 + k * kNT] : (R)0;
+    note_nonfinite(flag, any_nonfinite<R, kCheckPer>(v));
+}
+
 // ---- launchers -----------------------------------------------------------------
 
 // Pencil kernel launch: the line lengths of pencil_line with compile-time
@@ -737,14 +740,13 @@ hipError_t launch_field_in(const Plan& pl, const Phys<R>& ph, const void* Y1, co
     const int has_demag = (ph.terms & MAGX_DEMAG) ? 1 : 0;
     const PG g = make_pg(pl);
     const cx<R>* y = static_cast<const cx<R>*>(Y1);
-    const bool plain = !ph.msp && !ph.nf;
-    if (energy || (sum_input && !plain))
+    if (energy || (sum_input && ph.msp))
         MAGX_PENCIL_LAUNCH(field_reduce_kernel, (, 0), y, f, H, g, ph, has_demag, with_bias, energy, sum_input, partials);
     else if (sum_input)
         MAGX_PENCIL_LAUNCH(field_reduce_kernel, (, 1), y, f, H, g, ph, has_demag, with_bias, energy, sum_input, partials);
-    else if (plain && ahead(pl))
+    else if (!ph.msp && ahead(pl))
         MAGX_PENCIL_LAUNCH(field_kernel, (, 1, true), y, f, H, g, ph, has_demag, with_bias, energy, sum_input, partials);
-    else if (plain)
+    else if (!ph.msp)
         MAGX_PENCIL_LAUNCH(field_kernel, (, 1, false), y, f, H, g, ph, has_demag, with_bias, energy, sum_input, partials);
     else
         MAGX_PENCIL_LAUNCH(field_kernel, (, 0, false), y, f, H, g, ph, has_demag, with_bias, energy, sum_input, partials);
@@ -758,8 +760,8 @@ hipError_t launch_stage_in(const Plan& pl, const Phys<R>& ph, const void* Y1, vo
     const PG g = make_pg(pl);
     const cx<R>* y = static_cast<const cx<R>*>(Y1);
     cx<R>* x = static_cast<cx<R>*>(X1);
-    if (ph.msp && !ph.nf && !a.tapeH) MAGX_PENCIL_LAUNCH(stage_kernel, (, 3, false), y, x, g, ph, a, has_demag);
-    else if (ph.msp || ph.nf) MAGX_PENCIL_LAUNCH(stage_kernel, (, 0, false), y, x, g, ph, a, has_demag);
+    if (ph.msp && !a.tapeH) MAGX_PENCIL_LAUNCH(stage_kernel, (, 3, false), y, x, g, ph, a, has_demag);
+    else if (ph.msp) MAGX_PENCIL_LAUNCH(stage_kernel, (, 0, false), y, x, g, ph, a, has_demag);
     else if (a.tapeH) MAGX_PENCIL_LAUNCH(stage_kernel, (, 2, false), y, x, g, ph, a, has_demag);
     else if (ahead(pl)) MAGX_PENCIL_LAUNCH(stage_kernel, (, 1, true), y, x, g, ph, a, has_demag);
     else MAGX_PENCIL_LAUNCH(stage_kernel, (, 1, false), y, x, g, ph, a, has_demag);
@@ -781,8 +783,7 @@ hipError_t launch_bstage_in(const Plan& pl, const Phys<R>& ph, const void* Y1, v
     const PG g = make_pg(pl);
     const cx<R>* y = static_cast<const cx<R>*>(Y1);
     cx<R>* x = static_cast<cx<R>*>(X1);
-    if (ph.nf) MAGX_PENCIL_LAUNCH(bstage_kernel, (, 0), y, x, g, ph, a, has_demag, partials);
-    else MAGX_PENCIL_LAUNCH(bstage_kernel, (, 1), y, x, g, ph, a, has_demag, partials);
+    MAGX_PENCIL_LAUNCH(bstage_kernel, (), y, x, g, ph, a, has_demag, partials);
     return hipGetLastError();
 }
 
@@ -824,6 +825,13 @@ hipError_t launch_copy(const R* src, R* dst, long long n, hipStream_t s) {
     return hipGetLastError();
 }
 
+template <typename R>
+hipError_t launch_check_finite(const R* f, long long n, unsigned* flag, hipStream_t s) {
+    const long long per = kNT * kCheckPer;
+    hipLaunchKernelGGL(check_finite_kernel<R>, dim3((unsigned)((n + per - 1) / per)), dim3(kNT), 0, s, f, n, flag);
+    return hipGetLastError();
+}
+
 #define MAGX_INST(R)                                                                                            \
     template hipError_t launch_xfwd_in<R, MAGX_COLS>(const Plan&, const R*, void*, const R*, hipStream_t);                               \
     template hipError_t launch_field_in<R, MAGX_COLS>(const Plan&, const Phys<R>&, const void*, const R*, R*, int, int, int,   \
@@ -837,7 +845,8 @@ hipError_t launch_copy(const R* src, R* dst, long long n, hipStream_t s) {
 #define MAGX_INST_COMMON(R)                                                                                     \
     template hipError_t launch_rhs<R>(const Plan&, const Phys<R>&, const R*, const R*, R*, hipStream_t);         \
     template hipError_t launch_reduce_partials<R>(const double*, int, int, int, R*, int, hipStream_t);          \
-    template hipError_t launch_copy<R>(const R*, R*, long long, hipStream_t);
+    template hipError_t launch_copy<R>(const R*, R*, long long, hipStream_t);                                   \
+    template hipError_t launch_check_finite<R>(const R*, long long, unsigned*, hipStream_t);
 
 #if MAGX_REAL == 32
 MAGX_INST(float)
