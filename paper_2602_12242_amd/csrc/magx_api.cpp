@@ -507,6 +507,8 @@ static int do_heff(magx_ctx* c, const R* m, const magx_params* p, R* H, void* ws
     return MAGX_OK;
 }
 
+// Step n of the tape: y_1 ... y_4 (3N each), H_1 ... H_4, |x_2| ... |x_5| (N each), and
+// behind it y_1 of the next step or, after the last one, the final state.
 template <typename R>
 struct TapeView {
     R* base;
@@ -551,10 +553,8 @@ static int do_step(magx_ctx* c, R* m, const magx_params* p, double dt, int nstep
             a.mn = m;
             a.acc = acc;
             a.yout = st < 4 ? (tape ? tv.y(n, st + 1) : ybuf[(st + 1) % 2]) : m;
-            a.yout2 = (st == 4 && tape) ? tv.y(n, 5) : nullptr;
-            a.tapeH = tape ? tv.H(n, st) : nullptr;
-            a.tapeNx = tape ? tv.nx(n, st + 1) : nullptr;
-            a.tapeYin = (st == 1 && tape) ? tv.y(n, 1) : nullptr;
+            a.tape = tape ? tv.y(n, 1) : nullptr;
+            a.tape_n = tv.N;
             a.stage = st;
             a.dt = (R)dt;
             a.want_next = !(n == nsteps - 1 && st == 4);

@@ -210,11 +210,11 @@ __global__ void __launch_bounds__(kNT) field_reduce_kernel(const cx<R>* __restri
     field_body<R, ORD, LN, true, V, false>(Y1, f, H, g, ph, has_demag, with_bias, energy, sum_input, partials);
 }
 
-// V: 0 the general kernel (magnetisation profile and tape), 1 without either,
-// 2 without a profile but with a tape, 3 with a profile but without a tape (4 steps
-// of a 251x251x10 disc 1484 -> 1466 us).  The plain kernels carry
-// fewer uniform values (the general one spills about 60 scalar registers to
-// vector lanes, a lane read each time one is used) and no ghost selects.
+// V: 0 with a magnetisation profile, 1 without.  The plain kernel carries fewer
+// uniform values (the other one spills scalar registers to vector lanes, a lane
+// read each time one is used) and no ghost selects.  The tape is an argument of
+// either: a kernel of its own may round differently (fused multiply-adds), and a
+// re-run segment of a rollout has to repeat what its forward pass computed.
 // PRE (a thread's single cell pair on small systems, see ahead()): the
 // stencil and the RK4 registers are loaded before the inverse x pass.
 template <typename R, int ORD, int LN, int V, bool PRE>
@@ -235,15 +235,7 @@ __global__ void __launch_bounds__(kNT) stage_kernel(const cx<R>* Y1, cx<R>* X1, 
     a.mn += mo;
     a.acc += mo;
     a.yout += mo;
-    if constexpr (V == 1 || V == 3) {
-        a.yout2 = a.tapeH = a.tapeYin = a.tapeNx = nullptr;
-    } else {
-        if (a.yout2) a.yout2 += mo;
-        if (a.tapeH) a.tapeH += mo;
-        if (a.tapeYin) a.tapeYin += mo;
-        if (a.tapeNx) a.tapeNx += mo1;
-    }
-    if constexpr (V == 1 || V == 2) ph.msp = nullptr;
+    if constexpr (V == 1) ph.msp = nullptr;
     R hbv[3];
 #pragma unroll
     for (int c = 0; c < 3; ++c) hbv[c] = ph.hbm ? ph.hbm[mb * 3 + c] : ph.hb[c];
@@ -301,7 +293,7 @@ __global__ void __launch_bounds__(kNT) stage_kernel(const cx<R>* Y1, cx<R>* X1, 
             load_pair32(a.acc, g.N, off, vec, two, acc[0], acc[1], stream);
         }
         R ys[2][3], H[2][3], sw[2] = {(R)1, (R)1};
-        if constexpr (V == 1 || V == 2) {
+        if constexpr (V == 1) {
             local_field_plain<R, PRE>(t, a.yin, g, x0, y, z, off, vec, two, ph, H);
 #pragma unroll
             for (int q = 0; q < 2; ++q)
@@ -321,8 +313,6 @@ __global__ void __launch_bounds__(kNT) stage_kernel(const cx<R>* Y1, cx<R>* X1, 
                 if (ph.terms & MAGX_ZEEMAN) H[q][c] += inside * hbv[c];
             }
         }
-        if (a.tapeH) store_pair32(a.tapeH, g.N, off, vec, two, H[0], H[1], stream);
-        if (a.tapeYin) store_pair32(a.tapeYin, g.N, off, vec, two, ys[0], ys[1], stream);
 #pragma unroll
         for (int q = 0; q < 2; ++q) llg_rhs<R>(ys[q], H[q], ph.a, ph.alpha, k[q]);
         if (s <= 1) {
@@ -355,12 +345,17 @@ __global__ void __launch_bounds__(kNT) stage_kernel(const cx<R>* Y1, cx<R>* X1, 
             }
         }
         if (s >= 1 && s < 4) store_pair32(a.acc, g.N, off, vec, two, acc[0], acc[1], stream);
-        if (a.tapeNx) {
-            if (vec) *reinterpret_cast<cx<R>*>(a.tapeNx + id) = mk<R>(nrm[0], nrm[1]);
-            else { a.tapeNx[id] = nrm[0]; if (two) a.tapeNx[id + 1] = nrm[1]; }
-        }
         store_pair32(a.yout, g.N, off, vec, two, xn[0], xn[1], stream);
-        if (a.yout2) store_pair32(a.yout2, g.N, off, vec, two, xn[0], xn[1], stream);
+        if (__builtin_expect(a.tape != nullptr, 0)) {
+            // (one branch behind the arithmetic: several between its parts cost the untaped step 1 %)
+            const long long tn = a.tape_n;
+            store_pair32(a.tape + (3 * s + 9) * tn + mo, g.N, off, vec, two, H[0], H[1], stream);
+            R* nx = a.tape + (s + 23) * tn + mo1 + id;
+            if (vec) *reinterpret_cast<cx<R>*>(nx) = mk<R>(nrm[0], nrm[1]);
+            else { nx[0] = nrm[0]; if (two) nx[1] = nrm[1]; }
+            if (s == 1) store_pair32(a.tape + mo, g.N, off, vec, two, ys[0], ys[1], stream);
+            if (s == 4) store_pair32(a.tape + 28 * tn + mo, g.N, off, vec, two, xn[0], xn[1], stream);
+        }
         if (fwd) {
             // demag source of the next stage: Ms(r) m = Ms s m
 #pragma unroll
@@ -760,9 +755,7 @@ hipError_t launch_stage_in(const Plan& pl, const Phys<R>& ph, const void* Y1, vo
     const PG g = make_pg(pl);
     const cx<R>* y = static_cast<const cx<R>*>(Y1);
     cx<R>* x = static_cast<cx<R>*>(X1);
-    if (ph.msp && !a.tapeH) MAGX_PENCIL_LAUNCH(stage_kernel, (, 3, false), y, x, g, ph, a, has_demag);
-    else if (ph.msp) MAGX_PENCIL_LAUNCH(stage_kernel, (, 0, false), y, x, g, ph, a, has_demag);
-    else if (a.tapeH) MAGX_PENCIL_LAUNCH(stage_kernel, (, 2, false), y, x, g, ph, a, has_demag);
+    if (ph.msp) MAGX_PENCIL_LAUNCH(stage_kernel, (, 0, false), y, x, g, ph, a, has_demag);
     else if (ahead(pl)) MAGX_PENCIL_LAUNCH(stage_kernel, (, 1, true), y, x, g, ph, a, has_demag);
     else MAGX_PENCIL_LAUNCH(stage_kernel, (, 1, false), y, x, g, ph, a, has_demag);
     return hipGetLastError();

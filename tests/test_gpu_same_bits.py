@@ -1,7 +1,9 @@
 """Calls that compute the same thing give the same bits: check_finite = 1 adds a flag
-and leaves the computation unchanged.  Fields, steps (single, and long enough to be
-replayed in two chunks), Euler and multirate steps, the reverse mode, with and without
-a magnetisation profile, on every order and kind of line; no tolerance."""
+and leaves the computation unchanged, and a taped step records what the untaped one
+computes, so a rollout's re-run segments repeat its forward pass.  Fields, steps
+(single, and long enough to be replayed in two chunks), Euler and multirate steps, the
+reverse mode, with and without a magnetisation profile, on every order and kind of
+line; no tolerance."""
 import numpy as np
 import pytest
 
@@ -87,3 +89,18 @@ def test_overflow_inside_a_call_is_reported(n, dtype):
         assert ctx.status() == -6
     ctx.step(m, p, DT, 1)
     assert ctx.status() == 0
+
+
+@pytest.mark.parametrize("n,dtype", _cases())
+@pytest.mark.parametrize("profile", [0, 1])
+def test_taped_steps_equal_untaped(n, dtype, profile):
+    magx, ctx, m, _ = _setup(n, dtype)
+    if profile:
+        s = _profile(n, ctx.tdtype)
+        ctx.set_ms_profile(s)
+    p = magx.make_params(**MAT)
+    for steps in (1, 18):
+        a, b = m.clone(), m.clone()
+        ctx.step(a, p, DT, steps)
+        ctx.step(b, p, DT, steps, tape=ctx.tape(steps))
+        assert torch.equal(a, b), steps
