@@ -135,6 +135,9 @@ static int column_plan(const Plan& p) {
     return (long long)((3 * p.nz * column_width(p.Py)) | 1) * p.Py * 2 * p.esize <= kColumnLds ? 1 : 0;
 }
 
+// Whether a film kernel's tile of t columns of all three components fits in 64 KiB.
+static bool film_tile_fits(int Py, int t, int esize) { return 3LL * Py * t * 2 * esize <= 65536; }
+
 int make_plan(const magx_grid* g, magx_dtype dt, int nbatch, Plan* pl) {
     if (!g || !pl || nbatch < 1) return MAGX_EINVAL;
     if (dt != MAGX_F32 && dt != MAGX_F64) return MAGX_EDTYPE;
@@ -169,8 +172,13 @@ int make_plan(const magx_grid* g, magx_dtype dt, int nbatch, Plan* pl) {
             return MAGX_ESIZE;
     }
     p.Px = extended_length(p.nx, p.ncell, p.nz, 1536);
-    // (films of more than 1024 cells along x: the film kernel's lengths are powers of two)
-    if (p.nz > 1 || p.nx <= 1024) p.Py = extended_length(p.ny, p.ncell, p.nz, 768);
+    // Films the column convolution does not take (at most 8 or more than 1024 cells
+    // along x) keep the power of two for the film kernel, which knows no other length:
+    // four RK4 steps in single precision with it / with three passes at an odd factor,
+    // us, 8x75x1 252/312, 64 of them 637/1180, 5x96x1 283/343.  Narrow films too long
+    // for its tile have three passes either way (8x150x1 488/370).
+    const bool film = p.nz == 1 && (p.nx > 1024 || (p.nx <= 8 && film_tile_fits(p.Py, 8, p.esize)));
+    if (!film) p.Py = extended_length(p.ny, p.ncell, p.nz, 768);
     p.lgPx = ilog2(p.Px / odd_part(p.Px)); p.lgPy = ilog2(p.Py / odd_part(p.Py)); p.lgPz = ilog2(p.Pz);
     p.Lh = p.Px / 2; p.lgLh = p.lgPx - 1;
     p.Hx = p.Lh + 1; p.Hy = p.Py / 2 + 1; p.Hz = p.Pz / 2 + 1;
@@ -218,7 +226,7 @@ int make_plan(const magx_grid* g, magx_dtype dt, int nbatch, Plan* pl) {
     // of them, since there the kernel's latency, not its traffic, counts
     if (p.nz == 1 && !p.col && odd_part(p.Py) == 1) {
         int t = 16;
-        while (t >= 8 && 3LL * p.Py * t * 2 * p.esize > 65536) t >>= 1;
+        while (t >= 8 && !film_tile_fits(p.Py, t, p.esize)) t >>= 1;
         if (t >= 8) {
             while (t > 4 && (p.Hx + t - 1) / t < 64) t >>= 1;
             p.yzfilm = 1;
