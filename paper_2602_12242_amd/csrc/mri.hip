@@ -222,8 +222,12 @@ __global__ void __launch_bounds__(kSubX* kSubY)
                 for (int c = 0; c < 3; ++c) sv[c][z][ly][lx] = V[z][c];
             }
         __syncthreads();
-        // stage k is complete on the columns at least k + 1 cells inside the tile
-        if (in && lx > k && lx < kSubX - 1 - k && ly > k && ly < kSubY - 1 - k) {
+        // stage k is complete on the columns at least k + 1 cells inside the tile.
+        // Columns beyond the grid in x compute along (nothing reads their values):
+        // double-precision arithmetic of a wave with few active lanes ran at about
+        // half speed (4x20x6 25 -> 14 us a substep, 27x20x6 25 -> 15, 30x20x6 18 -> 15,
+        // 26x20x6 14 either way; single precision 4x20x6 11.7 -> 10.6).
+        if (y >= 0 && y < ny && lx > k && lx < kSubX - 1 - k && ly > k && ly < kSubY - 1 - k) {
             R below[3];
 #pragma unroll
             for (int z = 0; z < NZM; ++z) {
