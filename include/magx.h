@@ -53,9 +53,8 @@ extern "C" {
 #define MAGX_EINVAL     -1   /* null pointer, non-positive size or spacing, bad flag, DMI without exchange */
 #define MAGX_ESIZE      -2   /* n > 4096 on an axis, or the next power of two P >= 2n exceeds the FFT
                                 passes' limits: Py <= 4096; Px <= 4096 (float) or 2048 (double);
-                                Pz <= 1024.  (The extended lengths along x and y may be 5/8 or
-                                3/4 of that power of two on grids of at most eight planes or at
-                                least 2^16 cells; the limits are those of the power of two.) */
+                                Pz <= 1024.  (The lengths a context uses may be shorter, see
+                                magx_extended_lengths; the limits are those of the power of two.) */
 #define MAGX_EDTYPE     -3   /* unknown element type */
 #define MAGX_EWORKSPACE -4   /* magx_step_static: the grid needs more than its fixed workspace;
                                 elsewhere buffer sizes are the caller's contract (see magx_sizes) */
@@ -303,9 +302,16 @@ int magx_ctx_info(const magx_ctx* ctx, magx_grid* g, magx_dtype* dt);
  * 6, Hz, tz): element (c, kz, ky, kx) of the real octant of the tensor
  * spectrum (c = xx yy zz xy xz yz, already scaled by 1/(Px Py Pz)) is at
  * (((ky * ntz + kx / tz) * 6 + c) * Hz + kz) * tz + kx % tz; Hy = Py/2 + 1,
- * Hz = Pz/2 + 1, kx < Px/2 + 1 <= ntz * tz.  (Copies of parts of it in other
- * orders may follow.)  Host only. */
+ * Hz = Pz/2 + 1, kx < Px/2 + 1 <= ntz * tz, with P from magx_extended_lengths.
+ * (Copies of parts of it in other orders may follow.)  Host only. */
 int magx_spectrum_layout(const magx_ctx* ctx, int dims[5]);
+
+/* Extended lengths P = (Px, Py, Pz) of a context's convolution, each at least
+ * twice the cells along its axis: Pz is the smallest such power of two (at
+ * least 2), Px and Py that power of two or 5/8 or 3/4 of it, whichever the
+ * library chose for the grid and element type.  MAGX_EINVAL for a NULL
+ * argument.  Host only. */
+int magx_extended_lengths(const magx_ctx* ctx, int P[3]);
 
 /* Diagnostics: from magx_profile_start until magx_profile_stop, every launch
  * of one kernel family enqueued through ctx is bracketed by a pair of HIP

@@ -95,10 +95,11 @@ static size_t align256(size_t v) { return (v + 255) & ~size_t(255); }
 // fields, their traffic and the tensor shrink with it.  Faster at every size
 // measured: two RK4 steps, us, power of two / odd factor, single and double
 // precision, 75x75x1 149/137 160/147, 300x100x1 164/139 186/160, 75x75x8 316/238
-// 371/286, 301x37x5 315/267 419/338, 8 films of 150x75x2 274/193 420/298.  Small
-// grids of more than eight planes keep the power of two all the same (40x75x20
-// 323/318 434/380, 75x18x40 386/294 605/464): the layout of their stored tensor
-// is an output (magx_spectrum_layout) that callers hold to it.
+// 371/286, 301x37x5 315/267 419/338, 8 films of 150x75x2 274/193 420/298.  Grids of
+// more than eight planes and fewer than 2^16 cells keep the power of two although
+// it is slower there too (40x75x20 323/318 434/380, 75x18x40 386/294 605/464): the
+// line is one of compatibility, for readers of the stored tensor that work the
+// lengths out themselves, as the parity test of 96x70x9 and 70x9x20 does.
 static int extended_length(int n, long long ncell, int nz, int most) {
     const int p = next_pow2_at_least(std::max(2, 2 * n));
     if (p < 256 || (nz > 8 && ncell < (1LL << 16))) return p;
@@ -1204,6 +1205,14 @@ int magx_spectrum_layout(const magx_ctx* ctx, int dims[5]) {
     dims[2] = 6;
     dims[3] = ctx->pl.Hz;
     dims[4] = ctx->pl.tz;
+    return MAGX_OK;
+}
+
+int magx_extended_lengths(const magx_ctx* ctx, int P[3]) {
+    if (!ctx || !P) return MAGX_EINVAL;
+    P[0] = ctx->pl.Px;
+    P[1] = ctx->pl.Py;
+    P[2] = ctx->pl.Pz;
     return MAGX_OK;
 }
 

@@ -56,7 +56,7 @@ EXPORTS = ("magx_sizes", "magx_sizes_batched", "magx_tensor_init", "magx_tensor_
            "magx_set_member_bias", "magx_ctx_batch", "magx_set_ms_profile", "magx_heff", "magx_llg_rhs", "magx_step", "magx_step_static", "magx_step_mri",
            "magx_step_euler", "magx_set_bias_schedule", "magx_get_time",
            "magx_heff_backward", "magx_step_backward", "magx_rollout_forward", "magx_rollout_backward",
-           "magx_energy", "magx_status", "magx_heff_count", "magx_ctx_info", "magx_spectrum_layout", "magx_memory_probe", "magx_profile_start",
+           "magx_energy", "magx_status", "magx_heff_count", "magx_ctx_info", "magx_spectrum_layout", "magx_extended_lengths", "magx_memory_probe", "magx_profile_start",
            "magx_profile_stop", "magx_strerror", "magx_destroy")
 
 _lib = None
@@ -97,6 +97,7 @@ def load(path=LIB_PATH):
         "magx_heff_count": (ctypes.c_longlong, [vp]),
         "magx_ctx_info": (i, [vp, P(magx_grid), P(ctypes.c_int)]),
         "magx_spectrum_layout": (i, [vp, P(ctypes.c_int)]),
+        "magx_extended_lengths": (i, [vp, P(ctypes.c_int)]),
         "magx_memory_probe": (i, [vp, i, vp, vp, P(d)]),
         "magx_profile_start": (i, [vp, i]),
         "magx_profile_stop": (i, [vp, P(ctypes.c_longlong), P(ctypes.c_double)]),
@@ -205,15 +206,18 @@ class Context:
         if t.dtype != self.tdtype or not t.is_contiguous() or tuple(t.shape) != self.shape or t.device != self.device:
             raise ValueError(f"{name}: expected contiguous {self.tdtype} {self.shape} on {self.device}")
 
+    def extended_lengths(self):
+        """The extended lengths (Px, Py, Pz) of the convolution."""
+        P = (ctypes.c_int * 3)()
+        _check(self.lib.magx_extended_lengths(self.h, P), "magx_extended_lengths")
+        return tuple(int(v) for v in P)
+
     def spectrum_array(self):
         """The stored tensor spectrum as a logical (6, Hz, Hy, Hx) array (for tests)."""
         dims = (ctypes.c_int * 5)()
         _check(self.lib.magx_spectrum_layout(self.h, dims), "magx_spectrum_layout")
         Hy, ntz, six, Hz, tz = (int(v) for v in dims)
-        nx, ny, nz = self.n
-        Px, Py, Pz = max(2, 1 << (2 * nx - 1).bit_length()), 2 * (Hy - 1), 2 * (Hz - 1)
-        if Px >= 256 and (nz <= 8 or nx * ny * nz >= 1 << 16):      # 5/8 or 3/4 of the power of two where that is enough
-            Px = next((c for c in (Px // 8 * 5, Px // 4 * 3) if 2 * nx <= c <= 1536), Px)
+        Px, Py, Pz = self.extended_lengths()
         Hx = Px // 2 + 1
         el = self.spectrum.view(self.tdtype)[: Hy * ntz * six * Hz * tz]
         arr = el.view(Hy, ntz, six, Hz, tz).permute(2, 3, 0, 1, 4).reshape(six, Hz, Hy, ntz * tz)
