@@ -31,6 +31,29 @@ FILMS = [((8, 64, 1), 0, "film"), ((8, 65, 1), 0, "film"), ((8, 75, 1), 0, "film
          ((8, 97, 1), 0, "film"), ((1, 128, 1), 0, "film"), ((8, 64, 1), 1, "film"), ((8, 65, 1), 1, "passes"),
          ((8, 129, 1), 0, "passes"), ((1500, 75, 1), 0, "film")]
 
+# the line lengths Lh with kernels of their own, in row order (five planes and Py = 32:
+# three passes) and in column order: (cells along x, Lh)
+LINES = [(73, 80), (96, 96), (150, 160), (161, 192), (311, 320), (384, 384), (520, 640), (768, 768), (128, 128),
+         (256, 256), (512, 512), (1024, 1024)]
+# the lengths of the y passes, on five planes: (rows, Py)
+ROWS = [(50, 128), (80, 160), (83, 192), (160, 320), (171, 384), (257, 640), (384, 768), (400, 1024)]
+# the column convolution's lengths, at the most rows and planes of each (the largest
+# columns) and at the fewest: (Py, fewest rows)
+COLUMNS = [(32, 9), (64, 17), (128, 33), (160, 65), (192, 81), (256, 97), (320, 129), (384, 161), (512, 193),
+           (640, 257), (768, 321), (1024, 385)]
+
+
+def _columns():
+    for Py, low in COLUMNS:
+        for dtype in (1, 0):
+            for Pz in (2, 4, 8, 16):
+                if Pz == 16 and not (dtype == 0 and Py in (256, 512)):
+                    continue      # (other columns of nine and more values along z take the passes)
+                if dtype == 1 and Py == 1024 and Pz == 8:
+                    continue
+                yield Py, Pz, dtype, (9, Py // 2, Pz // 2)
+                yield Py, Pz, dtype, (20, low, Pz // 4 + 1 if Pz > 2 else 1)
+
 
 def _path(ctx, m, p):
     launches = {}
@@ -81,3 +104,109 @@ def test_narrow_and_long_films(n, dtype, path):
     ctx, q = magx.Context(n, D, dtype=dtype), magx.make_params(**MAT)
     assert _path(ctx, _dev(random_unit_field(n, 950, 2), dtype), q) == path
     _parity(ctx, q, n, dtype)
+
+
+def _context(n, dtype, path, lengths):
+    from paper_2602_12242_amd import magx
+    ctx, q = magx.Context(n, D, dtype=dtype), magx.make_params(**MAT)
+    for got, want in zip(ctx.extended_lengths(), lengths):
+        assert want is None or got == want
+    assert _path(ctx, _dev(random_unit_field(n, 950, 2), dtype), q) == path
+    return ctx, q
+
+
+@pytest.mark.parametrize("nx,Lh", LINES)
+@pytest.mark.parametrize("order", ["passes", "column"])
+@pytest.mark.parametrize("dtype", [1, 0])
+def test_line_lengths_in_both_orders(nx, Lh, order, dtype):
+    n = (nx, 6, 5) if order == "passes" else (nx, 10, 3)
+    ctx, q = _context(n, dtype, order, (2 * Lh, None, None))
+    _parity(ctx, q, n, dtype)
+
+
+@pytest.mark.parametrize("ny,Py", ROWS)
+@pytest.mark.parametrize("dtype", [1, 0])
+def test_lengths_of_the_y_passes(ny, Py, dtype):
+    n = (10, ny, 5)
+    ctx, q = _context(n, dtype, "passes", (32, Py, 16))
+    _parity(ctx, q, n, dtype)
+
+
+@pytest.mark.parametrize("Py,Pz,dtype,n", list(_columns()))
+def test_column_lengths_and_planes(Py, Pz, dtype, n):
+    ctx, q = _context(n, dtype, "column", (None, Py, Pz))
+    g, p = Grid(*n, *D), Params(**MAT)
+    m = random_unit_field(n, 953, 2).astype(np.float32)
+    ref = ofield.heff(g, p, m.astype(np.float64), onewell.spectrum(g))
+    assert _err(ctx.heff(_dev(m, dtype), q).cpu().numpy(), ref) <= (1e-11 if dtype == 1 else 1e-5)
+
+
+# lines with an odd factor: one and two of them per block, a packed Nyquist column of
+# 80 rows (no multiple of its groups' tile), both orders
+@pytest.mark.parametrize("n,dtype,path", [((90, 70, 5), 0, "passes"), ((90, 70, 8), 1, "passes"),
+                                          ((66, 258, 8), 0, "passes"), ((90, 20, 3), 0, "column"),
+                                          ((90, 20, 3), 1, "column")])
+@pytest.mark.parametrize("profile", [0, 1])
+def test_batch_equals_members(n, dtype, path, profile):
+    from paper_2602_12242_amd import magx
+    B = 3
+    one, q = _context(n, dtype, path, (2 * (80 if n[0] == 66 else 96), None, None))
+    many = magx.Context(n, D, dtype=dtype, nbatch=B)
+    if profile:
+        s = _dev(_disc(n), dtype)
+        one.set_ms_profile(s)
+        many.set_ms_profile(s)
+    m = torch.stack([_dev(random_unit_field(n, 960 + b, 2), dtype) for b in range(B)])
+    g = torch.stack([_dev(random_vector_field(n, 970 + b), dtype) for b in range(B)])
+
+    def outputs(ctx, m, g):
+        out = [ctx.heff(m, q)]
+        for call in (lambda y: ctx.step(y, q, 5e-14, 2), lambda y: ctx.step_euler(y, q, 1e-14, 2),
+                     lambda y: ctx.step_mri(y, q, 5e-14, 1)):
+            y = m.clone()
+            call(y)
+            out.append(y)
+        if not profile:
+            tape, lam = ctx.tape(1), g.clone()
+            gh = torch.zeros(ctx.lead + (3,), dtype=ctx.tdtype, device="cuda")
+            ctx.step(m.clone(), q, 5e-14, 1, tape=tape)
+            ctx.step_backward(tape, 1, q, 5e-14, lam, gh)
+            out += [lam, gh, *ctx.heff_backward(g, q)]
+        return out
+
+    got = outputs(many, m, g)
+    for b in range(B):
+        for k, (x, y) in enumerate(zip(outputs(one, m[b].contiguous(), g[b].contiguous()), got)):
+            assert torch.equal(x, y[b]), (b, k)
+
+
+def _disc(n):
+    # a disc with a weaker core; its corners, and most of the top plane, are empty
+    y, x = np.mgrid[0:n[1], 0:n[0]]
+    r = np.hypot((x - n[0] / 2) / n[0], (y - n[1] / 2) / n[1])
+    s = np.broadcast_to(np.where(r < 0.15, 0.6, np.where(r < 0.46, 1.0, 0.0)), (n[2], n[1], n[0])).copy()
+    s[-1, :, : 2 * n[0] // 3] = 0.0
+    return s
+
+
+@pytest.mark.parametrize("n,path", [((90, 20, 3), "column"), ((90, 12, 6), "passes"), ((301, 9, 5), "passes")])
+@pytest.mark.parametrize("dtype", [1, 0])
+def test_masked_steps_at_odd_lines(n, path, dtype):
+    ctx, q = _context(n, dtype, path, (192 if n[0] == 90 else 640, None, None))
+    s = _disc(n)
+    ctx.set_ms_profile(_dev(s, dtype))
+    g, p = Grid(*n, *D), Params(ms_profile=s, **MAT)
+    spec = onewell.spectrum(g)
+    tol = 1e-11 if dtype == 1 else 1e-5
+    m = random_unit_field(n, 954, 2).astype(np.float32)
+    m[:, s == 0] = 0.0
+    m64, dt = m.astype(np.float64), 3e-14
+    H = ctx.heff(_dev(m, dtype), q).cpu().numpy()
+    assert np.all(H[:, s == 0] == 0.0)
+    assert _err(H, ofield.heff(g, p, m64, spec)) <= tol
+    for call, ref in ((ctx.step, ollg.rk4_step(g, p, m64, dt, spec)), (ctx.step_euler, ollg.euler_step(g, p, m64, dt, spec))):
+        y = _dev(m, dtype)
+        call(y, q, dt, 1)
+        y = y.cpu().numpy()
+        assert np.all(y[:, s == 0] == 0.0)
+        assert _err(y, ref) <= tol
