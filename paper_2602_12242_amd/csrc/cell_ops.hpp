@@ -68,28 +68,34 @@ __device__ __forceinline__ void pg_fix(PG& g) {
     }
 }
 
-// Cases of a launch switch over the line length: the lengths with an odd factor.
+// Cases of a launch switch over the line length: the lengths with an odd factor
+// (_512: those of at most 512 values).
 // VV: further template arguments in parentheses, "()" or "(, value)".
 #define MAGX_UNWRAP(...) __VA_ARGS__
 #define MAGX_LINE_CASE(ORD, LN, KERNEL, VV, LDS, ...)                                                     \
     case LN:                                                                                              \
         hipLaunchKernelGGL((KERNEL<R, ORD, LN MAGX_UNWRAP VV>), grid_, block_, LDS, s, __VA_ARGS__);      \
         break;
-#define MAGX_ODD_LINES(ORD, KERNEL, VV, LDS, ...)          \
+#define MAGX_ODD_LINES_512(ORD, KERNEL, VV, LDS, ...)      \
     MAGX_LINE_CASE(ORD, 80, KERNEL, VV, LDS, __VA_ARGS__)  \
     MAGX_LINE_CASE(ORD, 96, KERNEL, VV, LDS, __VA_ARGS__)  \
     MAGX_LINE_CASE(ORD, 160, KERNEL, VV, LDS, __VA_ARGS__) \
     MAGX_LINE_CASE(ORD, 192, KERNEL, VV, LDS, __VA_ARGS__) \
     MAGX_LINE_CASE(ORD, 320, KERNEL, VV, LDS, __VA_ARGS__) \
-    MAGX_LINE_CASE(ORD, 384, KERNEL, VV, LDS, __VA_ARGS__) \
+    MAGX_LINE_CASE(ORD, 384, KERNEL, VV, LDS, __VA_ARGS__)
+#define MAGX_ODD_LINES(ORD, KERNEL, VV, LDS, ...)          \
+    MAGX_ODD_LINES_512(ORD, KERNEL, VV, LDS, __VA_ARGS__)  \
     MAGX_LINE_CASE(ORD, 640, KERNEL, VV, LDS, __VA_ARGS__) \
     MAGX_LINE_CASE(ORD, 768, KERNEL, VV, LDS, __VA_ARGS__)
 
 // log2 of the largest radix of a line transform.  Radix 8 in place of 16 costs a
 // pass at 256 (4 8 8 in place of 16 16) but spreads over twice the threads: a
 // gradient at 256x256x8 7100 -> 6870 us, at 190x75x9 in double precision (lines of
-// 192: 8 8 3 in place of 4 16 3) 2610 -> 2567; films (128) and 1024-cell lines were
-// 2 and 1 % slower with it, 320 and 512 equal.
+// 192: 8 8 3 in place of 4 16 3) 2610 -> 2567; four RK4 steps at lines of 96 and 160
+// (4 8 3 and 4 8 5 in place of 2 16 3 and 2 16 5) in single precision 90x60x1 257 -> 239,
+// 150x60x1 264 -> 245, 90x150x7 697 -> 674, 150x150x7 750 -> 724, in double precision up
+// to 8 %, equal at 90x300x12 and above; films (128) and 1024-cell lines were 2 and 1 %
+// slower with it, 320 and 512 equal.
 template <int ORD, int LN> constexpr int line_lgm() {
     return ORD == kBigRows ? 5 : (LN == 256 || LN == 192 || LN == 160 || LN == 96 ? 3 : 4);
 }

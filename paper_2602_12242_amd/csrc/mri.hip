@@ -299,10 +299,14 @@ static int odd_line(const Plan& pl) { return odd_part(pl.Lh) > 1 ? pl.Lh : 0; }
         switch (LINE) {                                                                                            \
             MAGX_ODD_LINES(kRows, KERNEL, VV, lds, __VA_ARGS__)                                                    \
             default:                                                                                               \
-                if (pencil_big(pl))                                                                                \
-                    hipLaunchKernelGGL((KERNEL<R, kBigRows, 0 MAGX_UNWRAP VV>), grid_, block_, lds, s, __VA_ARGS__); \
-                else                                                                                               \
-                    hipLaunchKernelGGL((KERNEL<R, kRows, 0 MAGX_UNWRAP VV>), grid_, block_, lds, s, __VA_ARGS__);  \
+                if constexpr (sizeof(R) == 4) {                                                                    \
+                    if (pencil_big(pl)) {                                                                          \
+                        hipLaunchKernelGGL((KERNEL<R, kBigRows, 0 MAGX_UNWRAP VV>), grid_, block_, lds, s,         \
+                                           __VA_ARGS__);                                                           \
+                        break;                                                                                     \
+                    }                                                                                              \
+                }                                                                                                  \
+                hipLaunchKernelGGL((KERNEL<R, kRows, 0 MAGX_UNWRAP VV>), grid_, block_, lds, s, __VA_ARGS__);      \
         }                                                                                                          \
     } while (0)
 

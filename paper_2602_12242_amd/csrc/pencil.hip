@@ -704,11 +704,28 @@ constexpr int kOrder = MAGX_COLS ? kColumns : kRows;
             MAGX_LINE_CASE(kOrder, 512, KERNEL, VV, lds_, __VA_ARGS__)                                             \
             MAGX_LINE_CASE(kOrder, 1024, KERNEL, VV, lds_, __VA_ARGS__)                                            \
             default:                                                                                               \
-                if (kOrder == kRows && pencil_big(pl))                                                             \
-                    hipLaunchKernelGGL((KERNEL<R, kOrder == kRows ? kBigRows : kOrder, 0 MAGX_UNWRAP VV>), grid_,  \
-                                       block_, lds_, s, __VA_ARGS__);                                              \
-                else                                                                                               \
-                    hipLaunchKernelGGL((KERNEL<R, kOrder, 0 MAGX_UNWRAP VV>), grid_, block_, lds_, s, __VA_ARGS__); \
+                if constexpr (kOrder == kRows && sizeof(R) == 4) {                                                 \
+                    if (pencil_big(pl)) {                                                                          \
+                        hipLaunchKernelGGL((KERNEL<R, kBigRows, 0 MAGX_UNWRAP VV>), grid_, block_, lds_, s,        \
+                                           __VA_ARGS__);                                                           \
+                        break;                                                                                     \
+                    }                                                                                              \
+                }                                                                                                  \
+                hipLaunchKernelGGL((KERNEL<R, kOrder, 0 MAGX_UNWRAP VV>), grid_, block_, lds_, s, __VA_ARGS__);    \
+        }                                                                                                          \
+    } while (0)
+// The same for kernels with loads ahead (see ahead()): lines of at most 512 values.
+#define MAGX_PENCIL_LAUNCH_AHEAD(KERNEL, VV, ...)                                                                  \
+    do {                                                                                                           \
+        const dim3 grid_((unsigned)pl.pencil_blocks), block_(kNT);                                                 \
+        const size_t lds_ = pencil_lds(pl);                                                                        \
+        switch (pencil_line(pl)) {                                                                                 \
+            MAGX_ODD_LINES_512(kOrder, KERNEL, VV, lds_, __VA_ARGS__)                                              \
+            MAGX_LINE_CASE(kOrder, 128, KERNEL, VV, lds_, __VA_ARGS__)                                             \
+            MAGX_LINE_CASE(kOrder, 256, KERNEL, VV, lds_, __VA_ARGS__)                                             \
+            MAGX_LINE_CASE(kOrder, 512, KERNEL, VV, lds_, __VA_ARGS__)                                             \
+            default:                                                                                               \
+                hipLaunchKernelGGL((KERNEL<R, kOrder, 0 MAGX_UNWRAP VV>), grid_, block_, lds_, s, __VA_ARGS__);    \
         }                                                                                                          \
     } while (0)
 
@@ -721,6 +738,7 @@ constexpr int kOrder = MAGX_COLS ? kColumns : kRows;
 // registers (74 -> 117 in single precision) cost a full GPU more than the wait,
 // 24 systems of 128x128x2 5491 -> 5943 us with it, 64 films 1607 -> 1616, while
 // one 128x128x2 system would gain 2 %.
+// (np Lh / 2 <= 256: lines of at most 512 values.)
 static bool ahead(const Plan& pl) { return pl.blocks_per_member <= 64 && pl.np * std::max(1, pl.Lh / 2) <= kNT; }
 
 template <typename R, bool COLS>
@@ -740,7 +758,7 @@ hipError_t launch_field_in(const Plan& pl, const Phys<R>& ph, const void* Y1, co
     else if (sum_input)
         MAGX_PENCIL_LAUNCH(field_reduce_kernel, (, 1), y, f, H, g, ph, has_demag, with_bias, energy, sum_input, partials);
     else if (!ph.msp && ahead(pl))
-        MAGX_PENCIL_LAUNCH(field_kernel, (, 1, true), y, f, H, g, ph, has_demag, with_bias, energy, sum_input, partials);
+        MAGX_PENCIL_LAUNCH_AHEAD(field_kernel, (, 1, true), y, f, H, g, ph, has_demag, with_bias, energy, sum_input, partials);
     else if (!ph.msp)
         MAGX_PENCIL_LAUNCH(field_kernel, (, 1, false), y, f, H, g, ph, has_demag, with_bias, energy, sum_input, partials);
     else
@@ -756,7 +774,7 @@ hipError_t launch_stage_in(const Plan& pl, const Phys<R>& ph, const void* Y1, vo
     const cx<R>* y = static_cast<const cx<R>*>(Y1);
     cx<R>* x = static_cast<cx<R>*>(X1);
     if (ph.msp) MAGX_PENCIL_LAUNCH(stage_kernel, (, 0, false), y, x, g, ph, a, has_demag);
-    else if (ahead(pl)) MAGX_PENCIL_LAUNCH(stage_kernel, (, 1, true), y, x, g, ph, a, has_demag);
+    else if (ahead(pl)) MAGX_PENCIL_LAUNCH_AHEAD(stage_kernel, (, 1, true), y, x, g, ph, a, has_demag);
     else MAGX_PENCIL_LAUNCH(stage_kernel, (, 1, false), y, x, g, ph, a, has_demag);
     return hipGetLastError();
 }
