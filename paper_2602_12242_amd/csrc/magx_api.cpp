@@ -563,7 +563,7 @@ static int do_step(magx_ctx* c, R* m, const magx_params* p, double dt, int nstep
             a.acc = acc;
             a.yout = st < 4 ? (tape ? tv.y(n, st + 1) : ybuf[(st + 1) % 2]) : m;
             a.tape = tape ? tv.y(n, 1) : nullptr;
-            a.tape_n = tv.N;
+            a.tape_n = tape ? (int)tv.N : 0;
             a.stage = st;
             a.dt = (R)dt;
             a.want_next = !(n == nsteps - 1 && st == 4);

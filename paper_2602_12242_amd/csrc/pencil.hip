@@ -230,11 +230,11 @@ __global__ void __launch_bounds__(kNT) stage_kernel(const cx<R>* Y1, cx<R>* X1, 
     int pen0, npen;
     block_pencils(g, lb - mb * g.bpm, pen0, npen);
     const long long mo = (long long)mb * 3 * g.N;   // member offset of vector fields
-    const long long mo1 = (long long)mb * g.N;      // member offset of scalar fields
     a.yin += mo;
     a.mn += mo;
     a.acc += mo;
     a.yout += mo;
+    a.tape += mo;
     if constexpr (V == 1) ph.msp = nullptr;
     R hbv[3];
 #pragma unroll
@@ -346,15 +346,19 @@ __global__ void __launch_bounds__(kNT) stage_kernel(const cx<R>* Y1, cx<R>* X1, 
         }
         if (s >= 1 && s < 4) store_pair32(a.acc, g.N, off, vec, two, acc[0], acc[1], stream);
         store_pair32(a.yout, g.N, off, vec, two, xn[0], xn[1], stream);
-        if (__builtin_expect(a.tape != nullptr, 0)) {
+        if (__builtin_expect(a.tape_n != 0, 0)) {
             // (one branch behind the arithmetic: several between its parts cost the untaped step 1 %)
-            const long long tn = a.tape_n;
-            store_pair32(a.tape + (3 * s + 9) * tn + mo, g.N, off, vec, two, H[0], H[1], stream);
-            R* nx = a.tape + (s + 23) * tn + mo1 + id;
+            int stride = a.tape_n;
+            // (double precision: keeps the addresses from being formed ahead of the loop and
+            // held in registers; 5 films of 64x256x1 783 -> 774 us for six steps)
+            if constexpr (sizeof(R) == 8) asm volatile("" : "+s"(stride));
+            const long long tn = stride;
+            store_pair32(a.tape + (3 * s + 9) * tn, g.N, off, vec, two, H[0], H[1], stream);
+            if (s == 1) store_pair32(a.tape, g.N, off, vec, two, ys[0], ys[1], stream);
+            R* nx = a.tape + (s + 23) * tn - 2 * mb * g.N + id;   // one value per cell
             if (vec) *reinterpret_cast<cx<R>*>(nx) = mk<R>(nrm[0], nrm[1]);
             else { nx[0] = nrm[0]; if (two) nx[1] = nrm[1]; }
-            if (s == 1) store_pair32(a.tape + mo, g.N, off, vec, two, ys[0], ys[1], stream);
-            if (s == 4) store_pair32(a.tape + 28 * tn + mo, g.N, off, vec, two, xn[0], xn[1], stream);
+            if (s == 4) store_pair32(a.tape + 28 * tn, g.N, off, vec, two, xn[0], xn[1], stream);
         }
         if (fwd) {
             // demag source of the next stage: Ms(r) m = Ms s m
