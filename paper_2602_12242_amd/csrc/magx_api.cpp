@@ -1,6 +1,6 @@
 // C ABI of the magx library: argument validation, planning, buffer layout and
 // launch sequencing on the caller's stream.  Every numeric step runs in the
-// HIP kernels of tensor.hip, conv.hip and pencil.hip.
+// HIP kernels of tensor.hip, conv.hip, column.hip, pencil.hip and mri.hip.
 #include <algorithm>
 #include <cmath>
 #include <cstring>
@@ -562,7 +562,6 @@ static int do_step(magx_ctx* c, R* m, const magx_params* p, double dt, int nstep
             a.mn = m;
             a.acc = acc;
             a.yout = st < 4 ? (tape ? tv.y(n, st + 1) : ybuf[(st + 1) % 2]) : m;
-            a.tape = tape ? tv.y(n, 1) : nullptr;
             a.tape_n = tape ? (int)tv.N : 0;
             a.stage = st;
             a.dt = (R)dt;

@@ -126,9 +126,9 @@ struct StageArgs {
     const R* mn;       // state m_n at the start of the step
     R* acc;            // running sum of b_s k_s
     R* yout;           // next stage input y_{s+1} (or m_{n+1} at s = 4)
-    R* tape;           // optional: record of the step (28 tape_n elements, see TapeView in magx_api.cpp):
-                       // H_s, |x_{s+1}| before normalisation, y_1 (s = 1), m_{n+1} (s = 4)
-    int tape_n;        // cells of the whole batch with a tape, 0 without
+    int tape_n;        // with a tape: cells of the whole batch, and yout (s = 1) or yin (s > 1) lies in
+                       // the step's record (TapeView in magx_api.cpp), into which the stage writes H_s,
+                       // |x_{s+1}| before normalisation, y_1 (s = 1) and m_{n+1} (s = 4); 0 without
     int stage;         // 1..4, or 0 for a forward Euler step
     R dt;
     int want_next;     // 1: forward x pass of y_{s+1} into X1

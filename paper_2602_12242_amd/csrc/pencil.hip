@@ -2,9 +2,9 @@
 // local to a cell (Section II-A/II-B, Eqs. (1), (2), (5), (7), (9), (10)).
 //
 // A block owns np "pencils" (z, y) and all three components of each: 3*np
-// x lines.  The real transform of length Px = 2^k (>= 2 nx, zero padded) is
-// done as a complex FFT of length Lh = Px/2 on z[n] = x[2n] + i x[2n+1] plus
-// the usual split/merge step, so each thread slot owns a PAIR of cells
+// x lines.  The real transform of length Px >= 2 nx (2^k, 3 2^k or 5 2^k, zero
+// padded) is done as a complex FFT of length Lh = Px/2 on z[n] = x[2n] + i x[2n+1]
+// plus the usual split/merge step, so each thread slot owns a PAIR of cells
 // (2n, 2n+1) and LDS line entries are written whole.
 //
 // Kernels
@@ -210,6 +210,16 @@ __global__ void __launch_bounds__(kNT) field_reduce_kernel(const cx<R>* __restri
     field_body<R, ORD, LN, true, V, false>(Y1, f, H, g, ph, has_demag, with_bias, energy, sum_input, partials);
 }
 
+// Waves per SIMD asked for, where the scalar registers that the tape spills to vector
+// lanes would cost the last one.  Double precision without a profile at run-time and
+// 512-value lines: 129 and 133 vector registers of the 128 of four waves (four steps
+// of 16 systems of 7x23x37 3065 -> 2701 us, of three of 393x44x6 1781 -> 1602).  Single precision with a profile at lines of 80: 86 of the 80 of six
+// (75x150x20 1072 -> 917, whose 1500 blocks are then resident at once; others equal).
+template <typename R, int LN, int V, bool PRE> constexpr int stage_waves() {
+    if (sizeof(R) == 8) return V == 1 && !PRE && (LN == 0 || LN == 512) ? 4 : 1;
+    return V == 0 && LN == 80 ? 6 : 1;
+}
+
 // V: 0 with a magnetisation profile, 1 without.  The plain kernel carries fewer
 // uniform values (the other one spills scalar registers to vector lanes, a lane
 // read each time one is used) and no ghost selects.  The tape is an argument of
@@ -218,8 +228,8 @@ __global__ void __launch_bounds__(kNT) field_reduce_kernel(const cx<R>* __restri
 // PRE (a thread's single cell pair on small systems, see ahead()): the
 // stencil and the RK4 registers are loaded before the inverse x pass.
 template <typename R, int ORD, int LN, int V, bool PRE>
-__global__ void __launch_bounds__(kNT) stage_kernel(const cx<R>* Y1, cx<R>* X1, PG g,
-                                                    Phys<R> ph, StageArgs<R> a, int has_demag) {
+__global__ void __launch_bounds__(kNT, (stage_waves<R, LN, V, PRE>()))
+    stage_kernel(const cx<R>* Y1, cx<R>* X1, PG g, Phys<R> ph, StageArgs<R> a, int has_demag) {
     pg_fix<LN>(g);
     const bool stream = stream_of<ORD>(g);
     extern __shared__ unsigned char smem_raw[];
@@ -234,7 +244,6 @@ __global__ void __launch_bounds__(kNT) stage_kernel(const cx<R>* Y1, cx<R>* X1, 
     a.mn += mo;
     a.acc += mo;
     a.yout += mo;
-    a.tape += mo;
     if constexpr (V == 1) ph.msp = nullptr;
     R hbv[3];
 #pragma unroll
@@ -349,16 +358,17 @@ __global__ void __launch_bounds__(kNT) stage_kernel(const cx<R>* Y1, cx<R>* X1, 
         if (__builtin_expect(a.tape_n != 0, 0)) {
             // (one branch behind the arithmetic: several between its parts cost the untaped step 1 %)
             int stride = a.tape_n;
-            // (double precision: keeps the addresses from being formed ahead of the loop and
-            // held in registers; 5 films of 64x256x1 783 -> 774 us for six steps)
-            if constexpr (sizeof(R) == 8) asm volatile("" : "+s"(stride));
+            // (keeps the addresses from being formed ahead of the loop and held in registers)
+            asm volatile("" : "+s"(stride));
             const long long tn = stride;
-            store_pair32(a.tape + (3 * s + 9) * tn, g.N, off, vec, two, H[0], H[1], stream);
-            if (s == 1) store_pair32(a.tape, g.N, off, vec, two, ys[0], ys[1], stream);
-            R* nx = a.tape + (s + 23) * tn - 2 * mb * g.N + id;   // one value per cell
+            // the record starts with y_1 ... y_4, this stage's input or output among them
+            R* tape = s == 1 ? a.yout - 3 * tn : const_cast<R*>(a.yin) - 3 * (s - 1) * tn;
+            store_pair32(tape + (3 * s + 9) * tn, g.N, off, vec, two, H[0], H[1], stream);
+            if (s == 1) store_pair32(tape, g.N, off, vec, two, ys[0], ys[1], stream);
+            R* nx = tape + (s + 23) * tn - 2 * mb * g.N + id;   // one value per cell
             if (vec) *reinterpret_cast<cx<R>*>(nx) = mk<R>(nrm[0], nrm[1]);
             else { nx[0] = nrm[0]; if (two) nx[1] = nrm[1]; }
-            if (s == 4) store_pair32(a.tape + 28 * tn, g.N, off, vec, two, xn[0], xn[1], stream);
+            if (s == 4) store_pair32(tape + 28 * tn, g.N, off, vec, two, xn[0], xn[1], stream);
         }
         if (fwd) {
             // demag source of the next stage: Ms(r) m = Ms s m
