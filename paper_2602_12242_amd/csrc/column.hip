@@ -119,7 +119,8 @@ __global__ void __launch_bounds__((ColCfg<PY>::NT))
     const unsigned st = (unsigned)st_;
     const unsigned n3 = 3u * (unsigned)nz, nseq = n3 * T;
     const int cpm = Lh / T;                                   // column groups of a member
-    // (the blocks of four columns that share lines are on one XCD)
+    // (most groups of four columns, which share lines, stay on one XCD: its range of
+    // blocks need not end at a group, then two XCDs hold parts of its lines)
     const int lb = xcd_logical_block(blockIdx.x, gridDim.x);
     const int mb = lb / cpm, kx0 = (lb - mb * cpm) * T;
     cx<R>* base = X1 + ((long long)mb * Lh + (kx0 & ~3)) * ny * n3 + (kx0 & 3);
