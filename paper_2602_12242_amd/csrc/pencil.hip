@@ -86,8 +86,7 @@ __global__ void __launch_bounds__(kNT) xfwd_kernel(const R* __restrict__ f, cx<R
 // which keeps it within the registers of five waves per SIMD.
 // V: 0 the general kernel, 1 without a magnetisation profile (energies, whose
 // densities the plain local field does not split, are general).
-// PRE: the stencil of a thread's single cell pair is loaded before the inverse x pass.
-template <typename R, int ORD, int LN, bool RED, int V, bool PRE>
+template <typename R, int ORD, int LN, bool RED, int V>
 __device__ __forceinline__ void field_body(const cx<R>* __restrict__ Y1, const R* __restrict__ f,
                                            R* __restrict__ H, PG g, Phys<R> ph, int has_demag,
                                            int with_bias, int energy, int sum_input,
@@ -114,16 +113,6 @@ __device__ __forceinline__ void field_body(const cx<R>* __restrict__ Y1, const R
 #pragma unroll
     for (int c = 0; c < 3; ++c) hbv[c] = ph.hbm ? ph.hbm[mb * 3 + c] : ph.hb[c];
     const bool vec = (g.nx & 1) == 0;
-    Stencil<R> t;
-    if constexpr (PRE) {
-        int p, n, y, z;
-        slot_of<LN>(g, threadIdx.x, p, n);
-        if ((int)threadIdx.x < slots_of<LN>(g, npen) && 2 * n < g.nx) {
-            pen_coords<R>(g, pen0 + p, y, z);
-            const unsigned id = (unsigned)(pen0 + p) * (unsigned)g.nx + (unsigned)(2 * n);
-            stencil_load<R>(t, f, g, 2 * n, y, z, id * (unsigned)sizeof(R), vec, 2 * n + 1 < g.nx, ph.terms);
-        }
-    }
     if (has_demag) c2r_lines<R, ORD, LN>(buf, Y1, g, mb, pen0, npen);
     double acc[6] = {0, 0, 0, 0, 0, 0};
     for (int e = threadIdx.x; e < slots_of<LN>(g, npen); e += kNT) {
@@ -137,7 +126,8 @@ __device__ __forceinline__ void field_body(const cx<R>* __restrict__ Y1, const R
         const unsigned id = (unsigned)(pen0 + p) * (unsigned)g.nx + (unsigned)x0;
         R m[2][3], hl[2][3], ex[2], dm[2], an[2], out[2][3], sw[2] = {(R)1, (R)1};
         if constexpr (V > 0) {
-            local_field_plain<R, PRE>(t, f, g, x0, y, z, id * (unsigned)sizeof(R), vec, two, ph, hl);
+            Stencil<R> t;
+            local_field_plain<R>(t, f, g, x0, y, z, id * (unsigned)sizeof(R), vec, two, ph, hl);
 #pragma unroll
             for (int q = 0; q < 2; ++q)
 #pragma unroll
@@ -194,12 +184,12 @@ __device__ __forceinline__ void field_body(const cx<R>* __restrict__ Y1, const R
     }
 }
 
-template <typename R, int ORD, int LN, int V, bool PRE>
+template <typename R, int ORD, int LN, int V>
 __global__ void __launch_bounds__(kNT) field_kernel(const cx<R>* __restrict__ Y1, const R* __restrict__ f,
                                                     R* __restrict__ H, PG g, Phys<R> ph, int has_demag,
                                                     int with_bias, int energy, int sum_input,
                                                     double* __restrict__ partials) {
-    field_body<R, ORD, LN, false, V, PRE>(Y1, f, H, g, ph, has_demag, with_bias, energy, sum_input, partials);
+    field_body<R, ORD, LN, false, V>(Y1, f, H, g, ph, has_demag, with_bias, energy, sum_input, partials);
 }
 
 template <typename R, int ORD, int LN, int V>
@@ -207,7 +197,7 @@ __global__ void __launch_bounds__(kNT) field_reduce_kernel(const cx<R>* __restri
                                                            R* __restrict__ H, PG g, Phys<R> ph, int has_demag,
                                                            int with_bias, int energy, int sum_input,
                                                            double* __restrict__ partials) {
-    field_body<R, ORD, LN, true, V, false>(Y1, f, H, g, ph, has_demag, with_bias, energy, sum_input, partials);
+    field_body<R, ORD, LN, true, V>(Y1, f, H, g, ph, has_demag, with_bias, energy, sum_input, partials);
 }
 
 // Waves per SIMD asked for, where the scalar registers that the tape spills to vector
@@ -744,16 +734,21 @@ constexpr int kOrder = MAGX_COLS ? kColumns : kRows;
     } while (0)
 
 // Loads ahead of the inverse x pass: at most one cell pair per thread and at most
-// 64 blocks per system, where nothing else hides the second wait for memory: 10
-// RK4 steps at 128x32x1 in double precision 616 -> 577 us, 16 such films in
-// single precision 722 -> 706.  The line depends on the system alone, since a
-// member of a batch gets the bits of a single system and the two kernels round
-// differently (fused multiply-adds); it lies this low for the batches: the
-// registers (74 -> 117 in single precision) cost a full GPU more than the wait,
-// 24 systems of 128x128x2 5491 -> 5943 us with it, 64 films 1607 -> 1616, while
-// one 128x128x2 system would gain 2 %.
+// 64 blocks per system, where nothing else hides the second wait for memory (ten
+// RK4 steps at 128x32x1 in double precision 576 -> 544 us), and only while every
+// block of the launch is resident: they take 117-140 vector registers of 70-90 in
+// single precision and 216-241 of 127-143 in double, so 1024 blocks (768 at odd
+// lines from 96 values on) and 512 fit on the card.  Four RK4 steps, us, without /
+// with them: 16 films of 128x32x1 241/230, 8 of 64x64x1 in double precision
+// 290/279; beyond the line 32 films of 8x35x1 296/328 and 16 of 150x60x1 349/431,
+// in double precision 16 of 8x35x1 278/334 and 32 of 33x20x3 689/928.  A member of
+// a batch has to get the bits of a single system across that line: the stage's two
+// instances round alike.  (The field kernel's did not, and gained nothing.)
 // (np Lh / 2 <= 256: lines of at most 512 values.)
-static bool ahead(const Plan& pl) { return pl.blocks_per_member <= 64 && pl.np * std::max(1, pl.Lh / 2) <= kNT; }
+static bool ahead(const Plan& pl) {
+    const int resident = pl.esize == 8 ? 512 : (odd_part(pl.Lh) > 1 && pl.Lh > 80 ? 768 : 1024);
+    return pl.blocks_per_member <= 64 && pl.pencil_blocks <= resident && pl.np * std::max(1, pl.Lh / 2) <= kNT;
+}
 
 template <typename R, bool COLS>
 hipError_t launch_xfwd_in(const Plan& pl, const R* f, void* X1, const R* msp, hipStream_t s) {
@@ -771,12 +766,10 @@ hipError_t launch_field_in(const Plan& pl, const Phys<R>& ph, const void* Y1, co
         MAGX_PENCIL_LAUNCH(field_reduce_kernel, (, 0), y, f, H, g, ph, has_demag, with_bias, energy, sum_input, partials);
     else if (sum_input)
         MAGX_PENCIL_LAUNCH(field_reduce_kernel, (, 1), y, f, H, g, ph, has_demag, with_bias, energy, sum_input, partials);
-    else if (!ph.msp && ahead(pl))
-        MAGX_PENCIL_LAUNCH_AHEAD(field_kernel, (, 1, true), y, f, H, g, ph, has_demag, with_bias, energy, sum_input, partials);
     else if (!ph.msp)
-        MAGX_PENCIL_LAUNCH(field_kernel, (, 1, false), y, f, H, g, ph, has_demag, with_bias, energy, sum_input, partials);
+        MAGX_PENCIL_LAUNCH(field_kernel, (, 1), y, f, H, g, ph, has_demag, with_bias, energy, sum_input, partials);
     else
-        MAGX_PENCIL_LAUNCH(field_kernel, (, 0, false), y, f, H, g, ph, has_demag, with_bias, energy, sum_input, partials);
+        MAGX_PENCIL_LAUNCH(field_kernel, (, 0), y, f, H, g, ph, has_demag, with_bias, energy, sum_input, partials);
     return hipGetLastError();
 }
 

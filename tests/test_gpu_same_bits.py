@@ -104,3 +104,38 @@ def test_taped_steps_equal_untaped(n, dtype, profile):
         ctx.step(a, p, DT, steps)
         ctx.step(b, p, DT, steps, tape=ctx.tape(steps))
         assert torch.equal(a, b), steps
+
+
+# enough members that the stage kernels of the batch are those of a full card, without
+# loads ahead of the inverse x pass: (grid, members in single and in double precision)
+FULL = [((8, 35, 1), 32, 16), ((128, 32, 1), 40, 20), ((33, 20, 3), 20, 10), ((90, 20, 3), 16, 12), ((37, 11, 5), 20, 11),
+        ((250, 30, 2), 20, 10)]
+TERMS = [(31, 2), (31, 0), (1, 2), (3, 1), (2, 2), (4 | 2, 2), (1 | 8, 0), (16, 2)]
+
+
+@pytest.mark.parametrize("n,b32,b64", FULL)
+@pytest.mark.parametrize("dtype", [0, 1])
+@pytest.mark.parametrize("terms,renorm", TERMS)
+def test_members_of_full_batches_equal_single_systems(n, b32, b64, dtype, terms, renorm):
+    from paper_2602_12242_amd import magx
+    B, N = (b32, b64)[dtype], n[0] * n[1] * n[2]
+    p = magx.make_params(renorm=renorm, **{**MAT, "terms": terms})
+    one, many = magx.Context(n, D, dtype=dtype), magx.Context(n, D, dtype=dtype, nbatch=B)
+    m = torch.stack([torch.from_numpy(random_unit_field(n, 910 + b, 2)) for b in range(B)]).to("cuda", one.tdtype)
+    g = torch.stack([torch.from_numpy(random_vector_field(n, 950 + b)) for b in range(B)]).to("cuda", one.tdtype)
+
+    def outputs(ctx, m, g):
+        out, tape, lam = [ctx.heff(m, p)], ctx.tape(1), g.clone()
+        for call in (lambda y: ctx.step(y, p, DT, 3), lambda y: ctx.step_euler(y, p, 0.1 * DT, 2),
+                     lambda y: ctx.step(y, p, DT, 1, tape=tape)):
+            out.append(m.clone())
+            call(out[-1])
+        tn = N * ctx.nbatch
+        out.append(tape.view(ctx.tdtype)[12 * tn:24 * tn].view((4,) + ctx.shape).movedim(0, -5))      # H_1 ... H_4
+        ctx.step_backward(tape, 1, p, DT, lam, torch.zeros(ctx.lead + (3,), dtype=ctx.tdtype, device="cuda"))
+        return out + [lam]
+
+    got = outputs(many, m, g)
+    for b in (0, B // 2, B - 1):
+        for k, (x, y) in enumerate(zip(outputs(one, m[b].contiguous(), g[b].contiguous()), got)):
+            assert torch.equal(x, y[b]), (b, k)
