@@ -113,6 +113,7 @@ __device__ __forceinline__ void field_body(const cx<R>* __restrict__ Y1, const R
 #pragma unroll
     for (int c = 0; c < 3; ++c) hbv[c] = ph.hbm ? ph.hbm[mb * 3 + c] : ph.hb[c];
     const bool vec = (g.nx & 1) == 0;
+    Stencil<R> t;
     if (has_demag) c2r_lines<R, ORD, LN>(buf, Y1, g, mb, pen0, npen);
     double acc[6] = {0, 0, 0, 0, 0, 0};
     for (int e = threadIdx.x; e < slots_of<LN>(g, npen); e += kNT) {
@@ -126,7 +127,6 @@ __device__ __forceinline__ void field_body(const cx<R>* __restrict__ Y1, const R
         const unsigned id = (unsigned)(pen0 + p) * (unsigned)g.nx + (unsigned)x0;
         R m[2][3], hl[2][3], ex[2], dm[2], an[2], out[2][3], sw[2] = {(R)1, (R)1};
         if constexpr (V > 0) {
-            Stencil<R> t;
             local_field_plain<R>(t, f, g, x0, y, z, id * (unsigned)sizeof(R), vec, two, ph, hl);
 #pragma unroll
             for (int q = 0; q < 2; ++q)
