@@ -128,11 +128,21 @@ static int pow2_floor(long long v) {
 // 512x128x1 225/153, 1000x64x1 265/202 265/234, 40x14x1 127/119 135/122.
 // More than 512 rows leave fewer registers per thread; lines of more than 1024
 // values have no pencil kernels in this order.
+// A block is one column (of 160 rows and more), a chain of phases: where it is
+// longest, a system of few columns leaves the card idle.  Four RK4 steps, us, three
+// kernels / one: in double precision at 640 rows and eight values along z 14x380x4
+// 554/943, 24x380x4 753/994, 40x380x4 883/1043 (eight systems of 24x380x4 2164/1566);
+// in single precision at 256 rows and seven or eight planes 16x100x8 415/549, 40x100x8
+// 495/588, 70x100x8 451/559 (six planes 40x100x6 524/533, five 510/478).  The line lies
+// where a system alone was slower than by three kernels at powers of two (24x380x4 939,
+// 40x380x4 1144, 40x100x8 565, 70x100x8 609); batches below it are slower for it.
 static int column_plan(const Plan& p) {
     const bool f32 = p.esize == 4;
     if (p.Py < 32 || p.Py > 1024 || p.Lh < 16 || p.Lh % 4 != 0 || p.Lh > 1024) return 0;
     const int maxPz = f32 ? (p.Py == 256 || p.Py == 512 ? 16 : 8) : (p.Py <= 768 ? 8 : 4);
     if (p.Pz > maxPz || 12LL * p.ny * p.nz >= (1LL << 24)) return 0;   // (24-bit stride of kx in the x passes)
+    const int few = f32 ? (p.Py == 256 && p.nz > 6 ? 64 : 0) : (p.Py >= 640 && p.Pz == 8 ? 32 : 0);
+    if (p.Lh <= few) return 0;
     return (long long)((3 * p.nz * column_width(p.Py)) | 1) * p.Py * 2 * p.esize <= kColumnLds ? 1 : 0;
 }
 

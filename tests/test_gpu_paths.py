@@ -51,8 +51,17 @@ def _columns():
                     continue      # (other columns of nine and more values along z take the passes)
                 if dtype == 1 and Py == 1024 and Pz == 8:
                     continue
-                yield Py, Pz, dtype, (9, Py // 2, Pz // 2)
-                yield Py, Pz, dtype, (20, low, Pz // 4 + 1 if Pz > 2 else 1)
+                # (the longest chains only from 33 and 65 cells along x on, see FEW)
+                few = 70 if (Py, Pz) == (256, 16) else (40 if dtype == 1 and Pz == 8 and Py >= 640 else 0)
+                yield Py, Pz, dtype, (max(9, few), Py // 2, Pz // 2)
+                yield Py, Pz, dtype, (max(20, few), low, Pz // 4 + 1 if Pz > 2 else 1)
+
+
+# both sides of the line below which a system has too few columns for the column
+# convolution
+FEW = [((32, 257, 3), 1, "passes"), ((33, 257, 3), 1, "column"), ((9, 384, 4), 1, "passes"), ((33, 384, 4), 1, "column"),
+       ((9, 256, 4), 1, "column"), ((64, 97, 7), 0, "passes"), ((65, 97, 7), 0, "column"), ((9, 128, 8), 0, "passes"),
+       ((16, 128, 6), 0, "column"), ((9, 129, 8), 0, "passes"), ((9, 250, 8), 0, "column")]
 
 
 def _path(ctx, m, p):
@@ -129,6 +138,12 @@ def test_line_lengths_in_both_orders(nx, Lh, order, dtype):
 def test_lengths_of_the_y_passes(ny, Py, dtype):
     n = (10, ny, 5)
     ctx, q = _context(n, dtype, "passes", (32, Py, 16))
+    _parity(ctx, q, n, dtype)
+
+
+@pytest.mark.parametrize("n,dtype,path", FEW)
+def test_few_columns(n, dtype, path):
+    ctx, q = _context(n, dtype, path, (None, None, None))
     _parity(ctx, q, n, dtype)
 
 
