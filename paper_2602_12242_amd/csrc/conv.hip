@@ -8,8 +8,9 @@
 //           are zero padding), then the pointwise product with the real
 //           symmetric tensor spectrum, H_a = -Ms sum_b N_ab M_b (tensor values
 //           held in registers), then the inverse z FFT; only rows z < nz are
-//           written back (in place).  Single precision with Pz = 8 ... 64
-//           has a register-resident variant (zconvr).
+//           written back (in place).  Register-resident variants: zconvr
+//           (single precision, Pz = 8 ... 64), zconvr128 and zconvd (double,
+//           Pz = 16 ... 128).
 //  * yinv : inverse y FFT; only rows y < ny (inside the box) are written.
 // FFT pass twiddles come from a two-level LDS table filled by each block.
 // yfwd, zconv and yinv write their outputs with streaming stores, and yinv

@@ -82,8 +82,9 @@ __global__ void __launch_bounds__(kNT) xfwd_kernel(const R* __restrict__ f, cx<R
 
 // mode: 0 -> write H (with bias if with_bias); 1 -> energy partials (m.H_term).
 // RED: the block sums (energy, or the sum of the input field) are wanted; the
-// plain field evaluation is a kernel of its own without their accumulators,
-// which keeps it within the registers of five waves per SIMD.
+// plain field evaluation is a kernel of its own without their accumulators: 63
+// registers without a profile and 75 with one at 512-value lines in single
+// precision, 95 with a profile and sums (five waves per SIMD).
 // V: 0 the general kernel, 1 without a magnetisation profile (energies, whose
 // densities the plain local field does not split, are general).
 template <typename R, int ORD, int LN, bool RED, int V>

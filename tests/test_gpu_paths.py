@@ -2,7 +2,8 @@
 the three passes (forward y, z product, inverse y) or one kernel in their place (the
 column convolution, whose spectrum ends with a copy of the tensor in its own order, or
 the film kernel).  Every grid names its path and extended lengths, so that a change of
-a rule cannot take a kernel out of the tests unseen.
+a rule cannot take a kernel out of the tests unseen; grids of other tests state only
+what they compute, and take whichever kernels the rules give them.
 
 Bars as in test_gpu_parity.py: double precision 1e-11, single precision 1e-5 (ten
 times that for the step's reverse mode)."""
