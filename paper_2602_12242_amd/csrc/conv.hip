@@ -132,8 +132,10 @@ __device__ __forceinline__ unsigned nyq_pack(int ky, int Py, unsigned Sx) {
     return (unsigned)prow * Sx + (unsigned)(q & 15);
 }
 
+// (double precision, runtime length: 175 registers of the 168 of three waves per SIMD
+// unless they are asked for; eight systems of 208x29x5 16.5 -> 12.6 us)
 template <typename R, int PY, bool SQ>
-__global__ void __launch_bounds__((YCfg<R, PY>::NT))
+__global__ void __launch_bounds__((YCfg<R, PY>::NT), (sizeof(R) == 8 && PY == 0 ? 3 : 1))
     yfwd_kernel(const cx<R>* __restrict__ X1, cx<R>* __restrict__ X2, int ny, int lgPy, int Hx, int Sx, int lgT,
                 int ntx, int ntiles, int nyq) {
     constexpr int EM = YCfg<R, PY>::EM, NT = YCfg<R, PY>::NT, LGM = YCfg<R, PY>::LGM, ODD = YCfg<R, PY>::ODD;
