@@ -70,8 +70,8 @@ struct PairWalk {
 // EM and log2 of the largest radix.  The length is a compile-time constant for
 // PY >= 128 (PY = 0 keeps runtime sizes, powers of two up to 64), so the pass
 // plan is straight-line code: with a runtime length the switch over the first
-// radix spilled 69-101 scalar registers into scratch memory.  Lengths with an
-// odd factor take a thread count that divides their butterflies evenly
+// radix spilled 69-101 scalar registers into scratch memory (but see long_walk).  Lengths
+// with an odd factor take a thread count that divides their butterflies evenly
 // (radices 4 8 5 at 160, 8 8 x at 192 and 320, 8 16 x at 384 and 640, 16 16 3 at 768).
 template <typename R, int PY> struct YCfg {
     static constexpr bool F = sizeof(R) == 4;
@@ -99,11 +99,12 @@ template <typename R, int PY> struct YCfg {
     static constexpr int LGM = ODD == 1 ? lgmax<EM>() : (LG >= 7 ? 4 : 3);
 };
 
-// Compile-time sizes of a y pass.  SQ: square power-of-two grids nx = ny = PY/2
-// (Px = Py): the row stride and the tile count are constants as well.
-template <typename R, int PY, bool SQ>
+// Compile-time sizes of a y pass (RT: runtime ones all the same).  SQ: square
+// power-of-two grids nx = ny = PY/2 (Px = Py): the row stride and the tile count are
+// constants as well.
+template <typename R, int PY, bool SQ, bool RT = false>
 __device__ __forceinline__ void ygeom_fix(int& ny, int& lgPy, int& Hx, int& Sx, int& lgT, int& ntx) {
-    if constexpr (PY > 0) {
+    if constexpr (PY > 0 && !RT) {
         lgPy = YCfg<R, PY>::LG;
         lgT = ilog2c(YCfg<R, PY>::T);
     }
@@ -134,12 +135,12 @@ __device__ __forceinline__ unsigned nyq_pack(int ky, int Py, unsigned Sx) {
 
 // (double precision, runtime length: 175 registers of the 168 of three waves per SIMD
 // unless they are asked for; eight systems of 208x29x5 16.5 -> 12.6 us)
-template <typename R, int PY, bool SQ>
+template <typename R, int PY, bool SQ, bool RT = false>
 __global__ void __launch_bounds__((YCfg<R, PY>::NT), (sizeof(R) == 8 && PY == 0 ? 3 : 1))
     yfwd_kernel(const cx<R>* __restrict__ X1, cx<R>* __restrict__ X2, int ny, int lgPy, int Hx, int Sx, int lgT,
                 int ntx, int ntiles, int nyq) {
     constexpr int EM = YCfg<R, PY>::EM, NT = YCfg<R, PY>::NT, LGM = YCfg<R, PY>::LGM, ODD = YCfg<R, PY>::ODD;
-    ygeom_fix<R, PY, SQ>(ny, lgPy, Hx, Sx, lgT, ntx);
+    ygeom_fix<R, PY, SQ, RT>(ny, lgPy, Hx, Sx, lgT, ntx);
     tw_lds_fill<R, ODD>();   // read by the second pass, after the first barrier
     extern __shared__ unsigned char smem_raw[];
     cx<R>* buf = reinterpret_cast<cx<R>*>(smem_raw);
@@ -191,12 +192,12 @@ __global__ void __launch_bounds__((YCfg<R, PY>::NT), (sizeof(R) == 8 && PY == 0 
     }
 }
 
-template <typename R, int PY, bool SQ>
+template <typename R, int PY, bool SQ, bool RT = false>
 __global__ void __launch_bounds__((YCfg<R, PY>::NT))
     yinv_kernel(const cx<R>* __restrict__ X2, cx<R>* __restrict__ Y1, int ny, int lgPy, int Hx, int Sx, int lgT,
                 int ntx, int ntiles, int nyq) {
     constexpr int EM = YCfg<R, PY>::EM, NT = YCfg<R, PY>::NT, LGM = YCfg<R, PY>::LGM, ODD = YCfg<R, PY>::ODD;
-    ygeom_fix<R, PY, SQ>(ny, lgPy, Hx, Sx, lgT, ntx);
+    ygeom_fix<R, PY, SQ, RT>(ny, lgPy, Hx, Sx, lgT, ntx);
     tw_lds_fill<R, ODD>();   // read by the second pass, after the first barrier
     extern __shared__ unsigned char smem_raw[];
     cx<R>* buf = reinterpret_cast<cx<R>*>(smem_raw);
@@ -1244,7 +1245,7 @@ static int pair_grid(int resident, long long nunits) {
     return (int)g;
 }
 
-template <typename R, int PY, bool SQ = false>
+template <typename R, int PY, bool SQ = false, bool RT = false>
 static hipError_t run_yfwd(const Plan& pl, const void* X1, void* X2, hipStream_t s) {
     constexpr int NT = YCfg<R, PY>::NT;
     if (PY ? (pl.Py != PY || pl.ty != YCfg<R, PY>::T) : (pl.Py * pl.ty > NT * YCfg<R, 0>::EM))
@@ -1253,16 +1254,16 @@ static hipError_t run_yfwd(const Plan& pl, const void* X1, void* X2, hipStream_t
     const int ntx = (pl.Hx + pl.ty - 1) / pl.ty;
     const int ntiles = ntx * 3 * pl.nz * pl.nbatch;
     const size_t lds = (size_t)pl.Py * pl.ty * sizeof(cx<R>);
-    const int grid = pair_grid(persistent_grid(reinterpret_cast<const void*>(&yfwd_kernel<R, PY, SQ>), lds,
+    const int grid = pair_grid(persistent_grid(reinterpret_cast<const void*>(&yfwd_kernel<R, PY, SQ, RT>), lds,
                                                1LL << 30, NT),
                                (long long)(ntiles / ntx) * ((ntx + 1) / 2));
     if (grid < 2) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((yfwd_kernel<R, PY, SQ>), dim3(grid), dim3(NT), lds, s, static_cast<const cx<R>*>(X1),
+    hipLaunchKernelGGL((yfwd_kernel<R, PY, SQ, RT>), dim3(grid), dim3(NT), lds, s, static_cast<const cx<R>*>(X1),
                        static_cast<cx<R>*>(X2), pl.ny, pl.lgPy, pl.Hx, pl.Sx, lgT, ntx, ntiles, pl.nyqpack);
     return hipGetLastError();
 }
 
-template <typename R, int PY, bool SQ = false>
+template <typename R, int PY, bool SQ = false, bool RT = false>
 static hipError_t run_yinv(const Plan& pl, const void* X2, void* Y1, hipStream_t s) {
     constexpr int NT = YCfg<R, PY>::NT;
     if (PY ? (pl.Py != PY || pl.ty != YCfg<R, PY>::T) : (pl.Py * pl.ty > NT * YCfg<R, 0>::EM))
@@ -1271,11 +1272,11 @@ static hipError_t run_yinv(const Plan& pl, const void* X2, void* Y1, hipStream_t
     const int ntx = (pl.Hx + pl.ty - 1) / pl.ty;
     const int ntiles = ntx * 3 * pl.nz * pl.nbatch;
     const size_t lds = (size_t)pl.Py * pl.ty * sizeof(cx<R>);
-    const int grid = pair_grid(persistent_grid(reinterpret_cast<const void*>(&yinv_kernel<R, PY, SQ>), lds,
+    const int grid = pair_grid(persistent_grid(reinterpret_cast<const void*>(&yinv_kernel<R, PY, SQ, RT>), lds,
                                                1LL << 30, NT),
                                (long long)(ntiles / ntx) * ((ntx + 1) / 2));
     if (grid < 2) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((yinv_kernel<R, PY, SQ>), dim3(grid), dim3(NT), lds, s, static_cast<const cx<R>*>(X2),
+    hipLaunchKernelGGL((yinv_kernel<R, PY, SQ, RT>), dim3(grid), dim3(NT), lds, s, static_cast<const cx<R>*>(X2),
                        static_cast<cx<R>*>(Y1), pl.ny, pl.lgPy, pl.Hx, pl.Sx, lgT, ntx, ntiles, pl.nyqpack);
     return hipGetLastError();
 }
@@ -1331,15 +1332,30 @@ static bool y_square(const Plan& pl) {
         default: return RUN<R, 0>(__VA_ARGS__);                                                       \
     }
 
+// Length 4096 (tiles of two or four columns): with a constant length the passes of a
+// block that walks many tiles are slower than with a runtime one, us, constant / runtime
+// in double precision 255x1098x6 (2322 tiles) forward 311/294, inverse 291/264, in single
+// 488x1124x12 (4644) forward 641/584, inverse the same; few tiles are faster with the
+// constant: a field of 100x2000x5 in double precision (975) 458/464, of 60x1500x1 (99)
+// 116/121, of 100x1300x9 in single (891) 371/382.  Six tiles per block on 256 CUs, of
+// one system, since the two may round differently.
+static bool long_walk(const Plan& pl) {
+    return pl.Py == 4096 && 3LL * pl.nz * ((pl.Hx + pl.ty - 1) / pl.ty) > 6 * 256;
+}
+
 template <typename R>
 hipError_t launch_yfwd(const Plan& pl, const void* X1, void* X2, hipStream_t s) {
     if (pl.Py == 2048) return run_y2<R, false>(pl, X1, X2, s);
+    if (long_walk(pl)) return run_yfwd<R, 4096, false, true>(pl, X1, X2, s);
     MAGX_Y_SWITCH(run_yfwd, pl, X1, X2, s)
 }
 
 template <typename R>
 hipError_t launch_yinv(const Plan& pl, const void* X2, void* Y1, hipStream_t s) {
     if (pl.Py == 2048) return run_y2<R, true>(pl, X2, Y1, s);
+    if constexpr (sizeof(R) == 8) {
+        if (long_walk(pl)) return run_yinv<R, 4096, false, true>(pl, X2, Y1, s);
+    }
     MAGX_Y_SWITCH(run_yinv, pl, X2, Y1, s)
 }
 

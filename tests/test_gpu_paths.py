@@ -226,3 +226,25 @@ def test_masked_steps_at_odd_lines(n, path, dtype):
         y = y.cpu().numpy()
         assert np.all(y[:, s == 0] == 0.0)
         assert _err(y, ref) <= tol
+
+
+# 4096 rows: both sides of the line between constant and runtime length of the y passes
+# (1536 tiles of two columns in double, four in single precision), against a padded
+# convolution in double precision with the stored tensor
+@pytest.mark.parametrize("n,dtype", [((17, 1030, 30), 1), ((17, 1030, 32), 1), ((17, 1030, 56), 0), ((17, 1030, 57), 0)])
+def test_long_columns(n, dtype):
+    from paper_2602_12242_amd import magx
+    q = magx.make_params(**{**MAT, "terms": 1})
+    ctx, m = magx.Context(n, D, dtype=dtype), _dev(random_unit_field(n, 955), dtype)
+    assert ctx.extended_lengths()[1] == 4096
+    arr, (Px, Py, Pz) = (ctx if dtype == 1 else magx.Context(n, D, dtype=1)).spectrum_array()
+    ky, kz = (torch.arange(P, device="cuda") for P in (Py, Pz))
+    t = arr[:, torch.minimum(kz, Pz - kz)][:, :, torch.minimum(ky, Py - ky)]
+    sy, sz = (torch.where(k <= P // 2, 1.0, -1.0).double() for k, P in ((ky, Py), (kz, Pz)))
+    sy, sz = sy[None, :, None], sz[:, None, None]
+    xx, yy, zz, xy, xz, yz = t[0], t[1], t[2], sy * t[3], sz * t[4], sy * sz * t[5]
+    M = torch.fft.rfftn(m.double(), s=(Pz, Py, Px), dim=(1, 2, 3))
+    rows = ((xx, xy, xz), (xy, yy, yz), (xz, yz, zz))
+    ref = torch.stack([torch.fft.irfftn(sum(a * b for a, b in zip(r, M)), s=(Pz, Py, Px), norm="forward") for r in rows])
+    ref = (-MAT["Ms"] * ref[:, : n[2], : n[1], : n[0]]).cpu().numpy()
+    assert _err(ctx.heff(m, q).cpu().numpy(), ref) <= (1e-11 if dtype == 1 else 1e-5)
